@@ -8,6 +8,8 @@
 // of per-block partials.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "nn.h"
 #include "tiles.h"
 
@@ -32,21 +34,20 @@ __device__ __forceinline__ unsigned short f2bf(float f)
     return (unsigned short)(u >> 16);
 }
 
+// Two values rounded to nearest even in one instruction (a in the low half).
+__device__ __forceinline__ unsigned f2bf2(float a, float b)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+
 __device__ __forceinline__ float bf2f(unsigned short h) { return __uint_as_float(unsigned(h) << 16); }
 
 __device__ __forceinline__ int wrap(int v, int n)
 {
     v %= n;
     return v < 0 ? v + n : v;
-}
-
-// Periodic wrap for an index that is at most one period out of range (the
-// general modulo only when it is not, i.e. on lattices smaller than a tile).
-__device__ __forceinline__ int wrap_near(int v, int n)
-{
-    v += v < 0 ? n : 0;
-    v -= v >= n ? n : 0;
-    return (v >= 0 && v < n) ? v : wrap(v, n);
 }
 
 __device__ __forceinline__ void tile_origin(const Grid3 &g, int t, int &x0, int &y0, int &z0)
@@ -57,51 +58,9 @@ __device__ __forceinline__ void tile_origin(const Grid3 &g, int t, int &x0, int 
     z0 = (r / g.ty) * TZs;
 }
 
-// Forward-style periodic 3x3x3 convolution of a CIN-channel activation into
-// COUT channels, as an implicit GEMM on v_mfma_f32_16x16x32_bf16: M = 16
-// output channels, N = 16 sites of one x-row, K = 32 (the CIN = 32 channels of
-// one tap, or the 16 channels of two taps when CIN = 16).
-//
-// One block of 8 waves per CU owns a tile of 16 x (WY RY) x (WZ RZ) = 16 x 8
-// x 4 output sites at a time; its input brick (tile plus a one-site periodic
-// halo, 69 KB for 32 channels) is staged in LDS, and the brick of the block's
-// next tile is fetched into registers while the current one is computed.
-// The layer's weights, pre-arranged in MFMA fragment order (k_wprep, 55 KB
-// for 32 -> 32), are staged in LDS once per block, so the per-kstep fragment
-// reads (one kstep ahead) are LDS reads.  Each wave owns 16 x RY x RZ output
-// sites with all COUT channels in its accumulators; for each x-offset of the
-// stencil it reads the (RY+2)(RZ+2) brick rows it needs into registers once
-// and runs all nine (y, z) taps of that offset against them.  Blocks take
-// contiguous runs of tiles, and the block index is remapped so that each XCD
-// (with its own L2) works on one contiguous part of the lattice.
-//
-// Epilogues:
-//  MODE_RELU:   out_bf16[s][co] = bf16(relu(acc + b[co])), 0 for co >= co_valid
-//  MODE_LINEAR: out_f32[s][co]  = acc + b[co] for co < co_valid (row stride co_valid)
-//  MODE_MASK:   out_bf16[s][co] = mask[s][co] > 0 ? bf16(acc) : 0   (backward through ReLU)
-//  MODE_RAW:    out_f32[s][co]  = acc (row stride COUT)
+// K = 32 slices of the nine (y, z) taps of one x-offset, times three: the 32
+// input channels of one tap, or the 16 channels of two taps.
 constexpr int nksteps(int cin) { return cin == 32 ? 27 : 15; }
-
-template <int CIN, int COUT, int RY, int RZ, int WY, int WZ>
-struct ConvShape {
-    static constexpr int NS = COUT / 16, NKS = nksteps(CIN), KPD = NKS / 3;
-    static constexpr int TY = WY * RY, TZ = WZ * RZ;              // block tile: 16 x TY x TZ
-    static constexpr int BX = 18, BY = TY + 2, BZ = TZ + 2;       // brick
-    static constexpr int BN = BX * BY * BZ;
-    static constexpr int V = CIN / 8;                             // 16-byte chunks per site
-    static constexpr int NCH = (BN * V + BLK - 1) / BLK;          // chunks staged per thread
-    static constexpr size_t lds_bytes = size_t(BN) * CIN * 2;
-};
-
-// LDS position (in 16-byte chunks) of chunk v of brick site `site`: sites
-// are unpadded and the chunk index is XOR-swizzled with the site so that the
-// 16 lanes of a quarter-wave reading one chunk of 16 consecutive sites hit
-// 16 different bank groups.
-template <int V>
-__device__ __forceinline__ int brick_chunk(int site, int v)
-{
-    return site * V + (v ^ ((site / (16 / V)) % V));
-}
 
 // Weight gradient dW[tap][ci][co] = sum_s dZ[s][co] X[s + off(tap)][ci] and
 // bias gradient db[co] = sum_s dZ[s][co] on v_mfma_f32_16x16x32_bf16: per
@@ -674,190 +633,288 @@ int device_cus()
     return cus;
 }
 
-// One block of WBLK threads (8 waves) per CU.
+// Forward-style periodic 3x3x3 convolution of a CIN-channel activation into
+// COUT channels, as an implicit GEMM on v_mfma_f32_16x16x32_bf16: M = 16
+// output channels, N = 16 sites of one x-row, K = 32 (the CIN = 32 channels of
+// one tap, or the 16 channels of two taps when CIN = 16).
+//
+// One block of 8 waves per CU takes a run of tiles of 16 x 8 x 4 output sites.
+// A wave owns one block of 16 output channels and a sub-tile of 16 x RY x RZ
+// sites, and holds the weights of its output channels (27 k-steps, 108
+// registers for 32 inputs) for all its tiles, so LDS carries the input rows
+// only: every row read (16 sites, one x-offset) feeds up to RY' RZ' = 6 of the
+// wave's accumulators.  With the weights in LDS, as this kernel had them
+// before, a k-step's weight and row reads took as long as its MFMAs.
+// The input brick of a tile (tile plus a one-site periodic halo, 69 KB for 32
+// channels) is copied from global memory straight into one of two LDS
+// buffers while the tile before it is computed, so no registers hold it and a
+// tile takes one barrier.
+//
+// Bound: the matrix cores, 46.7k cycles of MFMAs per SIMD and layer at 96^3
+// of about 77k cycles a wave lives (19 of 32 us; the kernel takes 42 us with
+// its launch and the write-back of its output, 1.16 PFLOP/s, against 62-72 us
+// before; 32 -> 16: 28 against 45 us).  The rest is the start of a block (its
+// weights and first brick) and the epilogues, which the two waves of a SIMD
+// reach together.  Nontemporal output stores measured 2% slower.
+//
+// Every output accumulates its taps x-offset major, then (z, y), in one chain
+// of MFMAs, whatever the sub-tile.
+//
+// Epilogues:
+//  MODE_RELU:   out_bf16[s][co] = bf16(relu(acc + b[co])), 0 for co >= co_valid
+//  MODE_LINEAR: out_f32[s][co]  = acc + b[co] for co < co_valid (row stride co_valid)
+//  MODE_MASK:   out_bf16[s][co] = mask[s][co] > 0 ? bf16(acc) : 0   (backward through ReLU)
+//  MODE_RAW:    out_f32[s][co]  = acc (row stride COUT)
 constexpr int WBLK = 512;
 
-template <int CIN, int COUT, int RY, int RZ, int WY, int WZ>
-struct ConvLds {
-    using S = ConvShape<CIN, COUT, RY, RZ, WY, WZ>;
-    static constexpr int NCH = (S::BN * S::V + WBLK - 1) / WBLK;   // brick chunks per thread
-    static constexpr int NW = S::NKS * S::NS * 64;                  // weight fragments (16 B)
-    static constexpr size_t brick_bytes = size_t(S::BN) * CIN * 2;
-    static constexpr size_t lds_bytes = brick_bytes + size_t(NW) * 16;
+template <int CIN, int COUT>
+struct ConvShape {
+    static constexpr int NS = COUT / 16, NKS = nksteps(CIN), KPD = NKS / 3;
+    static constexpr int NSUB = WBLK / 64 / NS;                   // waves per output-channel block
+    static constexpr int TY = 8, TZ = 4;                          // block tile: 16 x TY x TZ
+    static constexpr int RZ = 2, WZ = TZ / RZ, WY = NSUB / WZ, RY = TY / WY;
+    static constexpr int BX = 18, BY = TY + 2, BZ = TZ + 2;       // brick
+    static constexpr int BN = BX * BY * BZ;
+    static constexpr int V = CIN / 8;                             // 16-byte chunks per site
+    static constexpr int NCH = (BN * V + WBLK - 1) / WBLK;        // chunks staged per thread
+    static_assert(WY * RY == TY && WZ * RZ == TZ && WY * WZ == NSUB, "the waves cover the tile");
 };
 
-template <int CIN, int COUT, int MODE, int RY, int RZ, int WY, int WZ>
-__global__ __launch_bounds__(WBLK, 1) void k_conv(Grid3 g, int ctx, int cty, int ntiles, int per_block,
-                                                       const unsigned short *__restrict__ X,
-                                                       const u32x4 *__restrict__ Wfrag,
-                                                       const float *__restrict__ bias, void *__restrict__ out,
-                                                       const unsigned short *__restrict__ mask, int co_valid)
+// LDS position (in 16-byte chunks) of chunk v of the brick site at x = bx in
+// row r: sites are unpadded and the chunk index is XOR-swizzled with x, so
+// that the 16 lanes of a quarter-wave reading one chunk of 16 consecutive
+// sites hit 16 different bank groups, and a row's position enters as a
+// constant offset.
+template <int V>
+__device__ __forceinline__ int chunk_swizzle(int bx, int v)
 {
-    using S = ConvShape<CIN, COUT, RY, RZ, WY, WZ>;
-    using WS = ConvLds<CIN, COUT, RY, RZ, WY, WZ>;
-    constexpr int NS = S::NS, KPD = S::KPD, V = S::V, NCH = WS::NCH;
-    static_assert(WY * WZ == WBLK / 64, "one wave per sub-tile");
-    extern __shared__ __attribute__((aligned(16))) unsigned short smem[];
-    u32x4 *sB = reinterpret_cast<u32x4 *>(smem);
-    u32x4 *sW = reinterpret_cast<u32x4 *>(smem + WS::brick_bytes / 2);
+    return v ^ ((bx / (16 / V)) % V);
+}
 
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, li = l & 15, lg = l >> 4;
-    const int wy = w % WY, wz = w / WY;
-    const int cv = CIN == 32 ? lg : (lg & 1);
-    const bool upper = lg >= 2;
-    float bv[NS][4];
-#pragma unroll
-    for (int ns = 0; ns < NS; ++ns)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int co = ns * 16 + 4 * lg + r;
-            bv[ns][r] = ((MODE == MODE_RELU || MODE == MODE_LINEAR) && co < co_valid) ? bias[co] : 0.f;
-        }
+// Periodic wrap of a coordinate of a tile's halo-1 brick: -1 and n wrap.  Past
+// n, where the tile hangs over the lattice, any site does (no output that is
+// written reads it).
+__device__ __forceinline__ int halo_wrap(int v, int n)
+{
+    v += v < 0 ? n : 0;
+    v -= v >= n ? n : 0;
+    return min(v, n - 1);
+}
+
+// Copies 16 bytes per lane from global memory to LDS (lane i to l + 16 i),
+// without registers in between; complete once vmcnt has counted it.
+__device__ __forceinline__ void copy16_to_lds(const char *gp, u32x4 *l)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)gp,
+                                     (__attribute__((address_space(3))) void *)l, 16, 0, 0);
+}
+
+template <int CIN, int COUT, int MODE>
+__global__ __launch_bounds__(WBLK) void k_conv(Grid3 g, int ctx, int cty, int ntiles, int per_block,
+                                               const unsigned short *__restrict__ X,
+                                               const u32x4 *__restrict__ Wfrag, const float *__restrict__ bias,
+                                               void *__restrict__ out, const unsigned short *__restrict__ mask,
+                                               int co_valid)
+{
+    using S = ConvShape<CIN, COUT>;
+    constexpr int NS = S::NS, KPD = S::KPD, V = S::V, NCH = S::NCH, RY = S::RY, RZ = S::RZ;
+    // whole waves of chunks: the last copies write past the brick, into the pad
+    __shared__ u32x4 sB[2][NCH * WBLK];
+
+    const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    const int l = threadIdx.x & 63, li = l & 15, lg = l >> 4;
+    const int ns = w % NS, sub = w / NS, wy = sub % S::WY, wz = sub / S::WY;
+    const bool upper = lg >= 2;  // CIN = 16: the lane groups of a k-step's second tap
     const int b = xcd_logical_block();
     const int t_begin = b * per_block;
     const int t_end = min(ntiles, t_begin + per_block);
-    const u32x4 zero = {0u, 0u, 0u, 0u};
     if (t_begin >= t_end) return;
 
-    for (int e = threadIdx.x; e < WS::NW; e += WBLK) sW[e] = Wfrag[e];
-
-    // brick of tile t into registers: chunk e = threadIdx.x + k WBLK
-    u32x4 pre[NCH];
-    auto fetch = [&](int t) __attribute__((always_inline)) {
-        const int x0 = (t % ctx) * 16, rr = t / ctx;
-        const int yb = (rr % cty) * S::TY, zb = (rr / cty) * S::TZ;
-#pragma unroll
-        for (int k = 0; k < NCH; ++k) {
-            const int e = threadIdx.x + k * WBLK;
-            if (e < S::BN * V) {
-                const int site = e / V, v = e - site * V;
-                const int bx = site % S::BX, r2 = site / S::BX, by = r2 % S::BY, bz = r2 / S::BY;
-                const int x = wrap_near(x0 - 1 + bx, g.nx), y = wrap_near(yb - 1 + by, g.ny),
-                          z = wrap_near(zb - 1 + bz, g.nz);
-                const size_t gs = size_t(x) + size_t(g.nx) * (size_t(y) + size_t(g.ny) * z);
-                pre[k] = *reinterpret_cast<const u32x4 *>(X + gs * CIN + v * 8);
-            }
-        }
+    auto origin = [&](int t, int &x0, int &y0, int &z0) __attribute__((always_inline)) {
+        const int rr = t / ctx;
+        x0 = (t - rr * ctx) * 16;
+        const int r2 = rr / cty;
+        y0 = (rr - r2 * cty) * S::TY;
+        z0 = r2 * S::TZ;
     };
-    fetch(t_begin);
+    // This thread's chunks of a brick, position e = threadIdx.x + k WBLK: the
+    // brick coordinates of the site and the chunk's byte offset in it.
+    unsigned where[NCH];
+#pragma unroll
+    for (int k = 0; k < NCH; ++k) {
+        const int e = min(int(threadIdx.x) + k * WBLK, S::BN * V - 1);
+        const int site = e / V, r = site / S::BX, bx = site - r * S::BX, bz = r / S::BY, by = r - bz * S::BY;
+        where[k] = unsigned(bx) | unsigned(by) << 8 | unsigned(bz) << 16 | unsigned(chunk_swizzle<V>(bx, e % V)) << 24;
+    }
+    // chunk k of the brick at (x0, y0, z0) into buffer `buf`
+    auto stage = [&](int x0, int y0, int z0, int buf, int k) __attribute__((always_inline)) {
+        const int x = halo_wrap(x0 - 1 + int(where[k] & 255u), g.nx),
+                  y = halo_wrap(y0 - 1 + int(where[k] >> 8 & 255u), g.ny),
+                  z = halo_wrap(z0 - 1 + int(where[k] >> 16 & 255u), g.nz);
+        // below 2^32 bytes: hlbnn_workspace_bytes takes fewer than 2^26 sites
+        const unsigned at = unsigned(x + g.nx * (y + g.ny * z)) * (CIN * 2) + (where[k] >> 24) * 16;
+        copy16_to_lds(reinterpret_cast<const char *>(X) + at, &sB[buf][k * WBLK + w * 64]);
+    };
+    int xn, yn, zn;  // origin of the tile being staged
+    origin(t_begin, xn, yn, zn);
+#pragma unroll
+    for (int k = 0; k < NCH; ++k) stage(xn, yn, zn, 0, k);
 
-    for (int t = t_begin; t < t_end; ++t) {
-        const int x0 = (t % ctx) * 16, rr = t / ctx;
-        const int yb = (rr % cty) * S::TY, zb = (rr / cty) * S::TZ;
-        __syncthreads();  // the previous tile's reads of the brick are done
+    bf16x8 W[S::NKS];
 #pragma unroll
-        for (int k = 0; k < NCH; ++k) {
-            const int e = threadIdx.x + k * WBLK;
-            if (e < S::BN * V) {
-                const int site = e / V, v = e - site * V;
-                sB[brick_chunk<V>(site, v)] = pre[k];
-            }
-        }
+    for (int ks = 0; ks < S::NKS; ++ks) W[ks] = __builtin_bit_cast(bf16x8, Wfrag[(ks * NS + ns) * 64 + l]);
+    const int co = ns * 16 + 4 * lg;  // first of this lane's four output channels
+    f32x4 bv = {0.f, 0.f, 0.f, 0.f};
+    if (MODE == MODE_RELU || MODE == MODE_LINEAR)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) bv[r] = co + r < co_valid ? bias[co + r] : 0.f;
+
+    // this lane's chunk of the first row of its sub-tile, per x-offset
+    int off[3];
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx) {
+        const int cv = CIN == 32 ? lg : (lg & 1);
+        off[dx] = ((wz * RZ * S::BY + wy * RY) * S::BX + li + dx) * V + chunk_swizzle<V>(li + dx, cv);
+    }
+
+    auto next_brick = [&]() __attribute__((always_inline)) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (t + 1 < t_end) fetch(t + 1);  // in flight during this tile's MFMAs
-        f32x4 acc[RZ * RY][NS];
+    };
+    next_brick();
+    // One tile; with MORE the brick of tile t + 1 is staged along the way (no
+    // branch on it in the unrolled code, so its addresses are computed under
+    // the MFMAs).
+    auto tile = [&](int t, int buf, auto more_) __attribute__((always_inline)) {
+        constexpr bool more = decltype(more_)::value;
+        const int xo = xn + li, y0 = yn + wy * RY, z0 = zn + wz * RZ;
+        if (more) origin(t + 1, xn, yn, zn);
+
+        const int rows = min(RY, g.ny - y0), planes = min(RZ, g.nz - z0);  // of the sub-tile, inside the lattice
+        const unsigned s0 = unsigned(min(xo, g.nx - 1) + g.nx * (min(y0, g.ny - 1) + g.ny * min(z0, g.nz - 1)));
+        auto site = [&](int zz, int yy) __attribute__((always_inline)) {
+            return s0 + unsigned(g.nx * (yy + g.ny * zz));
+        };
+        uint2 mk[RZ][RY];
+        if (MODE == MODE_MASK)
 #pragma unroll
-        for (int m = 0; m < RZ * RY; ++m)
+            for (int zz = 0; zz < RZ; ++zz)
 #pragma unroll
-            for (int ns = 0; ns < NS; ++ns) acc[m][ns] = f32x4{0.f, 0.f, 0.f, 0.f};
-        u32x4 a[NS], an[NS];
-#pragma unroll
-        for (int ns = 0; ns < NS; ++ns) a[ns] = sW[ns * 64 + l];
-#pragma unroll 1
-        for (int dx = 0; dx < 3; ++dx) {
-            u32x4 f[RZ + 2][RY + 2];
-#pragma unroll
-            for (int zz = 0; zz < RZ + 2; ++zz)
-#pragma unroll
-                for (int yy = 0; yy < RY + 2; ++yy) {
-                    const int site = ((wz * RZ + zz) * S::BY + (wy * RY + yy)) * S::BX + li + dx;
-                    f[zz][yy] = sB[brick_chunk<V>(site, cv)];
-                }
-#pragma unroll
-            for (int k = 0; k < KPD; ++k) {
-                const int ks = dx * KPD + k;
-                if (ks + 1 < S::NKS) {
-#pragma unroll
-                    for (int ns = 0; ns < NS; ++ns) an[ns] = sW[((ks + 1) * NS + ns) * 64 + l];
-                }
-#pragma unroll
-                for (int zz = 0; zz < RZ; ++zz)
-#pragma unroll
-                    for (int yy = 0; yy < RY; ++yy) {
-                        u32x4 bop;
-                        if (CIN == 32) {
-                            bop = f[zz + k / 3][yy + k % 3];
-                        } else {
-                            const int qa = 2 * k, qb = 2 * k + 1 < 9 ? 2 * k + 1 : 0;
-                            const u32x4 lo = f[zz + qa / 3][yy + qa % 3];
-                            const u32x4 hi = 2 * k + 1 < 9 ? f[zz + qb / 3][yy + qb % 3] : zero;
-                            bop = upper ? hi : lo;
-                        }
-#pragma unroll
-                        for (int ns = 0; ns < NS; ++ns)
-                            acc[zz * RY + yy][ns] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                __builtin_bit_cast(bf16x8, a[ns]), __builtin_bit_cast(bf16x8, bop),
-                                acc[zz * RY + yy][ns], 0, 0, 0);
-                    }
-#pragma unroll
-                for (int ns = 0; ns < NS; ++ns) a[ns] = an[ns];
-            }
-        }
-        const int xo = x0 + li, y0 = yb + wy * RY, z0 = zb + wz * RZ;
+                for (int yy = 0; yy < RY; ++yy)
+                    if (yy < rows && zz < planes)
+                        mk[zz][yy] = *reinterpret_cast<const uint2 *>(mask + size_t(site(zz, yy)) * COUT + co);
+
+        f32x4 acc[RZ][RY];
 #pragma unroll
         for (int zz = 0; zz < RZ; ++zz)
 #pragma unroll
-            for (int yy = 0; yy < RY; ++yy) {
-                const int yo = y0 + yy, zo = z0 + zz;
-                if (xo >= g.nx || yo >= g.ny || zo >= g.nz) continue;
-                const size_t s = size_t(xo) + size_t(g.nx) * (size_t(yo) + size_t(g.ny) * zo);
+            for (int yy = 0; yy < RY; ++yy) acc[zz][yy] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const u32x4 *B = sB[buf];
+        if constexpr (CIN == 32) {
+            // Input rows plane by plane, x-offset major: each row feeds the
+            // outputs it is a tap of, while the rows of the next plane are read.
+            constexpr int NP = 3 * (RZ + 2);
+            bf16x8 f[2][RY + 2];
+            auto read = [&](int p) __attribute__((always_inline)) {
 #pragma unroll
-                for (int ns = 0; ns < NS; ++ns) {
-                    const f32x4 v = acc[zz * RY + yy][ns];
-                    const int co = ns * 16 + 4 * lg;
+                for (int yy = 0; yy < RY + 2; ++yy)
+                    f[p & 1][yy] = __builtin_bit_cast(
+                        bf16x8, B[off[p / (RZ + 2)] + (p % (RZ + 2) * S::BY + yy) * S::BX * V]);
+            };
+            read(0);
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                const int dx = p / (RZ + 2), zz = p % (RZ + 2);
+#pragma unroll
+                for (int yy = 0; yy < RY + 2; ++yy) {
+#pragma unroll
+                    for (int oz = 0; oz < RZ; ++oz)
+#pragma unroll
+                        for (int oy = 0; oy < RY; ++oy) {
+                            const int dz = zz - oz, dy = yy - oy;
+                            if (dz >= 0 && dz < 3 && dy >= 0 && dy < 3)
+                                acc[oz][oy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                    W[dx * KPD + dz * 3 + dy], f[p & 1][yy], acc[oz][oy], 0, 0, 0);
+                        }
+                    if (yy == 0 && p + 1 < NP) {
+                        // issued here and not later, with the other rows' MFMAs to arrive under
+                        __builtin_amdgcn_sched_barrier(6);
+                        read(p + 1);
+                        if (more && p < NCH) stage(xn, yn, zn, buf ^ 1, p);
+                        __builtin_amdgcn_sched_barrier(6);
+                    }
+                }
+            }
+        } else {
+            if (more)
+#pragma unroll
+                for (int k = 0; k < NCH; ++k) stage(xn, yn, zn, buf ^ 1, k);
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx) {
+                u32x4 f[RZ + 2][RY + 2];
+#pragma unroll
+                for (int zz = 0; zz < RZ + 2; ++zz)
+#pragma unroll
+                    for (int yy = 0; yy < RY + 2; ++yy) f[zz][yy] = B[off[dx] + (zz * S::BY + yy) * S::BX * V];
+#pragma unroll
+                for (int k = 0; k < KPD; ++k)
+#pragma unroll
+                    for (int oz = 0; oz < RZ; ++oz)
+#pragma unroll
+                        for (int oy = 0; oy < RY; ++oy) {
+                            const int qa = 2 * k, qb = 2 * k + 1;  // (z, y) taps of the k-step; none past the ninth
+                            const u32x4 lo = f[oz + qa / 3][oy + qa % 3];
+                            const u32x4 hi = qb < 9 ? f[oz + (qb < 9 ? qb / 3 : 0)][oy + qb % 3] : u32x4{0u, 0u, 0u, 0u};
+                            acc[oz][oy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                W[dx * KPD + k], __builtin_bit_cast(bf16x8, upper ? hi : lo), acc[oz][oy], 0, 0, 0);
+                        }
+            }
+        }
+        // the next brick is in LDS, and every wave has read this one; ahead of
+        // this tile's stores, which the wait would otherwise include
+        if (more) next_brick();
+        if (xo < g.nx)
+#pragma unroll
+            for (int zz = 0; zz < RZ; ++zz)
+#pragma unroll
+                for (int yy = 0; yy < RY; ++yy) {
+                    if (yy >= rows || zz >= planes) continue;
+                    const size_t s = site(zz, yy);
+                    f32x4 v = acc[zz][yy];
                     if (MODE == MODE_RELU) {
-                        unsigned short h[4];
+                        // output channels past co_valid: zero weights, zero bias, so zero
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) h[r] = co + r < co_valid ? f2bf(fmaxf(v[r] + bv[ns][r], 0.f)) : 0;
+                        for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r] + bv[r], 0.f);
                         *reinterpret_cast<uint2 *>(static_cast<unsigned short *>(out) + s * COUT + co) =
-                            make_uint2(unsigned(h[0]) | (unsigned(h[1]) << 16), unsigned(h[2]) | (unsigned(h[3]) << 16));
+                            make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
                     } else if (MODE == MODE_LINEAR) {
 #pragma unroll
                         for (int r = 0; r < 4; ++r)
-                            if (co + r < co_valid) static_cast<float *>(out)[s * co_valid + co + r] = v[r] + bv[ns][r];
+                            if (co + r < co_valid) static_cast<float *>(out)[s * co_valid + co + r] = v[r] + bv[r];
                     } else if (MODE == MODE_MASK) {
-                        const uint2 mk = *reinterpret_cast<const uint2 *>(mask + s * COUT + co);
-                        const unsigned short mh[4] = {(unsigned short)(mk.x & 0xffffu), (unsigned short)(mk.x >> 16),
-                                                      (unsigned short)(mk.y & 0xffffu), (unsigned short)(mk.y >> 16)};
-                        unsigned short h[4];
+                        const short mh[4] = {short(mk[zz][yy].x & 0xffffu), short(mk[zz][yy].x >> 16),
+                                             short(mk[zz][yy].y & 0xffffu), short(mk[zz][yy].y >> 16)};
+                        // the mask is a ReLU output, never NaN: positive where its bits are, as an integer
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) h[r] = bf2f(mh[r]) > 0.f ? f2bf(v[r]) : (unsigned short)0;
+                        for (int r = 0; r < 4; ++r) v[r] = mh[r] > 0 ? v[r] : 0.f;
                         *reinterpret_cast<uint2 *>(static_cast<unsigned short *>(out) + s * COUT + co) =
-                            make_uint2(unsigned(h[0]) | (unsigned(h[1]) << 16), unsigned(h[2]) | (unsigned(h[3]) << 16));
+                            make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
                     } else {
                         *reinterpret_cast<float4 *>(static_cast<float *>(out) + s * COUT + co) =
                             make_float4(v[0], v[1], v[2], v[3]);
                     }
                 }
-            }
-    }
+    };
+    int t = t_begin;
+    for (; t + 1 < t_end; ++t) tile(t, (t - t_begin) & 1, std::true_type{});
+    tile(t, (t - t_begin) & 1, std::false_type{});
 }
 
 template <int CIN, int COUT, int MODE>
 hipError_t conv_launch(const Grid3 &g, const unsigned short *X, const unsigned short *W, const float *bias,
-                            void *out, const unsigned short *mask, int co_valid, hipStream_t st)
+                       void *out, const unsigned short *mask, int co_valid, hipStream_t st)
 {
-    constexpr int RY = 2, RZ = 2, WY = 4, WZ = 2;
-    using S = ConvShape<CIN, COUT, RY, RZ, WY, WZ>;
-    using WS = ConvLds<CIN, COUT, RY, RZ, WY, WZ>;
-    auto kern = k_conv<CIN, COUT, MODE, RY, RZ, WY, WZ>;
-    static bool attr = false;
-    if (!attr) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(WS::lds_bytes));
-        if (e != hipSuccess) return e;
-        attr = true;
-    }
+    using S = ConvShape<CIN, COUT>;
     const int ctx = (g.nx + 15) / 16, cty = (g.ny + S::TY - 1) / S::TY, ctz = (g.nz + S::TZ - 1) / S::TZ;
     const int ntiles = ctx * cty * ctz;
     // one resident block per CU (the LDS bound), a multiple of the 8 XCDs
@@ -865,11 +922,10 @@ hipError_t conv_launch(const Grid3 &g, const unsigned short *X, const unsigned s
     grid = ntiles < grid ? ntiles : grid;
     grid = (grid + 7) & ~7;
     const int per_block = (ntiles + grid - 1) / grid;
-    kern<<<grid, WBLK, WS::lds_bytes, st>>>(g, ctx, cty, ntiles, per_block, X, reinterpret_cast<const u32x4 *>(W),
-                                            bias, out, mask, co_valid);
+    k_conv<CIN, COUT, MODE><<<grid, WBLK, 0, st>>>(g, ctx, cty, ntiles, per_block, X,
+                                                   reinterpret_cast<const u32x4 *>(W), bias, out, mask, co_valid);
     return hipGetLastError();
 }
-
 
 }  // namespace
 
