@@ -8,7 +8,6 @@ namespace nn {
 
 struct Grid3 {
     int nx, ny, nz, N;
-    int tx, ty, tz, ntiles;  // tiles of 16 x 4 x 4 sites
 };
 
 enum ConvMode { MODE_RELU = 0, MODE_LINEAR = 1, MODE_MASK = 2, MODE_RAW = 3 };
@@ -20,7 +19,7 @@ constexpr int NIN = 18;
 constexpr int NORM_IN_MEAN = 0, NORM_IN_STD = 18, NORM_OUT_MEAN = 36, NORM_OUT_STD = 41, NORM_BETA = 46;
 constexpr int NORM_SIZE = 47;
 
-constexpr int WGRAD_BLOCKS = 512;  // persistent blocks of the weight-gradient kernel
+constexpr int WGRAD_BLOCKS = 256;  // blocks of the weight-gradient kernel: one per CU
 
 Grid3 make_grid(int nx, int ny, int nz);
 int wgrad_grid(const Grid3 &g);

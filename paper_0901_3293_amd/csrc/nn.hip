@@ -24,7 +24,6 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 namespace {
 
 constexpr int BLK = 256;
-constexpr int TXs = 16, TYs = 4, TZs = 4;  // weight-gradient tile (Grid3)
 
 __device__ __forceinline__ unsigned short f2bf(float f)
 {
@@ -44,215 +43,9 @@ __device__ __forceinline__ unsigned f2bf2(float a, float b)
 
 __device__ __forceinline__ float bf2f(unsigned short h) { return __uint_as_float(unsigned(h) << 16); }
 
-__device__ __forceinline__ int wrap(int v, int n)
-{
-    v %= n;
-    return v < 0 ? v + n : v;
-}
-
-__device__ __forceinline__ void tile_origin(const Grid3 &g, int t, int &x0, int &y0, int &z0)
-{
-    x0 = (t % g.tx) * TXs;
-    const int r = t / g.tx;
-    y0 = (r % g.ty) * TYs;
-    z0 = (r / g.ty) * TZs;
-}
-
 // K = 32 slices of the nine (y, z) taps of one x-offset, times three: the 32
 // input channels of one tap, or the 16 channels of two taps.
 constexpr int nksteps(int cin) { return cin == 32 ? 27 : 15; }
-
-// Weight gradient dW[tap][ci][co] = sum_s dZ[s][co] X[s + off(tap)][ci] and
-// bias gradient db[co] = sum_s dZ[s][co] on v_mfma_f32_16x16x32_bf16: per
-// tile of 16x4x4 sites, M = 16 output channels, N = 16 input channels,
-// K = 32 sites (two x-rows).  The tile's dZ and its input brick (18x6x6
-// sites, periodic wrap) are staged channel-major in LDS (brick rows padded to
-// 24 sites; each channel plane padded so that its stride is 4 dwords modulo
-// the 32 LDS banks, which keeps the 16 channels a 16-byte operand read
-// touches on distinct banks).  An operand of 8 consecutive sites shifted by the tap's
-// x-offset comes from one aligned 16-byte read and one 4-byte read of the
-// brick row, shared by the three x-offsets of a (y, z) offset pair (odd
-// offsets take a 16-bit funnel shift).  With 32 output channels wave w owns
-// the (co block, ci block) pair (w >> 1, w & 1) for all 27 taps; with 16, ci
-// block w & 1 over half the K-chunks, the two halves summed in LDS at the end.
-// The bias gradient is summed while dZ is staged (each thread keeps the
-// running sums of the channels of the sites it stages; the block adds the
-// threads' sums per channel in thread order at the end).
-// Per-block FP32 partials; the final sum is FP64 in a fixed order
-// (k_wgrad_reduce), so the result is deterministic.
-template <int COP>
-__global__ __launch_bounds__(BLK) void k_wgrad(Grid3 g, const unsigned short *__restrict__ X,
-                                               const unsigned short *__restrict__ dZ, float *__restrict__ part)
-{
-    constexpr int CIP = 32;
-    constexpr int XR = 24, BYs = TYs + 2, BZs = TZs + 2, ROWS = BYs * BZs;
-    constexpr int TS = TXs * TYs * TZs;  // 256 sites, 8 K-chunks of 32
-    constexpr int CSX = ROWS * XR + 40;  // brick channel stride (halfwords): 452 dwords, 4 mod 32
-    constexpr int CSD = TS + 8;          // dZ channel stride (halfwords): 132 dwords, 4 mod 32
-    static_assert((CSX / 2) % 32 == 4 && (CSD / 2) % 32 == 4, "bank-spread channel strides");
-    static_assert(CSX % 8 == 0 && CSD % 8 == 0, "16-byte aligned operand rows");
-    static_assert((TXs + 2) % 2 == 0 && XR % 2 == 0 && TXs % 2 == 0, "sites staged in x-pairs");
-    constexpr int PS = 27 * CIP * COP + COP;
-    constexpr int NBX = (TXs + 2) * ROWS;  // brick sites
-    __shared__ __attribute__((aligned(16))) unsigned short sX[CIP * CSX];
-    __shared__ __attribute__((aligned(16))) unsigned short sD[COP * CSD];
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, li = l & 15, lg = l >> 4;
-    const int mt = COP == 32 ? (w >> 1) : 0, nt = w & 1;
-    const int half = COP == 32 ? 0 : (w >> 1);  // COP == 16: which K-chunks this wave takes
-    const int cstep = COP == 32 ? 1 : 2;
-    f32x4 acc[27];
-#pragma unroll
-    for (int j = 0; j < 27; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    static_assert(TS / 2 <= BLK, "one site pair of dZ per thread and tile");
-    float dsum[COP];
-#pragma unroll
-    for (int co = 0; co < COP; ++co) dsum[co] = 0.f;
-    for (int t = blockIdx.x; t < g.ntiles; t += gridDim.x) {
-        int x0, y0, z0;
-        tile_origin(g, t, x0, y0, z0);
-        __syncthreads();
-        // input brick, channel-major: sX[ci][bz][by][bx].  A thread takes two
-        // x-neighbouring sites (bx, bx + 1) with all their channels and writes
-        // one 32-bit word (the two sites' values) per channel.
-        unsigned *sXw = reinterpret_cast<unsigned *>(sX);
-        for (int e = threadIdx.x; e < NBX / 2; e += BLK) {
-            const int px = e % ((TXs + 2) / 2), r = e / ((TXs + 2) / 2), by = r % BYs, bz = r / BYs;
-            const int y = wrap(y0 - 1 + by, g.ny), z = wrap(z0 - 1 + bz, g.nz);
-            const size_t row = size_t(g.nx) * (size_t(y) + size_t(g.ny) * z);
-            const size_t ga = row + size_t(wrap(x0 - 1 + 2 * px, g.nx));
-            const size_t gb = row + size_t(wrap(x0 + 2 * px, g.nx));
-            unsigned *d = sXw + r * (XR / 2) + px;
-#pragma unroll
-            for (int v = 0; v < CIP / 8; ++v) {
-                const u32x4 a = *reinterpret_cast<const u32x4 *>(X + ga * CIP + v * 8);
-                const u32x4 b = *reinterpret_cast<const u32x4 *>(X + gb * CIP + v * 8);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    d[(8 * v + 2 * c) * (CSX / 2)] = (a[c] & 0xffffu) | (b[c] << 16);
-                    d[(8 * v + 2 * c + 1) * (CSX / 2)] = (a[c] >> 16) | (b[c] & 0xffff0000u);
-                }
-            }
-        }
-        // output gradient of the tile, channel-major: sD[co][site], two x-neighbouring
-        // sites per thread as above (sites outside the lattice contribute zero)
-        unsigned *sDw = reinterpret_cast<unsigned *>(sD);
-        for (int e = threadIdx.x; e < TS / 2; e += BLK) {
-            const int si = 2 * e, tx = si % TXs, r = si / TXs, ty = r % TYs, tz = r / TYs;
-            const int x = x0 + tx, y = y0 + ty, z = z0 + tz;
-            const bool inyz = y < g.ny && z < g.nz;
-            const bool oka = inyz && x < g.nx, okb = inyz && x + 1 < g.nx;
-            const size_t ga = size_t(x) + size_t(g.nx) * (size_t(y) + size_t(g.ny) * z);
-            unsigned *d = sDw + e;
-#pragma unroll
-            for (int v = 0; v < COP / 8; ++v) {
-                const u32x4 zero4 = {0u, 0u, 0u, 0u};
-                const u32x4 a = oka ? *reinterpret_cast<const u32x4 *>(dZ + ga * COP + v * 8) : zero4;
-                const u32x4 b = okb ? *reinterpret_cast<const u32x4 *>(dZ + (ga + 1) * COP + v * 8) : zero4;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    d[(8 * v + 2 * c) * (CSD / 2)] = (a[c] & 0xffffu) | (b[c] << 16);
-                    d[(8 * v + 2 * c + 1) * (CSD / 2)] = (a[c] >> 16) | (b[c] & 0xffff0000u);
-                    dsum[8 * v + 2 * c] += bf2f((unsigned short)(a[c] & 0xffffu)) + bf2f((unsigned short)(b[c] & 0xffffu));
-                    dsum[8 * v + 2 * c + 1] += bf2f((unsigned short)(a[c] >> 16)) + bf2f((unsigned short)(b[c] >> 16));
-                }
-            }
-        }
-        __syncthreads();
-#pragma unroll 1
-        for (int c = half; c < TS / 32; c += cstep) {
-            const int rowk = 2 * c + (lg >> 1), yy = rowk % TYs, zz = rowk / TYs, xo = 8 * (lg & 1);
-            const u32x4 A = *reinterpret_cast<const u32x4 *>(sD + (16 * mt + li) * CSD + c * 32 + 8 * lg);
-            const unsigned short *xrow = sX + (16 * nt + li) * CSX + xo;
-#pragma unroll
-            for (int q = 0; q < 9; ++q) {
-                const int dz = q / 3, dy = q % 3;
-                const unsigned short *rp = xrow + ((zz + dz) * BYs + (yy + dy)) * XR;
-                const u32x4 lo = *reinterpret_cast<const u32x4 *>(rp);
-                const unsigned hi = *reinterpret_cast<const unsigned *>(rp + 8);
-                const u32x4 b0 = lo;
-                const u32x4 b1 = {__builtin_amdgcn_alignbit(lo[1], lo[0], 16), __builtin_amdgcn_alignbit(lo[2], lo[1], 16),
-                                  __builtin_amdgcn_alignbit(lo[3], lo[2], 16), __builtin_amdgcn_alignbit(hi, lo[3], 16)};
-                const u32x4 b2 = {lo[1], lo[2], lo[3], hi};
-                const int tap = dz * 9 + dy * 3;
-                acc[tap] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, A),
-                                                                   __builtin_bit_cast(bf16x8, b0), acc[tap], 0, 0, 0);
-                acc[tap + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                    __builtin_bit_cast(bf16x8, A), __builtin_bit_cast(bf16x8, b1), acc[tap + 1], 0, 0, 0);
-                acc[tap + 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                    __builtin_bit_cast(bf16x8, A), __builtin_bit_cast(bf16x8, b2), acc[tap + 2], 0, 0, 0);
-            }
-        }
-    }
-    float *P = part + size_t(blockIdx.x) * PS;
-    {
-        // bias: channel co summed over the TS / 2 threads that stage dZ, in order
-        float *sS = reinterpret_cast<float *>(sX);
-        static_assert(size_t(TS / 2) * COP * sizeof(float) <= sizeof(sX), "bias sums fit the brick buffer");
-        __syncthreads();
-        if (int(threadIdx.x) < TS / 2)
-#pragma unroll
-            for (int co = 0; co < COP; ++co) sS[threadIdx.x * COP + co] = dsum[co];
-        __syncthreads();
-        if (int(threadIdx.x) < COP) {
-            float db = 0.f;
-            for (int t = 0; t < TS / 2; ++t) db += sS[t * COP + threadIdx.x];
-            P[27 * CIP * COP + threadIdx.x] = db;
-        }
-    }
-    if (COP == 16) {
-        // waves 2 and 3 hand their half-sums to waves 0 and 1 through LDS
-        float *sA = reinterpret_cast<float *>(sX);  // 2 x 27 x 64 x 4 floats <= sizeof(sX)
-        static_assert(2 * 27 * 64 * 4 * sizeof(float) <= sizeof(sX), "exchange fits the brick buffer");
-        __syncthreads();
-        if (half == 1)
-#pragma unroll
-            for (int j = 0; j < 27; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) sA[((nt * 27 + j) * 64 + l) * 4 + r] = acc[j][r];
-        __syncthreads();
-        if (half == 1) return;
-#pragma unroll
-        for (int j = 0; j < 27; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[j][r] += sA[((nt * 27 + j) * 64 + l) * 4 + r];
-    }
-    // D[r] of lane (li, lg): output channel 16 mt + 4 lg + r, input channel 16 nt + li
-#pragma unroll
-    for (int j = 0; j < 27; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) P[(j * CIP + 16 * nt + li) * COP + 16 * mt + 4 * lg + r] = acc[j][r];
-}
-
-// Sum the per-block partials (FP64, block order) into the flat gradient of
-// one layer: W[co][ci][tap] (ci < CI, co < CO) then b[co].  Threads walk the
-// partial layout contiguously, so every block's partials are read coalesced.
-__global__ __launch_bounds__(BLK) void k_wgrad_reduce(const float *__restrict__ part, int nblk, int CIP, int COP,
-                                                      int CI, int CO, float *__restrict__ grad)
-{
-    const int PS = 27 * CIP * COP + COP;
-    for (int idx = blockIdx.x * BLK + threadIdx.x; idx < PS; idx += gridDim.x * BLK) {
-        int e;
-        if (idx < 27 * CIP * COP) {
-            const int co = idx % COP, ci = (idx / COP) % CIP, tap = idx / (COP * CIP);
-            if (co >= CO || ci >= CI) continue;
-            e = (co * CI + ci) * 27 + tap;
-        } else {
-            const int co = idx - 27 * CIP * COP;
-            if (co >= CO) continue;
-            e = CO * CI * 27 + co;
-        }
-        // eight interleaved partial sums (block b into sum b % 8), combined in a
-        // fixed order: deterministic, with eight loads in flight per thread
-        double acc8[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        int b = 0;
-        for (; b + 8 <= nblk; b += 8)
-#pragma unroll
-            for (int k = 0; k < 8; ++k) acc8[k] += double(part[size_t(b + k) * PS + idx]);
-        for (; b < nblk; ++b) acc8[b & 7] += double(part[size_t(b) * PS + idx]);
-        const double s = ((acc8[0] + acc8[1]) + (acc8[2] + acc8[3])) + ((acc8[4] + acc8[5]) + (acc8[6] + acc8[7]));
-        grad[e] = float(s);
-    }
-}
 
 // Weights of one layer in MFMA fragment order for k_conv, from the flat FP32
 // parameters W[co][ci][tap].  A convolution as run maps CIN input channels to
@@ -608,14 +401,15 @@ Grid3 make_grid(int nx, int ny, int nz)
     g.ny = ny;
     g.nz = nz;
     g.N = nx * ny * nz;
-    g.tx = (nx + TXs - 1) / TXs;
-    g.ty = (ny + TYs - 1) / TYs;
-    g.tz = (nz + TZs - 1) / TZs;
-    g.ntiles = g.tx * g.ty * g.tz;
     return g;
 }
 
-int wgrad_grid(const Grid3 &g) { return g.ntiles < WGRAD_BLOCKS ? g.ntiles : WGRAD_BLOCKS; }
+// One block per CU, a multiple of the 8 XCDs; fewer on lattices of fewer tiles.
+int wgrad_grid(const Grid3 &g)
+{
+    const long long ntiles = (long long)((g.nx + 31) / 32) * ((g.ny + 3) / 4) * ((g.nz + 1) / 2);
+    return int(ntiles < WGRAD_BLOCKS ? (ntiles + 7) / 8 * 8 : WGRAD_BLOCKS);
+}
 
 size_t frag_bytes(int cin, int cout) { return size_t(nksteps(cin)) * (cout / 16) * 64 * 16; }
 
@@ -680,15 +474,18 @@ struct ConvShape {
     static_assert(WY * RY == TY && WZ * RZ == TZ && WY * WZ == NSUB, "the waves cover the tile");
 };
 
-// LDS position (in 16-byte chunks) of chunk v of the brick site at x = bx in
-// row r: sites are unpadded and the chunk index is XOR-swizzled with x, so
-// that the 16 lanes of a quarter-wave reading one chunk of 16 consecutive
-// sites hit 16 different bank groups, and a row's position enters as a
-// constant offset.
+// LDS position (in 16-byte chunks) of chunk v of the brick site at x = bx
+// within the site's chunks.  A 16-byte LDS read takes its 64 lanes in four
+// groups of 16 over 64 banks (256 bytes a cycle, measured): lanes 0-3, 12-15
+// and 20-27 together, then 4-11, 16-19 and 28-31, and so on 32 higher.  With
+// lane 16 lg + li reading chunk lg of site li + dx, a group mixes two chunks;
+// flipping bit 1 of the chunk on every other four sites gives the 16 lanes of
+// a group 16 different bank quads at every dx (with two chunks per site they
+// differ as they are).  The row of the site only adds a constant.
 template <int V>
 __device__ __forceinline__ int chunk_swizzle(int bx, int v)
 {
-    return v ^ ((bx / (16 / V)) % V);
+    return V == 4 ? v ^ (bx >> 1 & 2) : v;
 }
 
 // Periodic wrap of a coordinate of a tile's halo-1 brick: -1 and n wrap.  Past
@@ -927,6 +724,316 @@ hipError_t conv_launch(const Grid3 &g, const unsigned short *X, const unsigned s
     return hipGetLastError();
 }
 
+// Weight gradient dW[tap][ci][co] = sum_s dZ[s][co] X[s + off(tap)][ci] and
+// bias gradient db[co] = sum_s dZ[s][co] on v_mfma_f32_16x16x32_bf16: M = 16
+// output channels, N = 16 input channels, K = 32 sites of one x-row.
+//
+// One block of 8 waves per CU takes a run of tiles of 32 x 4 x 2 sites, z
+// fastest.  The input planes of a tile (34 x 6 sites, periodic wrap) and its dZ
+// lie channel-major in LDS (rows padded to 40 sites): the input in a ring of
+// three pairs of z-planes, two of them in use, so that a tile brings in two
+// planes and not four (1.6 instead of 3.2 times its sites; with all four, 235
+// MB per 96^3 layer, it took 64 us); dZ in two buffers.  The next
+// tile's are transposed into LDS between the MFMAs of this tile, from
+// registers loaded one tile ahead.  A staged unit is 8 channels of two
+// x-neighbouring sites, four units of a site pair in neighbouring lanes, so a
+// load instruction touches whole cache lines (64 strided pieces of one line
+// each before, which alone took longer than the MFMAs).  Channel 8 v + j is
+// plane (COP or 32) / 8 j + v, and planes are 8 dwords apart modulo 32: the 4
+// chunks of 8 site pairs that 32 lanes write as dwords fall on 32 banks, and
+// the 16 lanes of a 16-byte read's group (see chunk_swizzle) on 64.
+//
+// A wave owns one (output-channel block, input-channel block) pair for all 27
+// taps over a part of the tile's output rows (half with 32 output channels, a
+// quarter with 16), and holds the dZ operands of those rows in registers.
+// Each input row it reads, as two aligned 16-byte reads shared by the three
+// x-offsets (odd offsets take a 16-bit funnel shift; of the second read only
+// the first dword is used, but a 4-byte read would meet 4-way bank conflicts),
+// meets every output row it is a (y, z) tap of: up to 9 MFMAs per row (3
+// before).  The parts are summed in LDS at the end, in a fixed order.
+// The bias gradient is summed while dZ is staged (each thread keeps the
+// running sums of the channels it stages; the block adds the threads' sums
+// per channel in order at the end).
+// Per-block FP32 partials; the final sum is FP64 in a fixed order
+// (k_wgrad_reduce), so the result is deterministic.
+//
+// Bound: the matrix cores (19 us of MFMAs at 96^3) with the waits on loads
+// and barriers around them: 52 us per 32 -> 32 layer (0.94 PFLOP/s) against 120
+// us with 16 x 4 x 4 tiles staged between barriers, 32 -> 16 35 against 75 us.
+template <int COP>
+struct WgradShape {
+    static constexpr int TX = 32, TY = 4, TZ = 2;
+    static constexpr int BX = TX + 2, BY = TY + 2, ROWS = BY * TZ;  // input rows of a plane pair
+    static constexpr int XR = 40;                                 // padded input row (sites)
+    static constexpr int PAIR = ROWS * XR, RING = 3;              // halfwords of a plane pair; pairs in LDS
+    static constexpr int CSX = RING * PAIR + 48;                  // channel strides (halfwords)
+    static constexpr int CSD = TX * TY * TZ + 16;
+    static_assert((CSX / 2) % 32 == 8 && (CSD / 2) % 32 == 8, "bank-spread channel strides");
+    // the channel of plane p of an n-channel array
+    __device__ static constexpr int channel_of(int p, int n) { return p % (n / 8) * 8 + p / (n / 8); }
+    static_assert(CSX % 8 == 0 && CSD % 8 == 0 && XR % 8 == 0, "16-byte aligned operand rows");
+    static constexpr int UX = BX / 2 * ROWS * 4, UD = TX / 2 * TY * TZ * (COP / 8);  // staged units
+    static constexpr int NUX = (UX + WBLK - 1) / WBLK;            // input units per thread
+    static_assert(UD <= WBLK, "one dZ unit per thread");
+    static constexpr int NM = COP / 16, NPAIR = 2 * NM, NQ = WBLK / 64 / NPAIR;  // waves: pairs x parts
+    static constexpr int RY = TY * TZ / NQ;                       // output rows of a part (one z-plane)
+    static constexpr int PS = 27 * 32 * COP + COP;                // floats of a partial
+};
+
+template <int COP>
+__global__ __launch_bounds__(WBLK) void k_wgrad(Grid3 g, int ctx, int ctz, int ntiles, int per_block,
+                                                const unsigned short *__restrict__ X,
+                                                const unsigned short *__restrict__ dZ, float *__restrict__ part)
+{
+    using S = WgradShape<COP>;
+    constexpr int RY = S::RY, NUX = S::NUX;
+    struct Lds {
+        unsigned short x[32 * S::CSX], d[2][COP * S::CSD];
+    };
+    __shared__ __attribute__((aligned(16))) Lds lds;
+
+    const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    const int l = threadIdx.x & 63, li = l & 15, lg = l >> 4;
+    const int pair = w % S::NPAIR, mt = pair >> 1, nt = pair & 1, q = w / S::NPAIR;
+    const int oz = q * RY / S::TY, oy = q * RY % S::TY;  // first output row of the part
+    const int b = xcd_logical_block();
+    const int t_begin = b * per_block, t_end = min(ntiles, t_begin + per_block);
+    float *P = part + size_t(b) * S::PS;
+
+    f32x4 acc[27];
+#pragma unroll
+    for (int j = 0; j < 27; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float dsum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+
+    // Unit k of this thread: 8 channels (chunk v) of the sites bx, bx + 1 of
+    // row r of a plane pair, and the dword of its first channel there.
+    unsigned where[NUX];
+    int word[NUX];
+#pragma unroll
+    for (int k = 0; k < NUX; ++k) {
+        const int e = min(int(threadIdx.x) + k * WBLK, S::UX - 1), v = e & 3, p = e >> 2;
+        const int r = p / (S::BX / 2), px = p - r * (S::BX / 2), bz = r / S::BY, by = r - bz * S::BY;
+        where[k] = unsigned(2 * px) | unsigned(by) << 8 | unsigned(bz) << 16 | unsigned(v) << 24;
+        word[k] = v * (S::CSX / 2) + r * (S::XR / 2) + px;
+    }
+    const int de = min(int(threadIdx.x), S::UD - 1), dv = de % (COP / 8), dp = de / (COP / 8);
+    const int dtx = 2 * dp % S::TX, dty = 2 * dp / S::TX % S::TY, dtz = 2 * dp / (S::TX * S::TY);
+
+    u32x4 xa[NUX], xb[NUX], da, db;  // in flight: the units of one tile
+    // unit k of the planes zp, zp + 1
+    auto load_x = [&](int k, int x0, int y0, int zp) __attribute__((always_inline)) {
+        const int x = x0 - 1 + int(where[k] & 255u);
+        const int y = halo_wrap(y0 - 1 + int(where[k] >> 8 & 255u), g.ny),
+                  z = halo_wrap(zp + int(where[k] >> 16 & 255u), g.nz);
+        // below 2^32 bytes: hlbnn_workspace_bytes takes fewer than 2^26 sites
+        const unsigned row = unsigned(g.nx * (y + g.ny * z)), c = (where[k] >> 24) * 16;
+        const char *base = reinterpret_cast<const char *>(X);
+        xa[k] = *reinterpret_cast<const u32x4 *>(base + ((row + unsigned(halo_wrap(x, g.nx))) * 64u + c));
+        xb[k] = *reinterpret_cast<const u32x4 *>(base + ((row + unsigned(halo_wrap(x + 1, g.nx))) * 64u + c));
+    };
+    // dZ of the tile at (x0, y0, z0); zero outside the lattice and past the last tile
+    auto load_d = [&](int x0, int y0, int z0, bool live) __attribute__((always_inline)) {
+        const int x = x0 + dtx, y = y0 + dty, z = z0 + dtz;
+        const bool in = live && y < g.ny && z < g.nz;
+        const size_t s = size_t(x) + size_t(g.nx) * (size_t(y) + size_t(g.ny) * z);
+        const u32x4 zero = {0u, 0u, 0u, 0u};
+        da = in && x < g.nx ? *reinterpret_cast<const u32x4 *>(dZ + s * COP + dv * 8) : zero;
+        db = in && x + 1 < g.nx ? *reinterpret_cast<const u32x4 *>(dZ + (s + 1) * COP + dv * 8) : zero;
+    };
+    // two sites' 8 channels -> one dword per channel, `stride` dwords apart
+    auto put = [&](unsigned *d, int stride, const u32x4 &a, const u32x4 &c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            d[2 * j * stride] = __builtin_amdgcn_perm(c[j], a[j], 0x05040100u);
+            d[(2 * j + 1) * stride] = __builtin_amdgcn_perm(c[j], a[j], 0x07060302u);
+        }
+    };
+    auto put_x = [&](int k, int slot) __attribute__((always_inline)) {
+        if (int(threadIdx.x) + k * WBLK < S::UX)
+            put(reinterpret_cast<unsigned *>(lds.x + slot * S::PAIR) + word[k], 4 * (S::CSX / 2), xa[k], xb[k]);
+    };
+    auto put_d = [&](int slot) __attribute__((always_inline)) {
+        if (int(threadIdx.x) < S::UD) {
+            put(reinterpret_cast<unsigned *>(lds.d[slot]) + dv * (S::CSD / 2) + dp, COP / 8 * (S::CSD / 2), da, db);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                dsum[2 * j] += __uint_as_float(da[j] << 16) + __uint_as_float(db[j] << 16);
+                dsum[2 * j + 1] += __uint_as_float(da[j] & 0xffff0000u) + __uint_as_float(db[j] & 0xffff0000u);
+            }
+        }
+    };
+
+    // The tiles of a run that lie in one (x, y) column, from z0 up.
+    for (int t = t_begin, n; t < t_end; t += n) {
+        const int col = t / ctz, cy = col / ctx;
+        const int x0 = (col - cy * ctx) * S::TX, y0 = cy * S::TY, z0 = (t - col * ctz) * S::TZ;
+        n = min(t_end - t, ctz - (t - col * ctz));
+        __syncthreads();  // the last column's planes are no longer read
+        // plane pair j holds the planes z0 - 1 + 2 j and z0 + 2 j; tile i reads pairs i and i + 1
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+#pragma unroll
+            for (int k = 0; k < NUX; ++k) load_x(k, x0, y0, z0 - 1 + S::TZ * j);
+            if (j < 2)
+#pragma unroll
+                for (int k = 0; k < NUX; ++k) put_x(k, j);
+        }
+        load_d(x0, y0, z0, true);
+        put_d(0);
+        load_d(x0, y0, z0 + S::TZ, n > 1);
+        int s0 = 0, s1 = 1, s2 = 2;  // ring slots of the pairs i, i + 1 and i + 2
+        for (int i = 0; i < n; ++i) {
+            __syncthreads();  // this tile's planes are written, and those replaced now no longer read
+            const unsigned short *drow = lds.d[i & 1] + (16 * mt + li) * S::CSD + (oz * S::TY + oy) * S::TX + 8 * lg;
+            const unsigned short *xrow[3];  // first input row of the part, per z-offset
+#pragma unroll
+            for (int dz = 0; dz < 3; ++dz)
+                xrow[dz] = lds.x + (16 * nt + li) * S::CSX + 8 * lg + (oz + dz < 2 ? s0 : s1) * S::PAIR
+                         + (((oz + dz) & 1) * S::BY + oy) * S::XR;
+            bf16x8 A[RY];
+#pragma unroll
+            for (int y = 0; y < RY; ++y) A[y] = *reinterpret_cast<const bf16x8 *>(drow + y * S::TX);
+            constexpr int NR = 3 * (RY + 2);  // input rows of the part
+            u32x4 lo[2], hi[2];
+            auto read = [&](int r) __attribute__((always_inline)) {
+                const unsigned short *rp = xrow[r / (RY + 2)] + r % (RY + 2) * S::XR;
+                lo[r & 1] = *reinterpret_cast<const u32x4 *>(rp);
+                hi[r & 1] = *reinterpret_cast<const u32x4 *>(rp + 8);
+            };
+            read(0);
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                const int dz = r / (RY + 2), yi = r % (RY + 2);
+                __builtin_amdgcn_sched_barrier(0);
+                asm volatile("" : "+v"(hi[r & 1]));  // keeps the read at 16 bytes, and its wait here
+                const u32x4 a = lo[r & 1];
+                const unsigned h = hi[r & 1][0];
+                const u32x4 o[3] = {a,
+                                    {__builtin_amdgcn_alignbit(a[1], a[0], 16), __builtin_amdgcn_alignbit(a[2], a[1], 16),
+                                     __builtin_amdgcn_alignbit(a[3], a[2], 16), __builtin_amdgcn_alignbit(h, a[3], 16)},
+                                    {a[1], a[2], a[3], h}};
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx) {
+#pragma unroll
+                    for (int dy = 0; dy < 3; ++dy) {
+                        const int y = yi - dy;
+                        if (y >= 0 && y < RY)
+                            acc[dz * 9 + dy * 3 + dx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                A[y < 0 || y >= RY ? 0 : y], __builtin_bit_cast(bf16x8, o[dx]),
+                                acc[dz * 9 + dy * 3 + dx], 0, 0, 0);
+                    }
+                    if (dx == 0 && r + 1 < NR) {
+                        // issued here, with the other x-offsets' MFMAs to arrive under
+                        __builtin_amdgcn_sched_barrier(6);
+                        read(r + 1);
+                        __builtin_amdgcn_sched_barrier(6);
+                    }
+                }
+                // a unit of the next tile goes to LDS, and its registers to the tile after
+                // that (past the column's last tile whatever is there: no tile reads it,
+                // and its dZ is zero)
+                const int k = r / 3 - 1;
+                if (r % 3 == 0 && k >= 0 && k < NUX) {
+                    put_x(k < 0 ? 0 : k, s2);
+                    load_x(k < 0 ? 0 : k, x0, y0, min(z0 - 1 + S::TZ * (i + 3), g.nz));
+                } else if (r % 3 == 0 && k == NUX) {
+                    put_d(~i & 1);
+                    load_d(x0, y0, z0 + S::TZ * (i + 2), i + 2 < n);
+                }
+            }
+            static_assert((NR - 1) / 3 > NUX, "every unit is staged within a tile");
+            const int o = s0;
+            s0 = s1;
+            s1 = s2;
+            s2 = o;
+        }
+    }
+    {
+        // bias: channel co summed over the threads that stage it, in order
+        float *sS = reinterpret_cast<float *>(&lds);
+        static_assert(size_t(S::UD) * 8 * sizeof(float) <= sizeof(lds), "bias sums fit the buffers");
+        __syncthreads();
+        if (int(threadIdx.x) < S::UD)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) sS[dp * COP + 8 * dv + j] = dsum[j];
+        __syncthreads();
+        if (int(threadIdx.x) < COP) {
+            float s = 0.f;
+            for (int t = 0; t < S::UD / (COP / 8); ++t) s += sS[t * COP + threadIdx.x];
+            P[27 * 32 * COP + threadIdx.x] = s;
+        }
+    }
+    // the parts of a pair, halved until one is left
+    f32x4 *sA = reinterpret_cast<f32x4 *>(&lds);
+    static_assert(size_t(WBLK / 128) * 27 * 64 * 16 <= sizeof(lds), "half the waves' accumulators fit the buffers");
+#pragma unroll
+    for (int n = S::NQ / 2; n >= 1; n /= 2) {
+        __syncthreads();
+        if (q >= n && q < 2 * n)
+#pragma unroll
+            for (int j = 0; j < 27; ++j) sA[((w - n * S::NPAIR) * 27 + j) * 64 + l] = acc[j];
+        __syncthreads();
+        if (q < n)
+#pragma unroll
+            for (int j = 0; j < 27; ++j) acc[j] += sA[(w * 27 + j) * 64 + l];
+    }
+    // [pair][tap][lane][4]: lane (li, lg) holds the output channels of planes 16 mt + 4 lg + r and the input
+    // channel of plane 16 nt + li
+    if (q == 0)
+#pragma unroll
+        for (int j = 0; j < 27; ++j) reinterpret_cast<f32x4 *>(P)[(pair * 27 + j) * 64 + l] = acc[j];
+}
+
+// Sum the per-block partials (FP64, fixed order) into the flat gradient of one
+// layer: W[co][ci][tap] (ci < CI, co < CO) then b[co].  A block takes 64
+// consecutive values of the partial layout; each of its four waves adds every
+// fourth partial, in eight interleaved sums with as many loads in flight, and
+// the 32 sums are added in order.  (One thread per value over all partials
+// took 26 us for 512 partials of 32 -> 32; this takes 6.4 us for 256.)
+__global__ __launch_bounds__(BLK) void k_wgrad_reduce(const float *__restrict__ part, int nblk, int COP, int CI, int CO,
+                                                      float *__restrict__ grad)
+{
+    __shared__ double sum[4][64];
+    const int PS = 27 * 32 * COP + COP;
+    const int i = threadIdx.x & 63, q = threadIdx.x >> 6, idx = blockIdx.x * 64 + i;
+    double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (idx < PS) {
+        int b = q;
+        for (; b + 28 < nblk; b += 32)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) a[k] += double(part[size_t(b + 4 * k) * PS + idx]);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (b + 4 * k < nblk) a[k] += double(part[size_t(b + 4 * k) * PS + idx]);
+    }
+    sum[q][i] = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+    __syncthreads();
+    if (q != 0 || idx >= PS) return;
+    const float v = float((sum[0][i] + sum[1][i]) + (sum[2][i] + sum[3][i]));
+    if (idx < 27 * 32 * COP) {
+        const int r = idx & 3, l = idx >> 2 & 63, pt = idx >> 8, tap = pt % 27, pair = pt / 27;
+        using S = WgradShape<32>;
+        const int co = S::channel_of(16 * (pair >> 1) + 4 * (l >> 4) + r, COP),
+                  ci = S::channel_of(16 * (pair & 1) + (l & 15), 32);
+        if (co < CO && ci < CI) grad[(co * CI + ci) * 27 + tap] = v;
+    } else {
+        const int co = idx - 27 * 32 * COP;
+        if (co < CO) grad[CO * CI * 27 + co] = v;
+    }
+}
+
+template <int COP>
+hipError_t wgrad_launch(const Grid3 &g, const unsigned short *X, const unsigned short *dZ, float *part, int ci, int co,
+                        float *grad, hipStream_t st)
+{
+    using S = WgradShape<COP>;
+    const int ctx = (g.nx + S::TX - 1) / S::TX, cty = (g.ny + S::TY - 1) / S::TY, ctz = (g.nz + S::TZ - 1) / S::TZ;
+    const int ntiles = ctx * cty * ctz, grid = wgrad_grid(g), per_block = (ntiles + grid - 1) / grid;
+    k_wgrad<COP><<<grid, WBLK, 0, st>>>(g, ctx, ctz, ntiles, per_block, X, dZ, part);
+    k_wgrad_reduce<<<(S::PS + 63) / 64, BLK, 0, st>>>(part, grid, COP, ci, co, grad);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t conv(const Grid3 &g, int cin, int cout, int mode, const unsigned short *X, const unsigned short *W,
@@ -951,15 +1058,9 @@ hipError_t conv(const Grid3 &g, int cin, int cout, int mode, const unsigned shor
 hipError_t wgrad(const Grid3 &g, int cip, int cop, const unsigned short *X, const unsigned short *dZ, float *part,
                  int ci, int co, float *grad, hipStream_t st)
 {
-    const int gr = wgrad_grid(g);
-    if (cip == 32 && cop == 32)
-        k_wgrad<32><<<gr, BLK, 0, st>>>(g, X, dZ, part);
-    else if (cip == 32 && cop == 16)
-        k_wgrad<16><<<gr, BLK, 0, st>>>(g, X, dZ, part);
-    else
-        return hipErrorInvalidValue;
-    k_wgrad_reduce<<<(27 * cip * cop + cop + BLK - 1) / BLK, BLK, 0, st>>>(part, gr, cip, cop, ci, co, grad);
-    return hipGetLastError();
+    if (cip == 32 && cop == 32) return wgrad_launch<32>(g, X, dZ, part, ci, co, grad, st);
+    if (cip == 32 && cop == 16) return wgrad_launch<16>(g, X, dZ, part, ci, co, grad, st);
+    return hipErrorInvalidValue;
 }
 
 hipError_t wprep(const float *W, int ci, int co, int cip, int cop, unsigned short *Wf, unsigned short *Wt,
