@@ -274,8 +274,8 @@ def run_order(n=128, calls=20, threshold=0.19, relax=6000):
             "optics_ms_per_call": float(np.median(to)), "optics_mean_s0": float(img.mean()),
             "ms_per_call": ms,
             "msites_per_s": N / (ms / 1e3) / 1e6,
-            "note": "counts-only call: order kernel (reads 5 FP32 values, writes 1 flag byte per site), "
-                    "per-plane count kernel, one small device-to-host copy"}
+            "note": "counts-only call: one kernel (reads 5 FP32 values per site, counts per plane chunk), "
+                    "one small device-to-host copy"}
 
 
 def run_surrogate(n=96, steps=20000, k=32, M=4, iters=3000, train_set="mixed"):

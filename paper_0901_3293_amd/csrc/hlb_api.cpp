@@ -507,10 +507,16 @@ int hlb_get_fz(hlb_ctx *c, double *fz)
     HLB_GUARD(c);
     if (!fz) return set_error(c, HLB_ERR_ARG, "fz is null");
     if (!c->have_fields) return set_error(c, HLB_ERR_STATE, "no fields set");
-    const int nz = c->D.G.nz;
+    const int nz = c->D.G.nz, np = hlb::plane_parts(c->D.G);
+    std::vector<double> part(size_t(nz) * np);
     HIP_TRY(c, hlb::run_fz(c->D, c->p, c->D.part));
-    HIP_TRY(c, hipMemcpyAsync(fz, c->D.part, nz * sizeof(double), hipMemcpyDeviceToHost, c->D.stream));
+    HIP_TRY(c, hipMemcpyAsync(part.data(), c->D.part, part.size() * sizeof(double), hipMemcpyDeviceToHost, c->D.stream));
     HIP_TRY(c, hipStreamSynchronize(c->D.stream));
+    for (int z = 0; z < nz; ++z) {
+        double s = 0.0;
+        for (int k = 0; k < np; ++k) s += part[size_t(z) * np + k];
+        fz[z] = s;
+    }
     for (int z = 0; z < nz; ++z)
         if (!std::isfinite(fz[z])) return set_error(c, HLB_ERR_NONFINITE, "non-finite f(z) at z = %d", z);
     return HLB_OK;
@@ -530,6 +536,23 @@ int hlb_get_order(hlb_ctx *c, double threshold, double *q, double *dir3, unsigne
     double *dq = st, *dd = st + N, *dc = st + 4 * N;
     unsigned char *df = reinterpret_cast<unsigned char *>(st + 4 * N + nz);
     const bool want_flags = defect || defects_z || n_defect;
+    if (want_flags && !q && !dir3 && !defect) {  // counts only
+        const int np = hlb::plane_parts(c->D.G);
+        std::vector<int> cnt(size_t(nz) * np);
+        int *dn = reinterpret_cast<int *>(st);
+        HIP_TRY(c, hlb::run_count(c->D, threshold, dn));
+        HIP_TRY(c, hipMemcpyAsync(cnt.data(), dn, cnt.size() * sizeof(int), hipMemcpyDeviceToHost, c->D.stream));
+        HIP_TRY(c, hipStreamSynchronize(c->D.stream));
+        long long total = 0;
+        for (int z = 0; z < nz; ++z) {
+            long long v = 0;
+            for (int k = 0; k < np; ++k) v += cnt[size_t(z) * np + k];
+            if (defects_z) defects_z[z] = v;
+            total += v;
+        }
+        if (n_defect) *n_defect = total;
+        return HLB_OK;
+    }
     HIP_TRY(c, hlb::run_order(c->D, threshold, q ? dq : nullptr, dir3 ? dd : nullptr, want_flags ? df : nullptr,
                               (defects_z || n_defect) ? dc : nullptr));
     if (q) HIP_TRY(c, hipMemcpyAsync(q, dq, N * 8, hipMemcpyDeviceToHost, c->D.stream));
@@ -574,18 +597,10 @@ int hlb_get_optics(hlb_ctx *c, const hlb_optics_params *op, double *image)
         p.lam[k] = op->wavelength[k];
         p.w[k] = op->weight[k];
     }
-    // scratch: the population buffer that does not hold the state; the image
-    // first, the per-segment transfer matrices after it
+    // the image is staged in the population buffer that does not hold the state
     const size_t cols = size_t(c->D.G.nx) * c->D.G.ny;
-    const size_t e = c->D.fp32 ? 4 : 8;
-    const size_t stage_bytes = size_t(19) * c->D.G.N * e;
     double *st = stage_of(c);
-    const size_t img_bytes = (cols * 8 + 255) & ~size_t(255);
-    double *Tm = st + img_bytes / 8;
-    const size_t tm_bytes = stage_bytes - img_bytes;
-    if (hlb::optics_segments(c->D.G, p.nwl, tm_bytes) < 1)
-        return set_error(c, HLB_ERR_NOMEM, "optics: lattice too small for the transfer-matrix scratch");
-    HIP_TRY(c, hlb::run_optics(c->D, p, Tm, tm_bytes, st));
+    HIP_TRY(c, hlb::run_optics(c->D, p, st));
     HIP_TRY(c, hipMemcpyAsync(image, st, cols * 8, hipMemcpyDeviceToHost, c->D.stream));
     HIP_TRY(c, hipStreamSynchronize(c->D.stream));
     return HLB_OK;

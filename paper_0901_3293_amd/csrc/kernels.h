@@ -124,8 +124,16 @@ hipError_t run_init(Device &D, const PhysParams &p, const double *stage);
 hipError_t run_readout(Device &D, const PhysParams &p, double *stage, double *totals, double *part = nullptr);
 size_t readout_partials(const Geom &G);
 
-// Plane sums of the free-energy density of the current Q into device fz[nz].
-hipError_t run_fz(Device &D, const PhysParams &p, double *fz);
+// Chunks each z-plane is cut into for run_fz and run_count.
+int plane_parts(const Geom &G);
+
+// Sums of the free-energy density of the current Q over the chunks of every
+// plane, into device part[nz][plane_parts(G)].
+hipError_t run_fz(Device &D, const PhysParams &p, double *part);
+
+// Disclination sites (q < threshold) in the chunks of every plane, into device
+// cnt[nz][plane_parts(G)].
+hipError_t run_count(Device &D, double threshold, int *cnt);
 
 // Local order of the current Q into device buffers (any may be null; cnt
 // needs defect): q[N] largest eigenvalue, dir[3][N] unit eigenvector,
@@ -140,10 +148,7 @@ struct OpticsParams {
     int nwl;
     double lam[OPTICS_MAX_WL], w[OPTICS_MAX_WL];
 };
-// Segments per column for tm_bytes of transfer-matrix scratch (0: too small).
-int optics_segments(const Geom &G, int nwl, size_t tm_bytes);
-// image[ny][nx] (device, FP64): weighted S0 behind the analyser.  Tm: device
-// scratch of tm_bytes (per-segment 3x3 transfer matrices), not aliasing image.
-hipError_t run_optics(Device &D, const OpticsParams &op, double *Tm, size_t tm_bytes, double *image);
+// image[ny][nx] (device, FP64): weighted S0 behind the analyser.
+hipError_t run_optics(Device &D, const OpticsParams &op, double *image);
 
 }  // namespace hlb

@@ -38,6 +38,7 @@
 #include <algorithm>
 
 #include "kernels.h"
+#include "order.h"
 #include "site.h"
 #include "sitekern.h"
 #include "tiles.h"
@@ -904,89 +905,6 @@ __global__ __launch_bounds__(BLK) void k_reduce(const double *__restrict__ part,
     }
 }
 
-// Plane sums of the free-energy density: block z sums plane z in a fixed
-// order (FP64), so the profile f(z) is deterministic.
-template <typename T>
-__global__ __launch_bounds__(BLK) void k_fz(Geom G, Coef<T> c, const T *__restrict__ Q, double *__restrict__ fz)
-{
-    const int z = blockIdx.x;
-    const int sxy = G.nx * G.ny;
-    double acc = 0.0;
-    for (int k = threadIdx.x; k < sxy; k += BLK) acc += double(fdens_at(G, c, Q, z * sxy + k));
-    double v[1] = {acc};
-    block_sum<1, BLK>(v, fz + z);
-}
-
-// Largest eigenvalue of a symmetric traceless 3x3 tensor and a unit
-// eigenvector of it, in FP64 (local order, Sec. 2.1; director, Sec. 2.3), by
-// the cyclic Jacobi method: plane rotations over the pairs (0,1), (0,2),
-// (1,2), each zeroing its off-diagonal entry (tangent of the smaller rotation
-// angle), repeated until the off-diagonal mass is below 1e-30 of the squared
-// norm (at most 8 sweeps; 4 suffice in practice).  Unlike the closed form of
-// the characteristic cubic, whose double roots lose half the digits, this
-// keeps every eigenvalue within a few ulps of |Q|.  The director is the
-// rotation's column of the largest diagonal entry, signed so that its last
-// non-zero component is positive.  Q = 0 gives 0 and (0, 0, 1).
-__device__ __forceinline__ void order_site(const double q[5], double &lam, double d[3])
-{
-    double A[3][3] = {{q[0], q[1], q[2]}, {q[1], q[3], q[4]}, {q[2], q[4], -q[0] - q[3]}};
-    double V[3][3] = {{1.0, 0.0, 0.0}, {0.0, 1.0, 0.0}, {0.0, 0.0, 1.0}};
-    double nrm = 0.0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) nrm += A[a][b] * A[a][b];
-    if (!(nrm > 0.0)) {
-        lam = 0.0;
-        d[0] = 0.0;
-        d[1] = 0.0;
-        d[2] = 1.0;
-        return;
-    }
-    const int P[3] = {0, 0, 1}, R[3] = {1, 2, 2};
-#pragma unroll 1
-    for (int sweep = 0; sweep < 8; ++sweep) {
-        const double off = A[0][1] * A[0][1] + A[0][2] * A[0][2] + A[1][2] * A[1][2];
-        if (!(off > 1e-30 * nrm)) break;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const int p = P[k], r = R[k];
-            const double apr = A[p][r];
-            if (apr == 0.0) continue;
-            const double th = (A[r][r] - A[p][p]) / (2.0 * apr);
-            const double t = (th >= 0.0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
-            const double c = 1.0 / sqrt(t * t + 1.0), sn = t * c;
-#pragma unroll
-            for (int m = 0; m < 3; ++m) {
-                const double amp = A[m][p], amr = A[m][r];
-                A[m][p] = c * amp - sn * amr;
-                A[m][r] = sn * amp + c * amr;
-            }
-#pragma unroll
-            for (int m = 0; m < 3; ++m) {
-                const double apm = A[p][m], arm = A[r][m];
-                A[p][m] = c * apm - sn * arm;
-                A[r][m] = sn * apm + c * arm;
-            }
-#pragma unroll
-            for (int m = 0; m < 3; ++m) {
-                const double vmp = V[m][p], vmr = V[m][r];
-                V[m][p] = c * vmp - sn * vmr;
-                V[m][r] = sn * vmp + c * vmr;
-            }
-        }
-    }
-    int k = 0;
-    if (A[1][1] > A[k][k]) k = 1;
-    if (A[2][2] > A[k][k]) k = 2;
-    lam = A[k][k];
-    const double v0 = V[0][k], v1 = V[1][k], v2 = V[2][k];
-    const double sgn = (v2 != 0.0 ? v2 : (v1 != 0.0 ? v1 : v0)) < 0.0 ? -1.0 : 1.0;
-    d[0] = sgn * v0;
-    d[1] = sgn * v1;
-    d[2] = sgn * v2;
-}
-
 // Local order q, director and disclination flag (q < threshold) per site;
 // any output may be null.
 template <typename T>
@@ -1008,6 +926,93 @@ __global__ __launch_bounds__(BLK) void k_order(Geom G, const T *__restrict__ Q, 
     if (defect) defect[s] = lam < threshold ? 1 : 0;
 }
 
+// Chunks of `len` sites that a plane is cut into for the per-plane sums: 1024
+// sites, more where that would take over 16 chunks.
+struct PlaneChunks {
+    int len, n;
+};
+
+inline PlaneChunks plane_chunks(const Geom &G)
+{
+    const int sxy = G.nx * G.ny;
+    PlaneChunks c;
+    c.len = std::max(1024, ((sxy + 15) / 16 + BLK - 1) / BLK * BLK);
+    c.n = (sxy + c.len - 1) / c.len;
+    return c;
+}
+
+// Sums of the free-energy density over the chunks of a plane (block c + nc z),
+// FP64, in a fixed order, so the profile f(z) is deterministic.  (One block per
+// plane left the chip one wave per SIMD: 16.4 us on 64 x 64 x 256 sites, now 9.8.)
+template <typename T>
+__global__ __launch_bounds__(BLK) void k_fz(Geom G, Coef<T> c, const T *__restrict__ Q, PlaneChunks pc,
+                                            double *__restrict__ part)
+{
+    const int z = blockIdx.x / pc.n, k0 = (blockIdx.x - z * pc.n) * pc.len;
+    const int sxy = G.nx * G.ny, k1 = min(sxy, k0 + pc.len);
+    double acc = 0.0;
+    for (int k = k0 + int(threadIdx.x); k < k1; k += BLK) acc += double(fdens_at(G, c, Q, z * sxy + k));
+    double v[1] = {acc};
+    block_sum<1, BLK>(v, part + blockIdx.x);
+}
+
+// Disclination sites per chunk of a plane (block c + nc z), without the fields
+// of the order analysis: the signs of three minors decide (order_below).  5.8
+// us on 64 x 64 x 256 FP32 sites, where the eigen-solve per site, flags and a
+// count over them took 63 + 7.5 us.
+template <typename T>
+__global__ __launch_bounds__(BLK) void k_count(Geom G, const T *__restrict__ Q, double threshold, PlaneChunks pc,
+                                               int *__restrict__ cnt)
+{
+    __shared__ int total;
+    if (threadIdx.x == 0) total = 0;
+    __syncthreads();
+    const int z = blockIdx.x / pc.n, k0 = (blockIdx.x - z * pc.n) * pc.len;
+    const int sxy = G.nx * G.ny, k1 = min(sxy, k0 + pc.len);
+    const size_t N = G.N;
+    int n = 0;
+    for (int k = k0 + int(threadIdx.x); k < k1; k += BLK) {
+        const size_t s = size_t(z) * sxy + k;
+        double q[5];
+#pragma unroll
+        for (int j = 0; j < 5; ++j) q[j] = double(Q[j * N + s]);
+        n += order_below(q, threshold) ? 1 : 0;
+    }
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) n += __shfl_down(n, w);
+    if ((threadIdx.x & 63) == 0) atomicAdd(&total, n);
+    __syncthreads();
+    if (threadIdx.x == 0) cnt[blockIdx.x] = total;
+}
+
+// sin and cos of x: the Taylor sums up to pi/4 (rest under 1e-19), beyond it
+// after the nearest multiple of pi/2, in two parts, is taken off (exact to
+// 1e-17 up to 1e15).
+__device__ __forceinline__ void sincos64(double x, double &sn, double &cs)
+{
+    int n = 0;
+    if (!(fabs(x) <= 0.785)) {
+        const double k = rint(x * 0.63661977236758134308);  // 2 / pi
+        x = fma(-k, 6.12323399573676588614e-17, fma(-k, 1.57079632679489661923, x));
+        n = int((long long)k & 3);
+    }
+    const double y = x * x;
+    double s = 1.0 / 355687428096000.0, c = -1.0 / 6402373705728000.0;  // 1/17!, -1/18!
+    constexpr double S[8] = {-1.0 / 1307674368000.0, 1.0 / 6227020800.0, -1.0 / 39916800.0, 1.0 / 362880.0,
+                             -1.0 / 5040.0, 1.0 / 120.0, -1.0 / 6.0, 1.0};
+    constexpr double C[9] = {1.0 / 20922789888000.0, -1.0 / 87178291200.0, 1.0 / 479001600.0, -1.0 / 3628800.0,
+                             1.0 / 40320.0, -1.0 / 720.0, 1.0 / 24.0, -0.5, 1.0};
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s = fma(s, y, S[k]);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) c = fma(c, y, C[k]);
+    s *= x;
+    sn = n & 1 ? c : s;
+    cs = n & 1 ? s : c;
+    if (n & 2) sn = -sn;
+    if (n == 1 || n == 2) cs = -cs;
+}
+
 // Polarised-light texture of the current Q (Sec. 2.3), the beam along +z
 // (layer z = 0 first).  Unpolarised light behind the polariser at angle
 // phi_in is S = (1, cos 2phi_in, sin 2phi_in, 0)/2; each site acts as a linear
@@ -1015,31 +1020,41 @@ __global__ __launch_bounds__(BLK) void k_order(Geom G, const T *__restrict__ Q, 
 // sin 2beta = 2 dx dy/(dx^2 + dy^2)) and retardance
 // delta = 2 pi q h / lambda (n_o n_e / sqrt(n_o^2 sin^2 alpha + n_e^2 cos^2 alpha) - n_o),
 // cos alpha = d_z, from the FP64 local order q and director d (order_site).
-// A retarder leaves S0 unchanged and acts on (S1, S2, S3) by a 3x3 block; the
-// analyser at phi_out passes (S0 + cos 2phi_out S1 + sin 2phi_out S2)/2.
+// A retarder leaves S0 unchanged and turns (S1, S2, S3) by -delta about the axis
+// (cos 2beta, sin 2beta, 0), kept as the quaternion (cos delta/2, -sin delta/2
+// (cos 2beta, sin 2beta), 0): a layer costs 12 multiplications per wavelength
+// (a 3x3 matrix 27).  The analyser at phi_out passes
+// (S0 + cos 2phi_out S1 + sin 2phi_out S2)/2.
 //
-// Per group of up to OPT_G wavelengths, two kernels: k_optics_seg, one thread
-// per (column, z-segment), multiplies its segment's 3x3 blocks (later layers
-// on the left) into T[seg][g][9][col]; k_optics_compose, one thread per
-// column, applies the segments in order to the polarised input and adds the
-// group's weighted analyser output to the image.  FP64 throughout.
+// A block holds 256 / SPB columns with their SPB z-segments, one thread each,
+// for a group of up to OPT_G wavelengths: a thread multiplies the layers of its
+// segment (later layers on the left), then one thread per column and
+// wavelength the segments, out of LDS.  FP64 throughout.  Bound: the FP64
+// arithmetic (600 instructions per site), two waves per SIMD for its registers:
+// 49 us at 128^3, against 177 us with Jacobi sweeps and 3x3 matrices and 21 us
+// for a second kernel that composed the segments.
 constexpr int OPT_G = 3;
 
-template <typename T>
-__global__ __launch_bounds__(BLK) void k_optics_seg(Geom G, const T *__restrict__ Q, OpticsParams op, int wl0,
-                                                    int seglen, int nseg, double *__restrict__ Tm)
+template <typename T, int SPB>
+__global__ __launch_bounds__(BLK) void k_optics(Geom G, const T *__restrict__ Q, OpticsParams op, int wl0,
+                                                double *__restrict__ image)
 {
+    constexpr int CPB = BLK / SPB;
+    __shared__ double sq[SPB][OPT_G][4][CPB];
+    __shared__ double so[OPT_G][CPB];
     const int cols = G.nx * G.ny;
-    const int id = blockIdx.x * BLK + int(threadIdx.x);
-    if (id >= cols * nseg) return;
-    const int col = id % cols, seg = id / cols;
-    const int z0 = seg * seglen, z1 = min(G.nz, z0 + seglen);
+    const int ci = threadIdx.x % CPB, seg = threadIdx.x / CPB, col = blockIdx.x * CPB + ci;
+    const int ng = min(OPT_G, op.nwl - wl0);
+    const int seglen = (G.nz + SPB - 1) / SPB;
+    const int z0 = seg * seglen, z1 = col < cols ? min(G.nz, z0 + seglen) : 0;
     const size_t N = G.N;
-    double M[OPT_G][9];
+    double w[OPT_G], x[OPT_G], y[OPT_G], zq[OPT_G], half[OPT_G];
 #pragma unroll
-    for (int g = 0; g < OPT_G; ++g)
-#pragma unroll
-        for (int k = 0; k < 9; ++k) M[g][k] = (k % 4 == 0) ? 1.0 : 0.0;
+    for (int g = 0; g < OPT_G; ++g) {
+        w[g] = 1.0;
+        x[g] = y[g] = zq[g] = 0.0;
+        half[g] = g < ng ? 0.5 / op.lam[wl0 + g] : 0.0;
+    }
     const double two_pi_h = 2.0 * 3.14159265358979323846 * op.h;
     const double no2 = op.n_o * op.n_o, ne2 = op.n_e * op.n_e, none = op.n_o * op.n_e;
 #pragma unroll 1
@@ -1052,65 +1067,59 @@ __global__ __launch_bounds__(BLK) void k_optics_seg(Geom G, const T *__restrict_
         const double r2 = d[0] * d[0] + d[1] * d[1];
         double c = 1.0, sn = 0.0;
         if (r2 > 0.0) {
-            c = (d[0] * d[0] - d[1] * d[1]) / r2;
-            sn = 2.0 * d[0] * d[1] / r2;
+            const double ir2 = 1.0 / r2;
+            c = (d[0] * d[0] - d[1] * d[1]) * ir2;
+            sn = 2.0 * d[0] * d[1] * ir2;
         }
         const double cz = d[2] > 1.0 ? 1.0 : (d[2] < -1.0 ? -1.0 : d[2]);
         const double sin2a = 1.0 - cz * cz;
-        const double base = two_pi_h * qo * (none / sqrt(no2 * sin2a + ne2 * cz * cz) - op.n_o);
-        const double cc = c * c, ss = sn * sn, cs = c * sn;
+        const double base = two_pi_h * qo * (none * rsqrt64(no2 * sin2a + ne2 * cz * cz) - op.n_o);
 #pragma unroll
         for (int g = 0; g < OPT_G; ++g) {
-            if (wl0 + g >= op.nwl) break;
-            double sd, cd;
-            sincos(base / op.lam[wl0 + g], &sd, &cd);
-            const double R[9] = {cc + ss * cd, cs * (1.0 - cd), -sn * sd,
-                                 cs * (1.0 - cd), ss + cc * cd, c * sd,
-                                 sn * sd, -c * sd, cd};
-            double P[9];
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-#pragma unroll
-                for (int b = 0; b < 3; ++b)
-                    P[3 * a + b] = R[3 * a] * M[g][b] + R[3 * a + 1] * M[g][3 + b] + R[3 * a + 2] * M[g][6 + b];
-#pragma unroll
-            for (int k = 0; k < 9; ++k) M[g][k] = P[k];
+            if (g >= ng) break;
+            double sd, w1;
+            sincos64(base * half[g], sd, w1);
+            const double x1 = -sd * c, y1 = -sd * sn;
+            const double wn = w1 * w[g] - x1 * x[g] - y1 * y[g];
+            const double xn = w1 * x[g] + x1 * w[g] + y1 * zq[g];
+            const double yn = w1 * y[g] + y1 * w[g] - x1 * zq[g];
+            zq[g] = w1 * zq[g] + x1 * y[g] - y1 * x[g];
+            w[g] = wn;
+            x[g] = xn;
+            y[g] = yn;
         }
     }
-    const int ng = min(OPT_G, op.nwl - wl0);
 #pragma unroll
     for (int g = 0; g < OPT_G; ++g) {
-        if (g >= ng) break;
-#pragma unroll
-        for (int k = 0; k < 9; ++k) Tm[((size_t(seg) * ng + g) * 9 + k) * cols + col] = M[g][k];
+        sq[seg][g][0][ci] = w[g];
+        sq[seg][g][1][ci] = x[g];
+        sq[seg][g][2][ci] = y[g];
+        sq[seg][g][3][ci] = zq[g];
     }
-}
-
-__global__ __launch_bounds__(BLK) void k_optics_compose(int cols, int nseg, OpticsParams op, int wl0,
-                                                        const double *__restrict__ Tm, double *__restrict__ image)
-{
-    const int col = blockIdx.x * BLK + int(threadIdx.x);
-    if (col >= cols) return;
-    const int ng = min(OPT_G, op.nwl - wl0);
-    double out = 0.0;
+    __syncthreads();
+    if (seg < ng) {  // thread (column ci, wavelength g = seg)
+        const int g = seg, used = min(SPB, (G.nz + seglen - 1) / seglen);
+        double a = 1.0, b = 0.0, c = 0.0, d = 0.0;
 #pragma unroll 1
-    for (int g = 0; g < ng; ++g) {
-        const int w = wl0 + g;
-        double v[3] = {0.5 * op.c_in, 0.5 * op.s_in, 0.0};
-#pragma unroll 1
-        for (int seg = 0; seg < nseg; ++seg) {
-            const double *t = Tm + (size_t(seg) * ng + g) * 9 * size_t(cols) + col;
-            double u[3];
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-                u[a] = t[(3 * a) * size_t(cols)] * v[0] + t[(3 * a + 1) * size_t(cols)] * v[1] +
-                       t[(3 * a + 2) * size_t(cols)] * v[2];
-            v[0] = u[0];
-            v[1] = u[1];
-            v[2] = u[2];
+        for (int k = 0; k < used; ++k) {
+            const double a1 = sq[k][g][0][ci], b1 = sq[k][g][1][ci], c1 = sq[k][g][2][ci], d1 = sq[k][g][3][ci];
+            const double an = a1 * a - b1 * b - c1 * c - d1 * d;
+            const double bn = a1 * b + b1 * a + c1 * d - d1 * c;
+            const double cn = a1 * c - b1 * d + c1 * a + d1 * b;
+            d = a1 * d + b1 * c - c1 * b + d1 * a;
+            a = an;
+            b = bn;
+            c = cn;
         }
-        out += op.w[w] * 0.5 * (0.5 + op.c_out * v[0] + op.s_out * v[1]);
+        const double n2 = a * a + b * b + c * c + d * d;  // 1 but for rounding
+        const double v0 = ((a * a + b * b - c * c - d * d) * op.c_in + 2.0 * (b * c - a * d) * op.s_in) / n2;
+        const double v1 = (2.0 * (b * c + a * d) * op.c_in + (a * a - b * b + c * c - d * d) * op.s_in) / n2;
+        so[g][ci] = op.w[wl0 + g] * 0.25 * (1.0 + op.c_out * v0 + op.s_out * v1);
     }
+    __syncthreads();
+    if (seg != 0 || col >= cols) return;
+    double out = 0.0;
+    for (int g = 0; g < ng; ++g) out += so[g][ci];
     image[col] = wl0 == 0 ? out : image[col] + out;
 }
 
@@ -1313,10 +1322,25 @@ hipError_t readout_t(Device &D, const PhysParams &p, double *stage, double *tota
 }
 
 template <typename T>
-hipError_t fz_t(Device &D, const PhysParams &p, double *fz)
+hipError_t fz_t(Device &D, const PhysParams &p, double *part)
 {
-    k_fz<T><<<D.G.nz, BLK, 0, D.stream>>>(D.G, make_coef<T>(p), static_cast<const T *>(D.Q[D.qcur]), fz);
+    const PlaneChunks pc = plane_chunks(D.G);
+    k_fz<T><<<D.G.nz * pc.n, BLK, 0, D.stream>>>(D.G, make_coef<T>(p), static_cast<const T *>(D.Q[D.qcur]), pc, part);
     return hipGetLastError();
+}
+
+template <typename T>
+void optics_t(Device &D, const OpticsParams &op, double *image)
+{
+    const int cols = D.G.nx * D.G.ny;
+    const T *Q = static_cast<const T *>(D.Q[D.qcur]);
+    for (int wl0 = 0; wl0 < op.nwl; wl0 += OPT_G) {
+        // 16 segments where the columns alone give the chip some 500 blocks, 64 below
+        if (cols >= 8192)
+            k_optics<T, 16><<<(cols + 15) / 16, BLK, 0, D.stream>>>(D.G, Q, op, wl0, image);
+        else
+            k_optics<T, 64><<<(cols + 3) / 4, BLK, 0, D.stream>>>(D.G, Q, op, wl0, image);
+    }
 }
 
 }  // namespace
@@ -1334,47 +1358,39 @@ hipError_t run_order(Device &D, double threshold, double *q, double *dir, unsign
     return hipGetLastError();
 }
 
-int optics_segments(const Geom &G, int nwl, size_t scratch_bytes)
-{
-    const long long cols = (long long)G.nx * G.ny;
-    const int ng = nwl < OPT_G ? nwl : OPT_G;  // wavelengths per group
-    long long nseg = (262144 + cols - 1) / cols;  // enough threads to fill the device
-    if (nseg > G.nz) nseg = G.nz;
-    const long long cap = (long long)(scratch_bytes / (size_t(cols) * ng * 9 * 8));
-    if (nseg > cap) nseg = cap;
-    return int(nseg);
-}
+int plane_parts(const Geom &G) { return plane_chunks(G).n; }
 
-hipError_t run_optics(Device &D, const OpticsParams &op, double *Tm, size_t tm_bytes, double *image)
+hipError_t run_count(Device &D, double threshold, int *cnt)
 {
-    const Geom G = D.G;
-    const int cols = G.nx * G.ny;
-    const int nseg = optics_segments(G, op.nwl, tm_bytes);
-    if (nseg < 1) return hipErrorInvalidValue;
-    const int seglen = (G.nz + nseg - 1) / nseg;
-    const int nseg_used = (G.nz + seglen - 1) / seglen;
-    const int nb = int((size_t(cols) * nseg_used + BLK - 1) / BLK);
-    for (int wl0 = 0; wl0 < op.nwl; wl0 += OPT_G) {
-        if (D.fp32)
-            k_optics_seg<float><<<nb, BLK, 0, D.stream>>>(G, static_cast<const float *>(D.Q[D.qcur]), op, wl0,
-                                                          seglen, nseg_used, Tm);
-        else
-            k_optics_seg<double><<<nb, BLK, 0, D.stream>>>(G, static_cast<const double *>(D.Q[D.qcur]), op, wl0,
-                                                           seglen, nseg_used, Tm);
-        k_optics_compose<<<(cols + BLK - 1) / BLK, BLK, 0, D.stream>>>(cols, nseg_used, op, wl0, Tm, image);
-    }
+    const PlaneChunks pc = plane_chunks(D.G);
+    if (D.fp32)
+        k_count<float><<<D.G.nz * pc.n, BLK, 0, D.stream>>>(D.G, static_cast<const float *>(D.Q[D.qcur]), threshold,
+                                                            pc, cnt);
+    else
+        k_count<double><<<D.G.nz * pc.n, BLK, 0, D.stream>>>(D.G, static_cast<const double *>(D.Q[D.qcur]), threshold,
+                                                             pc, cnt);
     return hipGetLastError();
 }
 
-hipError_t run_fz(Device &D, const PhysParams &p, double *fz)
+hipError_t run_optics(Device &D, const OpticsParams &op, double *image)
 {
-    return D.fp32 ? fz_t<float>(D, p, fz) : fz_t<double>(D, p, fz);
+    if (D.fp32)
+        optics_t<float>(D, op, image);
+    else
+        optics_t<double>(D, op, image);
+    return hipGetLastError();
+}
+
+hipError_t run_fz(Device &D, const PhysParams &p, double *part)
+{
+    return D.fp32 ? fz_t<float>(D, p, part) : fz_t<double>(D, p, part);
 }
 
 size_t partial_doubles(int nx, int ny, int nz)
 {
     // per-site blocks x 4 (readout moments) + per-site blocks (free energy),
-    // or one value per z-plane (free-energy profile)
+    // or the chunks of every z-plane (free-energy profile; at least 1024 sites
+    // each but the last)
     return size_t(5) * site_blocks(nx * ny * nz) + size_t(nz) + 16;
 }
 

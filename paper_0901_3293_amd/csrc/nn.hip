@@ -41,8 +41,6 @@ __device__ __forceinline__ unsigned f2bf2(float a, float b)
     return __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
 
-__device__ __forceinline__ float bf2f(unsigned short h) { return __uint_as_float(unsigned(h) << 16); }
-
 // K = 32 slices of the nine (y, z) taps of one x-offset, times three: the 32
 // input channels of one tap, or the 16 channels of two taps.
 constexpr int nksteps(int cin) { return cin == 32 ? 27 : 15; }
