@@ -147,8 +147,8 @@ struct PlaneLoader {
     }
 };
 
-// Derivatives of the 5-component Q at staged coordinate r of plane p: the
-// value and its in-plane neighbours from the staged slot `mid` (two-site
+// Q, twice its derivatives and its Laplacian at staged coordinate r of plane p:
+// the value and its in-plane neighbours from the staged slot `mid` (two-site
 // halo, RN points per component), the z-neighbours from `lo` (plane p-1,
 // registers of the thread owning the point) and the staged slot `hi`
 // (plane p+1).
@@ -159,15 +159,9 @@ __device__ __forceinline__ void stencil_staged(const T lo[5], const T *mid, cons
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
         const int o = k * Shape::RN + r;
-        const T v = mid[o];
-        const T xp = mid[o + 1], xm = mid[o - 1];
-        const T yp = mid[o + Shape::RX], ym = mid[o - Shape::RX];
-        const T zp = hi[o], zm = lo[k];
-        q[k] = v;
-        d[0][k] = T(0.5) * (xp - xm);
-        d[1][k] = T(0.5) * (yp - ym);
-        d[2][k] = T(0.5) * (zp - zm);
-        lap[k] = ((xp + xm) + (yp + ym)) + (zp + zm) - T(6) * v;
+        q[k] = mid[o];
+        stencil7(q[k], mid[o + 1], mid[o - 1], mid[o + Shape::RX], mid[o - Shape::RX], hi[o], lo[k], d[0][k], d[1][k],
+                 d[2][k], lap[k]);
     }
 }
 
@@ -179,21 +173,15 @@ __device__ __forceinline__ void stencil_ring(const T *lo, const T *mid, const T 
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
         const int o = k * Shape::RN + r;
-        const T v = mid[o];
-        const T xp = mid[o + 1], xm = mid[o - 1];
-        const T yp = mid[o + Shape::RX], ym = mid[o - Shape::RX];
-        const T zp = hi[o], zm = lo[o];
-        q[k] = v;
-        d[0][k] = T(0.5) * (xp - xm);
-        d[1][k] = T(0.5) * (yp - ym);
-        d[2][k] = T(0.5) * (zp - zm);
-        lap[k] = ((xp + xm) + (yp + ym)) + (zp + zm) - T(6) * v;
+        q[k] = mid[o];
+        stencil7(q[k], mid[o + 1], mid[o - 1], mid[o + Shape::RX], mid[o - Shape::RX], hi[o], lo[o], d[0][k], d[1][k],
+                 d[2][k], lap[k]);
     }
 }
 
-// Derivatives of a 5-component field held on the evaluation plane (PX x PY,
-// PN points per component) at point r: value and in-plane neighbours from
-// `mid`, z-neighbours from registers.
+// Same for a 5-component field held on the evaluation plane (PX x PY, PN points
+// per component) at point r: value and in-plane neighbours from `mid`,
+// z-neighbours from registers.
 template <class Shape, typename T>
 __device__ __forceinline__ void stencil_eval(const T lo[5], const T *mid, const T hi[5], int r, T q[5],
                                              T d[3][5], T lap[5])
@@ -201,20 +189,14 @@ __device__ __forceinline__ void stencil_eval(const T lo[5], const T *mid, const 
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
         const int o = k * Shape::PN + r;
-        const T v = mid[o];
-        const T xp = mid[o + 1], xm = mid[o - 1];
-        const T yp = mid[o + Shape::PX], ym = mid[o - Shape::PX];
-        const T zp = hi[k], zm = lo[k];
-        q[k] = v;
-        d[0][k] = T(0.5) * (xp - xm);
-        d[1][k] = T(0.5) * (yp - ym);
-        d[2][k] = T(0.5) * (zp - zm);
-        lap[k] = ((xp + xm) + (yp + ym)) + (zp + zm) - T(6) * v;
+        q[k] = mid[o];
+        stencil7(q[k], mid[o + 1], mid[o - 1], mid[o + Shape::PX], mid[o - Shape::PX], hi[k], lo[k], d[0][k], d[1][k],
+                 d[2][k], lap[k]);
     }
 }
 
-// u and its centred gradient W_ab = d_b u_a at staged coordinate r of plane
-// p: in-plane from `mid`, z from `lo` (registers, plane p-1) and `hi`.
+// u and twice its centred gradient, W_ab = 2 d_b u_a, at staged coordinate r of
+// plane p: in-plane from `mid`, z from `lo` (registers, plane p-1) and `hi`.
 template <class Shape, typename T>
 __device__ __forceinline__ void velocity_staged(const T lo[3], const T *mid, const T *hi, int r, T uc[3],
                                                 T W[3][3])
@@ -223,9 +205,9 @@ __device__ __forceinline__ void velocity_staged(const T lo[3], const T *mid, con
     for (int a = 0; a < 3; ++a) {
         const int o = a * Shape::RN + r;
         uc[a] = mid[o];
-        W[a][0] = T(0.5) * (mid[o + 1] - mid[o - 1]);
-        W[a][1] = T(0.5) * (mid[o + Shape::RX] - mid[o - Shape::RX]);
-        W[a][2] = T(0.5) * (hi[o] - lo[a]);
+        W[a][0] = mid[o + 1] - mid[o - 1];
+        W[a][1] = mid[o + Shape::RX] - mid[o - Shape::RX];
+        W[a][2] = hi[o] - lo[a];
     }
 }
 
@@ -311,7 +293,7 @@ __global__ __launch_bounds__(KernelTile<T>::NB) __attribute__((amdgpu_waves_per_
         if (eval && (tile || (p >= B.z0 && p < B.z1))) {
             T q[5], d[3][5], lap[5], P[3][3], fd, H[5];
             stencil_ring<Shape>(sQ[s1], sQ[s2], sQ[s3], rc, q, d, lap);
-            site_stress(c, q, d, lap, P, fd, H);
+            site_stress<T, 2>(c, q, d, lap, P, fd, H);
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 Pc[a * Shape::PN + pc] = P[a][0];
@@ -429,14 +411,14 @@ __global__ __launch_bounds__(KernelTile<T>::NB) __attribute__((amdgpu_waves_per_
             stencil_ring<Shape>(sQ[s1], sQ[s2], sQ[s3], rc, q, d, lap);
             if constexpr (SPLIT) {
                 T tau3[3];
-                site_split(c, q, d, lap, sig0, tau3, h0, fd);
+                site_split<T, 2>(c, q, d, lap, sig0, tau3, h0, fd);
 #pragma unroll
                 for (int k = 0; k < 3; ++k) Pc[k * Shape::PN + pc] = tau3[k];
                 Pz[0] = tau3[1];
                 Pz[1] = tau3[2];
             } else {
                 T P[3][3], H[5];
-                site_stress(c, q, d, lap, P, fd, H);
+                site_stress<T, 2>(c, q, d, lap, P, fd, H);
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
                     Pc[a * Shape::PN + pc] = P[a][0];
@@ -452,10 +434,10 @@ __global__ __launch_bounds__(KernelTile<T>::NB) __attribute__((amdgpu_waves_per_
                     // b_a = d_b tau_ab + h_a at plane p-1: in-plane differences from LDS,
                     // z differences from the own point's tau at planes p and p-2
                     const T *txy = Pp, *txz = Pp + Shape::PN, *tyz = Pp + 2 * Shape::PN;
-                    f[0] = T(0.5) * ((txy[pc + Shape::PX] - txy[pc - Shape::PX]) + (Pz[0] - Pz2[0])) + h1[0];
-                    f[1] = T(0.5) * ((Pz[1] - Pz2[1]) - (txy[pc + 1] - txy[pc - 1])) + h1[1];
-                    f[2] = T(0.5) * (-(txz[pc + 1] - txz[pc - 1]) - (tyz[pc + Shape::PX] - tyz[pc - Shape::PX])) +
-                           h1[2];
+                    f[0] = fmat(T(0.5), (txy[pc + Shape::PX] - txy[pc - Shape::PX]) + (Pz[0] - Pz2[0]), h1[0]);
+                    f[1] = fmat(T(0.5), (Pz[1] - Pz2[1]) - (txy[pc + 1] - txy[pc - 1]), h1[1]);
+                    f[2] = fmat(T(0.5), -(txz[pc + 1] - txz[pc - 1]) - (tyz[pc + Shape::PX] - tyz[pc - Shape::PX]),
+                                h1[2]);
                     lb_collide_split(c, g, f, sig1, uu, rho);
                 } else {
 #pragma unroll
@@ -591,7 +573,7 @@ __global__ __launch_bounds__(KernelTile<T>::NB) void k_qupdate(Geom G, Coef<T> c
             T q[5], d[3][5], lap[5], uc[3], R[5];
             stencil_staged<Shape>(qmm, sQ[sc], sQ[sn], rc, q, d, lap);
             velocity_staged<Shape>(umm, sU[sc], sU[sn], rc, uc, W0);
-            site_rhs(c, q, d, lap, uc, W0, R);
+            site_rhs<T, 2>(c, q, d, lap, uc, W0, R);
 #pragma unroll
             for (int k = 0; k < 5; ++k) qs0[k] = q[k] + R[k];
             if (ONE)
@@ -601,7 +583,7 @@ __global__ __launch_bounds__(KernelTile<T>::NB) void k_qupdate(Geom G, Coef<T> c
         if (tile && p - 1 >= B.z0) {
             T q[5], d[3][5], lap[5], R[5];
             stencil_eval<Shape>(qs2, Sprev, qs0, pc, q, d, lap);
-            site_rhs(c, q, d, lap, umm, Wmm, R);
+            site_rhs<T, 2>(c, q, d, lap, umm, Wmm, R);
             if (mine) {
                 const size_t o = size_t(p - 1) * sxy + size_t(gy) * G.nx + gx;
 #pragma unroll

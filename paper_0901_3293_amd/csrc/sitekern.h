@@ -140,6 +140,18 @@ __device__ __forceinline__ int pull_from(const Geom &G, const Nbr &S, int cx, in
     return xs + G.nx * (ys + G.ny * zs);
 }
 
+// Differences of a value's neighbours (twice the centred derivatives) and its
+// 7-point Laplacian.
+template <typename T>
+__device__ __forceinline__ void stencil7(T v, T xp, T xm, T yp, T ym, T zp, T zm, T &dx, T &dy, T &dz, T &lap)
+{
+    dx = xp - xm;
+    dy = yp - ym;
+    dz = zp - zm;
+    lap = fmat(T(-6), v, ((xp + xm) + (yp + ym)) + (zp + zm));
+}
+
+// Q, twice its derivatives and its Laplacian at one site.
 template <typename T>
 __device__ __forceinline__ void gather_q(const T *__restrict__ Q, int N, const Off<T> &O, T q[5], T d[3][5],
                                          T lap[5])
@@ -147,18 +159,13 @@ __device__ __forceinline__ void gather_q(const T *__restrict__ Q, int N, const O
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
         const T *P = plane(Q, c, N);
-        const T v = *at(P, O.s);
-        const T xp = *at(P, O.nb[0]), xm = *at(P, O.nb[1]);
-        const T yp = *at(P, O.nb[2]), ym = *at(P, O.nb[3]);
-        const T zp = *at(P, O.nb[4]), zm = *at(P, O.nb[5]);
-        q[c] = v;
-        d[0][c] = T(0.5) * (xp - xm);
-        d[1][c] = T(0.5) * (yp - ym);
-        d[2][c] = T(0.5) * (zp - zm);
-        lap[c] = ((xp + xm) + (yp + ym)) + (zp + zm) - T(6) * v;
+        q[c] = *at(P, O.s);
+        stencil7(q[c], *at(P, O.nb[0]), *at(P, O.nb[1]), *at(P, O.nb[2]), *at(P, O.nb[3]), *at(P, O.nb[4]),
+                 *at(P, O.nb[5]), d[0][c], d[1][c], d[2][c], lap[c]);
     }
 }
 
+// u and twice its gradient, W_ab = 2 d_b u_a.
 template <typename T>
 __device__ __forceinline__ void gather_u(const T *__restrict__ u, int N, const Off<T> &O, T uc[3], T W[3][3])
 {
@@ -166,9 +173,9 @@ __device__ __forceinline__ void gather_u(const T *__restrict__ u, int N, const O
     for (int a = 0; a < 3; ++a) {
         const T *P = plane(u, a, N);
         uc[a] = *at(P, O.s);
-        W[a][0] = T(0.5) * (*at(P, O.nb[0]) - *at(P, O.nb[1]));
-        W[a][1] = T(0.5) * (*at(P, O.nb[2]) - *at(P, O.nb[3]));
-        W[a][2] = T(0.5) * (*at(P, O.nb[4]) - *at(P, O.nb[5]));
+        W[a][0] = *at(P, O.nb[0]) - *at(P, O.nb[1]);
+        W[a][1] = *at(P, O.nb[2]) - *at(P, O.nb[3]);
+        W[a][2] = *at(P, O.nb[4]) - *at(P, O.nb[5]);
     }
 }
 
@@ -194,7 +201,7 @@ __device__ __forceinline__ T stress_at(const Geom &G, const Coef<T> &c, const T 
     const Off<T> O = offsets<T>(nbr_of(G, s));
     T q[5], d[3][5], lap[5], P[3][3], fd, H[5];
     gather_q(Q, G.N, O, q, d, lap);
-    site_stress(c, q, d, lap, P, fd, H);
+    site_stress<T, 2>(c, q, d, lap, P, fd, H);
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
@@ -231,7 +238,7 @@ __device__ __forceinline__ T split_at(const Geom &G, const Coef<T> &c, const T *
     const Off<T> O = offsets<T>(nbr_of(G, s));
     T q[5], d[3][5], lap[5], sig[6], tau3[3], h[3], fd;
     gather_q(Q, N, O, q, d, lap);
-    site_split(c, q, d, lap, sig, tau3, h, fd);
+    site_split<T, 2>(c, q, d, lap, sig, tau3, h, fd);
 #pragma unroll
     for (int k = 0; k < 6; ++k) *at(plane(P, k, N), O.s) = sig[k];
 #pragma unroll
@@ -247,12 +254,12 @@ template <typename T>
 __device__ __forceinline__ void split_force(const T *__restrict__ P, int N, const Off<T> &O, T b[3])
 {
     const T *txy = plane(P, 6, N), *txz = plane(P, 7, N), *tyz = plane(P, 8, N);
-    b[0] = T(0.5) * ((*at(txy, O.nb[2]) - *at(txy, O.nb[3])) + (*at(txz, O.nb[4]) - *at(txz, O.nb[5]))) +
-           *at(plane(P, 9, N), O.s);
-    b[1] = T(0.5) * ((*at(tyz, O.nb[4]) - *at(tyz, O.nb[5])) - (*at(txy, O.nb[0]) - *at(txy, O.nb[1]))) +
-           *at(plane(P, 10, N), O.s);
-    b[2] = T(0.5) * (-(*at(txz, O.nb[0]) - *at(txz, O.nb[1])) - (*at(tyz, O.nb[2]) - *at(tyz, O.nb[3]))) +
-           *at(plane(P, 11, N), O.s);
+    b[0] = fmat(T(0.5), (*at(txy, O.nb[2]) - *at(txy, O.nb[3])) + (*at(txz, O.nb[4]) - *at(txz, O.nb[5])),
+                *at(plane(P, 9, N), O.s));
+    b[1] = fmat(T(0.5), (*at(tyz, O.nb[4]) - *at(tyz, O.nb[5])) - (*at(txy, O.nb[0]) - *at(txy, O.nb[1])),
+                *at(plane(P, 10, N), O.s));
+    b[2] = fmat(T(0.5), -(*at(txz, O.nb[0]) - *at(txz, O.nb[1])) - (*at(tyz, O.nb[2]) - *at(tyz, O.nb[3])),
+                *at(plane(P, 11, N), O.s));
 }
 
 // LB step of the split coupling at one site: pull, collide with the stress in
@@ -345,7 +352,7 @@ __device__ __forceinline__ void pred_at(const Geom &G, const Coef<T> &c, const T
     T q[5], d[3][5], lap[5], uc[3], W[3][3], R[5];
     gather_q(Q, N, O, q, d, lap);
     gather_u(u, N, O, uc, W);
-    site_rhs(c, q, d, lap, uc, W, R);
+    site_rhs<T, 2>(c, q, d, lap, uc, W, R);
 #pragma unroll
     for (int k = 0; k < 5; ++k) *at(plane(Qs, k, N), O.s) = q[k] + R[k];
 }
@@ -363,7 +370,7 @@ __device__ __forceinline__ void corr_at(const Geom &G, const Coef<T> &c, T *__re
     for (int k = 0; k < 5; ++k) qn[k] = *at(plane(Q, k, N), O.s);  // issued with the stencil loads
     gather_q(Qs, N, O, q, d, lap);
     gather_u(u, N, O, uc, W);
-    site_rhs(c, q, d, lap, uc, W, R);
+    site_rhs<T, 2>(c, q, d, lap, uc, W, R);
 #pragma unroll
     for (int k = 0; k < 5; ++k) *at(plane(Q, k, N), O.s) = T(0.5) * (qn[k] + q[k] + R[k]);
 }
@@ -375,6 +382,10 @@ __device__ __forceinline__ T fdens_at(const Geom &G, const Coef<T> &c, const T *
     const Off<T> O = offsets<T>(nbr_of(G, s));
     T q[5], d[3][5], lap[5], Qf[3][3], dQ[3][3][3], CQ[3][3], Q2[3][3], M[3][3], div[3];
     gather_q(Q, G.N, O, q, d, lap);
+#pragma unroll
+    for (int g = 0; g < 3; ++g)
+#pragma unroll
+        for (int k = 0; k < 5; ++k) d[g][k] *= T(0.5);
     full3(q, Qf);
     full_grad(d, dQ);
     curl(dQ, CQ);
@@ -405,6 +416,19 @@ Coef<T> make_coef(const PhysParams &p)
     c.rho0 = T(p.rho0);
     c.omega = T(1.0 / p.tau);
     c.pref = T(1.0 - 0.5 / p.tau);
+    c.lin0 = T(-(p.A0 * (1.0 - p.gamma / 3.0) + 4.0 * p.K * p.q0 * p.q0));
+    c.Kq0 = T(p.K * p.q0);
+    c.K4 = T(0.25 * p.K);
+    c.K8 = T(0.125 * p.K);
+    c.xip = T(p.xi + 1.0);
+    c.xim = T(1.0 - p.xi);
+    c.xi23 = T(2.0 * p.xi / 3.0);
+    c.hp = T(0.25 * (p.xi + 1.0));
+    c.hm = T(0.25 * (p.xi - 1.0));
+    c.xih = T(0.5 * p.xi);
+    c.xi3 = T(p.xi / 3.0);
+    c.xi6 = T(p.xi / 6.0);
+    c.xi9 = T(p.xi / 9.0);
     return c;
 }
 
