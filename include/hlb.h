@@ -237,10 +237,12 @@ int hlb_set_state(hlb_ctx *ctx, const void *host_buf, size_t nbytes);
 
 /* Step schedules.  HLB_SCHED_SITES: four sweeps with one lattice site per
  * thread (stress to HBM, LB with its divergence, predictor, corrector in
- * place).  HLB_SCHED_TILED: three sweeps in which 2.5D z-marching LDS tiles
- * hold the stress and the predictor stage (recomputed on a one-site halo
- * ring; tiles of 32 x 8 sites in FP32 and 16 x 12 in FP64), tz planes per
- * tile column (0: 16).  HLB_SCHED_MIXED: the per-site stress and LB sweeps,
+ * place), on lattices too small to fill the device two sweeps of the same
+ * arithmetic, bit for bit (stress and LB, predictor and corrector).
+ * HLB_SCHED_TILED: three sweeps in which 2.5D z-marching LDS tiles hold the
+ * stress and the predictor stage (recomputed on a one-site halo ring; tiles
+ * of 32 x 8 sites in FP32 and 16 x 12 in FP64), tz planes per tile column
+ * (0: 16).  HLB_SCHED_MIXED: the per-site stress and LB sweeps,
  * then the tiled predictor-corrector.  HLB_SCHED_FUSED: the tiled stress
  * fused with the LB step (the force never leaves the CU), then the per-site
  * predictor and corrector.  HLB_SCHED_FUSED_TILED: the fused stress and LB

@@ -16,6 +16,7 @@
 //  per site cross HBM):
 //   k_stress  Q^n -> Pi;  k_lb  g, div Pi -> g', u^n;
 //   k_qpred   Q^n, u^n -> Q*;  k_qcorr  Q*, u^n -> Q^{n+1} (in place)
+//  on small lattices in pairs (k_blb, k_bq; see small_lattice)
 //  TILED (3 sweeps; the stress and the predictor stage live in LDS of 2.5D
 //  z-marching tiles and are recomputed on a one-site halo ring; 65 values):
 //   k_qforce  Q^n -> F^n;  k_lbf  g, F^n -> g', u^n;  k_qupdate  Q^n, u^n -> Q^{n+1}
@@ -708,6 +709,167 @@ __global__ __launch_bounds__(BLK, sizeof(T) == 8 ? 4 : 1) void k_qcorr(Geom G, C
     if (s < G.N) corr_at(G, c, Q, Qs, u, s);
 }
 
+// ---------------------------------------------------------------- small lattices
+// The per-site sweeps in pairs, over bricks of sites: k_blb is k_stress and
+// k_lb, k_bq is k_qpred and k_qcorr.  A block evaluates the first of the two on
+// its brick and the brick's six faces, one point per thread, into LDS, and the
+// second on the brick out of LDS; the stencils come from global memory as in
+// the per-site sweeps, whose results these give bit for bit.  That is about
+// twice the evaluations, but on a lattice that does not fill the chip a kernel
+// takes 3.5 us or more, whatever it computes, and a step has two of them instead
+// of four (see small_lattice).
+template <int BX_, int BY_, int BZ_>
+struct Brick {
+    static constexpr int BX = BX_, BY = BY_, BZ = BZ_;
+    static constexpr int NT = BX * BY * BZ;                                     // sites, the first threads
+    static constexpr int FX = 2 * BY * BZ, FY = 2 * BX * BZ, FZ = 2 * BX * BY;  // face points
+    static constexpr int NP = NT + FX + FY + FZ, NB = (NP + 63) / 64 * 64;      // points; threads
+    static constexpr int PX = BX + 2, PY = BY + 2, PN = PX * PY * (BZ + 2);     // plane of a value in LDS
+    static_assert(NB <= 1024, "one point per thread");
+
+    // Thread t's point (t < NP): coordinates in the brick, -1 and BX, BY, BZ on the faces.
+    __device__ static __forceinline__ void point(int t, int &i, int &j, int &k)
+    {
+        if (t < NT) {
+            i = t % BX;
+            j = t / BX % BY;
+            k = t / (BX * BY);
+        } else if ((t -= NT) < FX) {
+            j = t % BY;
+            k = t / BY % BZ;
+            i = t < FX / 2 ? -1 : BX;
+        } else if ((t -= FX) < FY) {
+            i = t % BX;
+            k = t / BX % BZ;
+            j = t < FY / 2 ? -1 : BY;
+        } else {
+            t -= FY;
+            i = t % BX;
+            j = t / BX % BY;
+            k = t < FZ / 2 ? -1 : BZ;
+        }
+    }
+    static int blocks(const Geom &G)
+    {
+        return ((G.nx + BX - 1) / BX) * ((G.ny + BY - 1) / BY) * ((G.nz + BZ - 1) / BZ);
+    }
+};
+
+// The point of a thread: its site and neighbours (periodic; where the brick
+// hangs over the lattice past its first halo plane any site does), its place in
+// an LDS plane, and whether it is a site of the brick.
+struct BrickPoint {
+    Nbr S;
+    int p;
+    bool mine;
+};
+
+template <class B>
+__device__ __forceinline__ BrickPoint brick_point(const Geom &G, int block)
+{
+    const int nbx = (G.nx + B::BX - 1) / B::BX, nby = (G.ny + B::BY - 1) / B::BY;
+    const int r = block / nbx, bz = r / nby;
+    int i, j, k;
+    // the threads past the last point repeat it (same values to the same places)
+    B::point(min(int(threadIdx.x), B::NP - 1), i, j, k);
+    int x = (block - r * nbx) * B::BX + i, y = (r - bz * nby) * B::BY + j, z = bz * B::BZ + k;
+    BrickPoint b;
+    b.mine = int(threadIdx.x) < B::NT && x < G.nx && y < G.ny && z < G.nz;
+    b.p = ((k + 1) * B::PY + j + 1) * B::PX + i + 1;
+    auto wrap1 = [](int v, int n) __attribute__((always_inline)) {
+        v += v < 0 ? n : 0;
+        v -= v >= n ? n : 0;
+        return min(v, n - 1);
+    };
+    x = wrap1(x, G.nx);
+    y = wrap1(y, G.ny);
+    z = wrap1(z, G.nz);
+    b.S = nbr_at(G, x + G.nx * (y + G.ny * z), x, y, z);
+    return b;
+}
+
+template <typename T, bool SPLIT, class B>
+__global__ __launch_bounds__(B::NB) void k_blb(Geom G, Coef<T> c, int nblocks, const T *__restrict__ Q,
+                                               const T *__restrict__ gin, T *__restrict__ gout, T *__restrict__ u)
+{
+    constexpr int PN = B::PN, DX = 1, DY = B::PX, DZ = B::PX * B::PY;
+    __shared__ T sP[SPLIT ? 3 : 9][PN];
+    const int block = logical_block();
+    if (block >= nblocks) return;
+    const BrickPoint b = brick_point<B>(G, block);
+    const int N = G.N, p = b.p;
+    const Off<T> O = offsets<T>(b.S);
+    T g[19];
+    if (b.mine)
+#pragma unroll
+        for (int i = 0; i < 19; ++i) g[i] = pop_load<false>(plane(gin, i, N), pull_off(O, CX[i], CY[i], CZ[i]));
+    T q[5], d[3][5], lap[5], fd, sig[6], h[3];
+    gather_q(Q, N, O, q, d, lap);
+    if constexpr (SPLIT) {
+        T tau3[3];
+        site_split<T, 2>(c, q, d, lap, sig, tau3, h, fd);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) sP[k][p] = tau3[k];
+    } else {
+        T P[3][3], H[5];
+        site_stress<T, 2>(c, q, d, lap, P, fd, H);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) sP[k][p] = P[k / 3][k % 3];
+    }
+    __syncthreads();
+    if (!b.mine) return;
+    T f[3], uu[3], rho;
+    if constexpr (SPLIT) {
+        const T *txy = sP[0], *txz = sP[1], *tyz = sP[2];
+        f[0] = fmat(T(0.5), (txy[p + DY] - txy[p - DY]) + (txz[p + DZ] - txz[p - DZ]), h[0]);
+        f[1] = fmat(T(0.5), (tyz[p + DZ] - tyz[p - DZ]) - (txy[p + DX] - txy[p - DX]), h[1]);
+        f[2] = fmat(T(0.5), -(txz[p + DX] - txz[p - DX]) - (tyz[p + DY] - tyz[p - DY]), h[2]);
+        lb_collide_split(c, g, f, sig, uu, rho);
+    } else {
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            f[a] = T(0.5) * ((sP[3 * a][p + DX] - sP[3 * a][p - DX]) + (sP[3 * a + 1][p + DY] - sP[3 * a + 1][p - DY]) +
+                             (sP[3 * a + 2][p + DZ] - sP[3 * a + 2][p - DZ]));
+        lb_collide(c, g, f, uu, rho);
+    }
+#pragma unroll
+    for (int i = 0; i < 19; ++i) pop_store<false>(plane(gout, i, N), O.s, g[i]);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) *at(plane(u, a, N), O.s) = uu[a];
+}
+
+template <typename T, class B>
+__global__ __launch_bounds__(B::NB) void k_bq(Geom G, Coef<T> c, int nblocks, const T *__restrict__ Q,
+                                              const T *__restrict__ u, T *__restrict__ Qout)
+{
+    constexpr int PN = B::PN, DX = 1, DY = B::PX, DZ = B::PX * B::PY;
+    __shared__ T sS[5][PN];
+    const int block = logical_block();
+    if (block >= nblocks) return;
+    const BrickPoint b = brick_point<B>(G, block);
+    const int N = G.N, p = b.p;
+    const Off<T> O = offsets<T>(b.S);
+    T qn[5], q[5], d[3][5], lap[5], uc[3], W[3][3], R[5];
+    gather_q(Q, N, O, qn, d, lap);
+    gather_u(u, N, O, uc, W);
+    site_rhs<T, 2>(c, qn, d, lap, uc, W, R);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        q[k] = qn[k] + R[k];
+        sS[k][p] = q[k];
+    }
+    __syncthreads();
+    if (!b.mine) return;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        const T *P = sS[k] + p;
+        stencil7(q[k], P[DX], P[-DX], P[DY], P[-DY], P[DZ], P[-DZ], d[0][k], d[1][k], d[2][k], lap[k]);
+    }
+    site_rhs<T, 2>(c, q, d, lap, uc, W, R);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) *at(plane(Qout, k, N), O.s) = T(0.5) * (qn[k] + q[k] + R[k]);
+}
+
 // D3Q15 predictor-corrector LB, the two passes (see pc1_at, pc2_at).
 template <typename T, bool SPLIT>
 __global__ __launch_bounds__(BLK) void k_pc1(Geom G, Coef<T> c, const T *__restrict__ g, const T *__restrict__ Pi,
@@ -1176,6 +1338,25 @@ int tz_fill_t(const Device &D, int rounds)
     return int((D.G.nz + chunks - 1) / chunks);
 }
 
+// Lattices whose per-site sweeps run in pairs over bricks: those of at most one
+// brick per CU, which is as far as the doubled evaluations stay hidden behind
+// the two launches saved.  A step in us, single sweeps and pairs: 16^3 (32 bricks)
+// 13.7 and 9.3 in FP32, 17.0 and 12.1 in FP64; 32^3 (256) 13.3 and 9.3, 17.8 and
+// 13.2; past one brick per CU 64 x 32 x 32 (512) 13.3 and 12.5, but 19.2 and 20.2
+// in FP64; 40^3 (600) 14.2 and 17.2, 19.7 and 25.8; 64^3 (2048) 26 and 32, 50 and
+// 65.  The brick: larger ones (8 x 8 x 4, 16 x 8 x 4) evaluate fewer face points,
+// but leave CUs idle on the lattices in question.
+typedef Brick<16, 4, 2> StepBrick;
+
+bool small_lattice(const Geom &G)
+{
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return false;
+    return StepBrick::blocks(G) <= cus;
+}
+
 template <typename T, bool SPLIT>
 hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *timer)
 {
@@ -1198,6 +1379,8 @@ hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *time
     const TileGrid tg = tile_grid(G.nx, G.ny, G.nz, KernelTile<T>::TX, KernelTile<T>::TY, tile_tz(D));
     const TileGrid tgq = tile_grid(G.nx, G.ny, G.nz, KernelTile<T>::TX, KernelTile<T>::TY, tile_tzq(D));
     const int tb = KernelTile<T>::NB;
+    const bool pairs = sc == SCHED_SITES && small_lattice(G);
+    const int nbr = StepBrick::blocks(G), lbr = (nbr + 7) / 8 * 8;
     for (int n = 0; n < nsteps && e == hipSuccess; ++n) {
         T *Q = static_cast<T *>(D.Q[D.qcur]);
         T *Qs = static_cast<T *>(D.Q[D.qcur ^ 1]);  // predictor stage, or Q^{n+1} of the tiled update
@@ -1214,6 +1397,10 @@ hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *time
                 });
                 if (e == hipSuccess)
                     e = mark(K_LBF, [&] { k_lbf<T><<<nb, BLK, 0, D.stream>>>(G, c, gin, Pi, gout, u); });
+            } else if (pairs && !pc) {
+                e = mark(K_QLB, [&] {
+                    k_blb<T, SPLIT, StepBrick><<<lbr, StepBrick::NB, 0, D.stream>>>(G, c, nbr, Q, gin, gout, u);
+                });
             } else {
                 e = mark(K_STRESS, [&] { k_stress<T, SPLIT><<<nb, BLK, 0, D.stream>>>(G, c, Q, Pi, nullptr); });
                 if (pc) {
@@ -1238,6 +1425,13 @@ hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *time
                 e = mark(K_QUPDATE, [&] {
                     k_qupdate<T><<<tgq.launch, tb, 0, D.stream>>>(G, c, tgq, Q, u, Qs, dbg_nan);
                 });
+            D.qcur ^= 1;
+        } else if (pairs && (p.flow || (n ^ 1) < nsteps)) {
+            // without flow only Q alternates: the last of an odd number of steps goes by the
+            // in-place sweeps below, so that a caller's graph of any such call can be replayed
+            if (e == hipSuccess)
+                e = mark(K_QUPDATE,
+                         [&] { k_bq<T, StepBrick><<<lbr, StepBrick::NB, 0, D.stream>>>(G, c, nbr, Q, u, Qs); });
             D.qcur ^= 1;
         } else {
             if (e == hipSuccess)
