@@ -241,8 +241,8 @@ int hlb_set_state(hlb_ctx *ctx, const void *host_buf, size_t nbytes);
  * arithmetic, bit for bit (stress and LB, predictor and corrector).
  * HLB_SCHED_TILED: three sweeps in which 2.5D z-marching LDS tiles hold the
  * stress and the predictor stage (recomputed on a one-site halo ring; tiles
- * of 32 x 8 sites in FP32 and 16 x 12 in FP64), tz planes per tile column
- * (0: 16).  HLB_SCHED_MIXED: the per-site stress and LB sweeps,
+ * of 16 x 12 sites, in FP32 of 32 x 8 for the stress), tz planes per tile
+ * column (0: 16).  HLB_SCHED_MIXED: the per-site stress and LB sweeps,
  * then the tiled predictor-corrector.  HLB_SCHED_FUSED: the tiled stress
  * fused with the LB step (the force never leaves the CU), then the per-site
  * predictor and corrector.  HLB_SCHED_FUSED_TILED: the fused stress and LB

@@ -148,18 +148,73 @@ struct PlaneLoader {
     }
 };
 
+// FP32 planes can go from global memory straight into LDS, 64 points of a
+// component per instruction: no registers in between, and since the points'
+// in-plane offsets are the same for every component, a wave keeps one or two of
+// them and the rest of the address is scalar.  (A kernel that uses it has its
+// LDS in one array: between arrays that the compiler tells apart, it waits for
+// the copies before the next LDS read.)
+__device__ __forceinline__ void copy4_to_lds(const char *gp, float *l)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)gp,
+                                     (__attribute__((address_space(3))) void *)l, 4, 0, 0);
+}
+
+template <class Shape>
+struct PlaneCopy {
+    using P = ChunkPlan<Shape>;
+    unsigned off[P::FULL + P::REM];  // byte offset in the plane of the lane's point of the wave's chunks
+    int w;
+
+    __device__ __forceinline__ void init(const Geom &G, int x0, int y0)
+    {
+        w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+#pragma unroll
+        for (int f = 0; f < P::FULL + P::REM; ++f)
+            off[f] = 4u * unsigned(TileMap<Shape>::staged_at(P::point(P::chunk(f, w), int(threadIdx.x) & 63), x0, y0,
+                                                             G.nx, G.ny));
+    }
+    // Issues the copy of one plane of an NC-component field into a slot of
+    // stride RS; done after copies_done() of every wave and a barrier.
+    template <int NC>
+    __device__ __forceinline__ void issue(const float *__restrict__ src, size_t N, int plane_off, float *slot,
+                                          int turn) const
+    {
+        auto one = [&](int c, int f) __attribute__((always_inline)) {
+            copy4_to_lds(reinterpret_cast<const char *>(src + c * N + plane_off) + off[f],
+                         slot + c * Shape::RS + P::chunk(f, w) * 64);
+        };
+#pragma unroll
+        for (int f = 0; f < P::FULL; ++f)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) one(c, f);
+        if constexpr (P::REM)
+#pragma unroll
+            for (int i = 0; i < (NC + P::NW - 1) / P::NW; ++i) {
+                const int c = P::left_over(i, w, turn);
+                if (c < NC) one(c, P::FULL);
+            }
+    }
+};
+
+__device__ __forceinline__ void copies_done()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), no other counter
+}
+
 // Q, twice its derivatives and its Laplacian at staged coordinate r of plane p:
 // the value and its in-plane neighbours from the staged slot `mid` (two-site
-// halo, RN points per component), the z-neighbours from `lo` (plane p-1,
+// halo, RS values from one component to the next), the z-neighbours from `lo` (plane p-1,
 // registers of the thread owning the point) and the staged slot `hi`
 // (plane p+1).
-template <class Shape, typename T>
+template <class Shape, int RS, typename T>
 __device__ __forceinline__ void stencil_staged(const T lo[5], const T *mid, const T *hi, int r, T q[5],
                                                T d[3][5], T lap[5])
 {
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
-        const int o = k * Shape::RN + r;
+        const int o = k * RS + r;
         q[k] = mid[o];
         stencil7(q[k], mid[o + 1], mid[o - 1], mid[o + Shape::RX], mid[o - Shape::RX], hi[o], lo[k], d[0][k], d[1][k],
                  d[2][k], lap[k]);
@@ -198,13 +253,13 @@ __device__ __forceinline__ void stencil_eval(const T lo[5], const T *mid, const 
 
 // u and twice its centred gradient, W_ab = 2 d_b u_a, at staged coordinate r of
 // plane p: in-plane from `mid`, z from `lo` (registers, plane p-1) and `hi`.
-template <class Shape, typename T>
+template <class Shape, int RS, typename T>
 __device__ __forceinline__ void velocity_staged(const T lo[3], const T *mid, const T *hi, int r, T uc[3],
                                                 T W[3][3])
 {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const int o = a * Shape::RN + r;
+        const int o = a * RS + r;
         uc[a] = mid[o];
         W[a][0] = mid[o + 1] - mid[o - 1];
         W[a][1] = mid[o + Shape::RX] - mid[o - Shape::RX];
@@ -492,27 +547,34 @@ __global__ __launch_bounds__(KernelTile<T>::NB) __attribute__((amdgpu_waves_per_
 // the tile threads the corrector at plane p-1 from Q*(p-1) in LDS and
 // Q*(p-2), Q*(p) in registers, with u(p-1) and W(p-1) kept from the
 // predictor of plane p-1.  FP32: Q*(p) goes into the other of two LDS
-// buffers and the plane p+2, fetched into registers at the start, into the
-// third staging slot, so a plane takes one barrier.  FP64 (where three slots
-// and two buffers would not leave LDS for two blocks per CU): after a barrier
-// Q*(p) replaces Q*(p-1) in LDS and the plane p+2 replaces plane p, and a
+// buffers and the plane p+2 is copied into the third staging slot meanwhile,
+// so a plane takes one barrier; 127 registers and 40.8 kB, so that four blocks
+// share a CU.  FP64 (where three slots and two buffers would not leave LDS for
+// two blocks per CU): after a barrier Q*(p) replaces Q*(p-1) in LDS and the
+// plane p+2, fetched into registers at the start, replaces plane p, and a
 // second barrier ends the plane.
+// Bound by issue: about 400 vector instructions a point and plane, of which the
+// ring and the two extra planes of a chunk repeat half.  FP32 at 192^3: 222 us
+// with 32 x 8 tiles staged through registers, 157 us now (590 MB of Q and u, 3.8
+// TB/s); at 128^3 65 and 51 us, where k_qpred and k_qcorr take 52.
 template <typename T>
-__global__ __launch_bounds__(KernelTile<T>::NB) void k_qupdate(Geom G, Coef<T> c, TileGrid tg,
+__global__ __launch_bounds__(UpdateTile<T>::NB) void k_qupdate(Geom G, Coef<T> c, TileGrid tg,
                                                        const T *__restrict__ Qin, const T *__restrict__ u,
                                                        T *__restrict__ Qout, bool dbg_nan)
 {
-    using Shape = KernelTile<T>;
+    using Shape = UpdateTile<T>;
     constexpr bool ONE = sizeof(T) == 4;      // one barrier per plane
     constexpr int NQS = ONE ? 3 : 2, NSS = ONE ? 2 : 1;
-    __shared__ T sQ[NQS][5 * Shape::RN];
-    __shared__ T sU[NQS][3 * Shape::RN];
-    __shared__ T sS[NSS][5 * Shape::PN];
+    constexpr int RS = ONE ? Shape::RS : Shape::RN;  // component stride of a staged slot
+    __shared__ T smem[NQS * 8 * RS + NSS * 5 * Shape::PN];
+    T(*sQ)[5 * RS] = reinterpret_cast<T(*)[5 * RS]>(smem);
+    T(*sU)[3 * RS] = reinterpret_cast<T(*)[3 * RS]>(smem + NQS * 5 * RS);
+    T(*sS)[5 * Shape::PN] = reinterpret_cast<T(*)[5 * Shape::PN]>(smem + NQS * 8 * RS);
     const Block B = block_of<Shape>(G, tg);
     if (!B.ok) return;
     if (dbg_nan) {
-        nan_fill(&sQ[0][0], NQS * 5 * Shape::RN);
-        nan_fill(&sU[0][0], NQS * 3 * Shape::RN);
+        nan_fill(&sQ[0][0], NQS * 5 * RS);
+        nan_fill(&sU[0][0], NQS * 3 * RS);
         nan_fill(&sS[0][0], NSS * 5 * Shape::PN);
         __syncthreads();
     }
@@ -525,15 +587,28 @@ __global__ __launch_bounds__(KernelTile<T>::NB) void k_qupdate(Geom G, Coef<T> c
     const int gx = B.x0 + t % Shape::TX, gy = B.y0 + t / Shape::TX;
     const bool mine = tile && gx < G.nx && gy < G.ny;
 
-    PlaneLoader<Shape, 5> LQ;
-    PlaneLoader<Shape, 3> LU;
-    LQ.init(G, B.x0, B.y0);
-    LU.init(G, B.x0, B.y0);
     int sc = 0, sn = 1, sf = NQS - 1;  // slots of planes p, p+1; FP32: the free slot
-    LQ.load(Qin, N, wrapi(B.z0 - 1, G.nz) * sxy, sQ[sc]);
-    LQ.load(Qin, N, wrapi(B.z0, G.nz) * sxy, sQ[sn]);
-    LU.load(u, N, wrapi(B.z0 - 1, G.nz) * sxy, sU[sc]);
-    LU.load(u, N, wrapi(B.z0, G.nz) * sxy, sU[sn]);
+    PlaneLoader<Shape, 5> LQ;  // FP64
+    PlaneLoader<Shape, 3> LU;
+    PlaneCopy<Shape> L;  // FP32
+    auto stage = [&](int z, int slot) __attribute__((always_inline)) {
+        const int o = wrapi(z, G.nz) * sxy;
+        if constexpr (ONE) {
+            L.template issue<5>(Qin, N, o, sQ[slot], 0);
+            L.template issue<3>(u, N, o, sU[slot], 3);
+        } else {
+            LQ.load(Qin, N, o, sQ[slot]);
+            LU.load(u, N, o, sU[slot]);
+        }
+    };
+    if constexpr (ONE) {
+        L.init(G, B.x0, B.y0);
+    } else {
+        LQ.init(G, B.x0, B.y0);
+        LU.init(G, B.x0, B.y0);
+    }
+    stage(B.z0 - 1, sc);
+    stage(B.z0, sn);
     // Plane state of the own point in two register sets: one holds Q, u and,
     // on tile sites, W of plane p-1, the other receives those of plane p.  In
     // FP32 they swap roles from one plane to the next (the loop below is
@@ -548,6 +623,7 @@ __global__ __launch_bounds__(KernelTile<T>::NB) void k_qupdate(Geom G, Coef<T> c
 #pragma unroll
         for (int a = 0; a < 3; ++a) uA[a] = u[size_t(a) * N + o];
     }
+    if (ONE) copies_done();
     __syncthreads();
 
     T qs2[5] = {T(0), T(0), T(0), T(0), T(0)};  // Q* at the own site, plane p-2
@@ -556,7 +632,9 @@ __global__ __launch_bounds__(KernelTile<T>::NB) void k_qupdate(Geom G, Coef<T> c
     auto plane = [&](int p, const T (&qmm)[5], const T (&umm)[3], const T (&Wmm)[3][3], T (&q0)[5], T (&u0)[3],
                      T (&W0)[3][3]) __attribute__((always_inline)) {
         const bool more = p + 2 <= B.z1 + 1;
-        if (more) {
+        if constexpr (ONE) {
+            if (more && !dbg_nan) stage(p + 2, sf);
+        } else if (more) {
             LQ.fetch(Qin, N, wrapi(p + 2, G.nz) * sxy, preQ);
             LU.fetch(u, N, wrapi(p + 2, G.nz) * sxy, preU);
         }
@@ -565,15 +643,15 @@ __global__ __launch_bounds__(KernelTile<T>::NB) void k_qupdate(Geom G, Coef<T> c
         const T *Sprev = sS[ONE ? (~p & 1) : 0];  // holds Q*(p-1)
         if (eval) {
 #pragma unroll
-            for (int k = 0; k < 5; ++k) q0[k] = sQ[sc][k * Shape::RN + rc];
+            for (int k = 0; k < 5; ++k) q0[k] = sQ[sc][k * RS + rc];
 #pragma unroll
-            for (int a = 0; a < 3; ++a) u0[a] = sU[sc][a * Shape::RN + rc];
+            for (int a = 0; a < 3; ++a) u0[a] = sU[sc][a * RS + rc];
         }
         const bool pred = eval && (tile || (p >= B.z0 && p < B.z1));
         if (pred) {
             T q[5], d[3][5], lap[5], uc[3], R[5];
-            stencil_staged<Shape>(qmm, sQ[sc], sQ[sn], rc, q, d, lap);
-            velocity_staged<Shape>(umm, sU[sc], sU[sn], rc, uc, W0);
+            stencil_staged<Shape, RS>(qmm, sQ[sc], sQ[sn], rc, q, d, lap);
+            velocity_staged<Shape, RS>(umm, sU[sc], sU[sn], rc, uc, W0);
             site_rhs<T, 2>(c, q, d, lap, uc, W0, R);
 #pragma unroll
             for (int k = 0; k < 5; ++k) qs0[k] = q[k] + R[k];
@@ -581,33 +659,37 @@ __global__ __launch_bounds__(KernelTile<T>::NB) void k_qupdate(Geom G, Coef<T> c
 #pragma unroll
                 for (int k = 0; k < 5; ++k) Scur[k * Shape::PN + pc] = qs0[k];
         }
+        T out[5];
         if (tile && p - 1 >= B.z0) {
             T q[5], d[3][5], lap[5], R[5];
             stencil_eval<Shape>(qs2, Sprev, qs0, pc, q, d, lap);
             site_rhs<T, 2>(c, q, d, lap, umm, Wmm, R);
-            if (mine) {
-                const size_t o = size_t(p - 1) * sxy + size_t(gy) * G.nx + gx;
 #pragma unroll
-                for (int k = 0; k < 5; ++k) Qout[k * N + o] = T(0.5) * (qmm[k] + q[k] + R[k]);
+            for (int k = 0; k < 5; ++k) {
+                out[k] = T(0.5) * (qmm[k] + q[k] + R[k]);
+                qs2[k] = q[k];
+                if (ONE) asm volatile("" : "+v"(out[k]));  // evaluated here, not after the wait below
             }
-#pragma unroll
-            for (int k = 0; k < 5; ++k) qs2[k] = q[k];
         } else if (tile && p == B.z0) {
             // Q*(z0 - 1) is not corrected but is the z-neighbour of the corrector at z0
 #pragma unroll
             for (int k = 0; k < 5; ++k) qs2[k] = Sprev[k * Shape::PN + pc];
         }
+        if (ONE) copies_done();  // ahead of the stores, which are not waited for
+        if (mine && p - 1 >= B.z0) {
+            const size_t o = size_t(p - 1) * sxy + size_t(gy) * G.nx + gx;
+#pragma unroll
+            for (int k = 0; k < 5; ++k) Qout[k * N + o] = out[k];
+        }
         if constexpr (ONE) {
             if (dbg_nan) {  // the free slots and Q*(p-1) are no longer read
                 __syncthreads();
-                nan_fill(sQ[sf], 5 * Shape::RN);
-                nan_fill(sU[sf], 3 * Shape::RN);
+                nan_fill(sQ[sf], 5 * RS);
+                nan_fill(sU[sf], 3 * RS);
                 nan_fill(const_cast<T *>(Sprev), 5 * Shape::PN);
                 __syncthreads();
-            }
-            if (more) {
-                LQ.store(preQ, sQ[sf]);
-                LU.store(preU, sU[sf]);
+                if (more) stage(p + 2, sf);
+                copies_done();
             }
             __syncthreads();
             const int o = sc;
@@ -617,8 +699,8 @@ __global__ __launch_bounds__(KernelTile<T>::NB) void k_qupdate(Geom G, Coef<T> c
         } else {
             __syncthreads();  // plane p, Q*(p-1) are no longer read
             if (dbg_nan) {
-                nan_fill(sQ[sc], 5 * Shape::RN);
-                nan_fill(sU[sc], 3 * Shape::RN);
+                nan_fill(sQ[sc], 5 * RS);
+                nan_fill(sU[sc], 3 * RS);
                 nan_fill(Scur, 5 * Shape::PN);
                 __syncthreads();
             }
@@ -1328,7 +1410,7 @@ int tz_fill_t(const Device &D, int rounds)
     int dev = 0, cus = 0, bq = 0, bf = 0, bl = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bq, k_qupdate<T>, S::NB, 0) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bq, k_qupdate<T>, UpdateTile<T>::NB, 0) != hipSuccess) return 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bf, k_qforce<T, false>, S::NB, 0) != hipSuccess) return 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bl, k_qlb<T, false>, S::NB, 0) != hipSuccess) return 0;
     const long long slots = (long long)cus * std::max(1, std::min(bq, std::min(bf, bl))) * rounds;
@@ -1377,7 +1459,7 @@ hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *time
     if (!p.flow && nsteps > 0)  // pure relaxation: u == 0 (Sec. 2.1)
         k_fill<T><<<1024, BLK, 0, D.stream>>>(u, 3 * size_t(G.N), T(0));
     const TileGrid tg = tile_grid(G.nx, G.ny, G.nz, KernelTile<T>::TX, KernelTile<T>::TY, tile_tz(D));
-    const TileGrid tgq = tile_grid(G.nx, G.ny, G.nz, KernelTile<T>::TX, KernelTile<T>::TY, tile_tzq(D));
+    const TileGrid tgq = tile_grid(G.nx, G.ny, G.nz, UpdateTile<T>::TX, UpdateTile<T>::TY, tile_tzq(D));
     const int tb = KernelTile<T>::NB;
     const bool pairs = sc == SCHED_SITES && small_lattice(G);
     const int nbr = StepBrick::blocks(G), lbr = (nbr + 7) / 8 * 8;
@@ -1423,7 +1505,7 @@ hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *time
         if (tiled_q) {
             if (e == hipSuccess)
                 e = mark(K_QUPDATE, [&] {
-                    k_qupdate<T><<<tgq.launch, tb, 0, D.stream>>>(G, c, tgq, Q, u, Qs, dbg_nan);
+                    k_qupdate<T><<<tgq.launch, UpdateTile<T>::NB, 0, D.stream>>>(G, c, tgq, Q, u, Qs, dbg_nan);
                 });
             D.qcur ^= 1;
         } else if (pairs && (p.flow || (n ^ 1) < nsteps)) {

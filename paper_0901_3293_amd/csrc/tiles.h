@@ -20,6 +20,7 @@ struct TileShape {
     static constexpr int NT = TX * TY;                  // tile sites
     static constexpr int RX = TX + 4, RY = TY + 4;      // staged input plane (halo 2)
     static constexpr int RN = RX * RY;
+    static constexpr int RS = (RN + 63) / 64 * 64;      // whole copies of 64 points
     static constexpr int PX = TX + 2, PY = TY + 2;      // evaluated plane (halo 1)
     static constexpr int PN = PX * PY;
     static constexpr int NH = PN - NT;                  // halo-ring points
@@ -44,14 +45,24 @@ struct TileShape {
     }
 };
 
-// The tile of the fused Q-side kernels, per precision.  FP32: 32 x 8 sites
-// (340 evaluation points, six waves; three blocks of the stress kernel or two
-// of the Q update share a CU).  FP64: 16 x 12 sites (252 points, four waves):
-// the FP64 kernels hold about 180 and 254 registers, two waves per SIMD, so
-// two four-wave blocks share a CU where a six-wave block would run alone with
-// a quarter of the CU's wave slots empty.
+// The tile of the stress kernels, per precision.  FP32: 32 x 8 sites (340
+// evaluation points, six waves; three blocks of the stress kernel or two of
+// the fused stress and LB share a CU): the LB moves 41 values per site, and
+// rows of 16 sites, 64 bytes, cost it more than the blocks gain (a 192^3 step
+// 600 us where 32 x 8 takes 475).  FP64: 16 x 12 sites (252 points, four
+// waves): the FP64 kernels hold about 180 and 230 registers, two waves per
+// SIMD, so two four-wave blocks share a CU where a six-wave block would run
+// alone with a quarter of the CU's wave slots empty.
 template <typename T>
 using KernelTile = typename std::conditional<sizeof(T) == 8, TileShape<16, 12>, TileShape<32, 8>>::type;
+
+// The tile of the Q update, which is bound by its instructions and not by
+// memory: blocks of four waves, one to each SIMD, of which four share a CU in
+// FP32 (two in FP64).  In FP32 at 192^3: 32 x 8 (six waves, two blocks) 222 us,
+// 32 x 12 172, 16 x 12 166 (157 with the planes copied straight into LDS);
+// 24 x 7, 32 x 5, 20 x 10 and 64 x 6 were slower.
+template <typename T>
+using UpdateTile = TileShape<16, 12>;
 
 __host__ __device__ __forceinline__ int wrapi(int v, int n)
 {
@@ -107,9 +118,30 @@ struct TileMap {
     __host__ __device__ static __forceinline__ void staged(int e, int x0, int y0, int nx, int ny, int &comp, int &off)
     {
         comp = e / S::RN;
-        const int r = e - comp * S::RN;
-        const int ri = r % S::RX, rj = r / S::RX;
-        off = wrapi(x0 - 2 + ri, nx) + nx * wrapi(y0 - 2 + rj, ny);
+        off = staged_at(e - comp * S::RN, x0, y0, nx, ny);
+    }
+    // The in-plane offset of staged point r.
+    __host__ __device__ static __forceinline__ int staged_at(int r, int x0, int y0, int nx, int ny)
+    {
+        return wrapi(x0 - 2 + r % S::RX, nx) + nx * wrapi(y0 - 2 + r / S::RX, ny);
+    }
+};
+
+// Staging in chunks of 64 points of one component (RS of them a component, the
+// last RS - RN repeating the last point): which chunks the NW waves of a block
+// take.  Chunk k < FULL NW of every component belongs to wave k % NW; the one
+// chunk left over, if there is one, to the waves in turn by component.
+template <class S>
+struct ChunkPlan {
+    static constexpr int NW = S::NB / 64, CH = S::RS / 64, FULL = CH / NW, REM = CH % NW;
+    static_assert(REM <= 1, "at most one chunk left over");
+    // The f-th chunk of wave w (f < FULL + REM), and the i-th component of
+    // which it takes the left-over chunk (NC and past it: none).
+    __host__ __device__ static constexpr int chunk(int f, int w) { return f < FULL ? f * NW + w : CH - 1; }
+    __host__ __device__ static constexpr int left_over(int i, int w, int turn) { return (w + turn) % NW + i * NW; }
+    __host__ __device__ static constexpr int point(int chunk, int lane)
+    {
+        return chunk * 64 + lane < S::RN ? chunk * 64 + lane : S::RN - 1;
     }
 };
 
