@@ -148,49 +148,51 @@ struct PlaneLoader {
     }
 };
 
-// FP32 planes can go from global memory straight into LDS, 64 points of a
-// component per instruction: no registers in between, and since the points'
-// in-plane offsets are the same for every component, a wave keeps one or two of
-// them and the rest of the address is scalar.  (A kernel that uses it has its
-// LDS in one array: between arrays that the compiler tells apart, it waits for
-// the copies before the next LDS read.)
-__device__ __forceinline__ void copy4_to_lds(const char *gp, float *l)
+// Planes can go from global memory straight into LDS, 64 dwords of a component
+// per instruction: no registers in between, and since the points' in-plane
+// offsets are the same for every component, a wave keeps two or three of them
+// and the rest of the address is scalar.  (A kernel that uses it has its LDS in
+// one array: between arrays that the compiler tells apart, it waits for the
+// copies before the next LDS read.)
+__device__ __forceinline__ void copy4_to_lds(const char *gp, unsigned *l)
 {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)gp,
                                      (__attribute__((address_space(3))) void *)l, 4, 0, 0);
 }
 
-template <class Shape>
+template <class Shape, typename T>
 struct PlaneCopy {
-    using P = ChunkPlan<Shape>;
-    unsigned off[P::FULL + P::REM];  // byte offset in the plane of the lane's point of the wave's chunks
+    static constexpr int E = sizeof(T) / 4;
+    using P = ChunkPlan<Shape, E>;
+    unsigned off[P::FULL + P::LEFT];  // byte offset in the plane of the lane's dword of the wave's chunks
     int w;
 
     __device__ __forceinline__ void init(const Geom &G, int x0, int y0)
     {
         w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+        const int lane = int(threadIdx.x) & 63;
 #pragma unroll
-        for (int f = 0; f < P::FULL + P::REM; ++f)
-            off[f] = 4u * unsigned(TileMap<Shape>::staged_at(P::point(P::chunk(f, w), int(threadIdx.x) & 63), x0, y0,
-                                                             G.nx, G.ny));
+        for (int f = 0; f < P::FULL + P::LEFT; ++f) {
+            const int r = P::point(P::chunk(f, w), lane);
+            off[f] = unsigned(sizeof(T)) * unsigned(TileMap<Shape>::staged_at(r, x0, y0, G.nx, G.ny)) + lane % E * 4;
+        }
     }
     // Issues the copy of one plane of an NC-component field into a slot of
     // stride RS; done after copies_done() of every wave and a barrier.
     template <int NC>
-    __device__ __forceinline__ void issue(const float *__restrict__ src, size_t N, int plane_off, float *slot,
-                                          int turn) const
+    __device__ __forceinline__ void issue(const T *__restrict__ src, size_t N, int plane_off, T *slot, int turn) const
     {
         auto one = [&](int c, int f) __attribute__((always_inline)) {
             copy4_to_lds(reinterpret_cast<const char *>(src + c * N + plane_off) + off[f],
-                         slot + c * Shape::RS + P::chunk(f, w) * 64);
+                         reinterpret_cast<unsigned *>(slot + c * Shape::RS) + P::chunk(f, w) * 64);
         };
 #pragma unroll
         for (int f = 0; f < P::FULL; ++f)
 #pragma unroll
             for (int c = 0; c < NC; ++c) one(c, f);
-        if constexpr (P::REM)
+        if constexpr (P::LEFT)
 #pragma unroll
-            for (int i = 0; i < (NC + P::NW - 1) / P::NW; ++i) {
+            for (int i = 0; i < (NC + P::STEP - 1) / P::STEP; ++i) {
                 const int c = P::left_over(i, w, turn);
                 if (c < NC) one(c, P::FULL);
             }
@@ -546,26 +548,23 @@ __global__ __launch_bounds__(KernelTile<T>::NB) __attribute__((amdgpu_waves_per_
 // staged plane p+1; ring points only where a tile site needs them); then on
 // the tile threads the corrector at plane p-1 from Q*(p-1) in LDS and
 // Q*(p-2), Q*(p) in registers, with u(p-1) and W(p-1) kept from the
-// predictor of plane p-1.  FP32: Q*(p) goes into the other of two LDS
-// buffers and the plane p+2 is copied into the third staging slot meanwhile,
-// so a plane takes one barrier; 127 registers and 40.8 kB, so that four blocks
-// share a CU.  FP64 (where three slots and two buffers would not leave LDS for
-// two blocks per CU): after a barrier Q*(p) replaces Q*(p-1) in LDS and the
-// plane p+2, fetched into registers at the start, replaces plane p, and a
-// second barrier ends the plane.
+// predictor of plane p-1.  Q*(p) goes into the other of two LDS buffers and the
+// plane p+2 is copied into the third staging slot meanwhile, so a plane takes
+// one barrier.  FP32: 127 registers and 40.8 kB, four blocks a CU; FP64: 170
+// and 81.6 kB, two.
 // Bound by issue: about 400 vector instructions a point and plane, of which the
 // ring and the two extra planes of a chunk repeat half.  FP32 at 192^3: 222 us
 // with 32 x 8 tiles staged through registers, 157 us now (590 MB of Q and u, 3.8
-// TB/s); at 128^3 65 and 51 us, where k_qpred and k_qcorr take 52.
+// TB/s); at 128^3 65 and 51 us, where k_qpred and k_qcorr take 52.  FP64, staged
+// through registers into two slots and one buffer with two barriers a plane:
+// 96^3 55 us and now 44, 128^3 95 and 93, 192^3 297 and 272.
 template <typename T>
 __global__ __launch_bounds__(UpdateTile<T>::NB) void k_qupdate(Geom G, Coef<T> c, TileGrid tg,
                                                        const T *__restrict__ Qin, const T *__restrict__ u,
                                                        T *__restrict__ Qout, bool dbg_nan)
 {
     using Shape = UpdateTile<T>;
-    constexpr bool ONE = sizeof(T) == 4;      // one barrier per plane
-    constexpr int NQS = ONE ? 3 : 2, NSS = ONE ? 2 : 1;
-    constexpr int RS = ONE ? Shape::RS : Shape::RN;  // component stride of a staged slot
+    constexpr int NQS = 3, NSS = 2, RS = Shape::RS;
     __shared__ T smem[NQS * 8 * RS + NSS * 5 * Shape::PN];
     T(*sQ)[5 * RS] = reinterpret_cast<T(*)[5 * RS]>(smem);
     T(*sU)[3 * RS] = reinterpret_cast<T(*)[3 * RS]>(smem + NQS * 5 * RS);
@@ -587,26 +586,14 @@ __global__ __launch_bounds__(UpdateTile<T>::NB) void k_qupdate(Geom G, Coef<T> c
     const int gx = B.x0 + t % Shape::TX, gy = B.y0 + t / Shape::TX;
     const bool mine = tile && gx < G.nx && gy < G.ny;
 
-    int sc = 0, sn = 1, sf = NQS - 1;  // slots of planes p, p+1; FP32: the free slot
-    PlaneLoader<Shape, 5> LQ;  // FP64
-    PlaneLoader<Shape, 3> LU;
-    PlaneCopy<Shape> L;  // FP32
+    int sc = 0, sn = 1, sf = 2;  // slots of planes p, p+1 and the free one
+    PlaneCopy<Shape, T> L;
+    L.init(G, B.x0, B.y0);
     auto stage = [&](int z, int slot) __attribute__((always_inline)) {
         const int o = wrapi(z, G.nz) * sxy;
-        if constexpr (ONE) {
-            L.template issue<5>(Qin, N, o, sQ[slot], 0);
-            L.template issue<3>(u, N, o, sU[slot], 3);
-        } else {
-            LQ.load(Qin, N, o, sQ[slot]);
-            LU.load(u, N, o, sU[slot]);
-        }
+        L.template issue<5>(Qin, N, o, sQ[slot], 0);
+        L.template issue<3>(u, N, o, sU[slot], PlaneCopy<Shape, T>::P::STEP - 1);
     };
-    if constexpr (ONE) {
-        L.init(G, B.x0, B.y0);
-    } else {
-        LQ.init(G, B.x0, B.y0);
-        LU.init(G, B.x0, B.y0);
-    }
     stage(B.z0 - 1, sc);
     stage(B.z0, sn);
     // Plane state of the own point in two register sets: one holds Q, u and,
@@ -623,24 +610,17 @@ __global__ __launch_bounds__(UpdateTile<T>::NB) void k_qupdate(Geom G, Coef<T> c
 #pragma unroll
         for (int a = 0; a < 3; ++a) uA[a] = u[size_t(a) * N + o];
     }
-    if (ONE) copies_done();
+    copies_done();
     __syncthreads();
 
     T qs2[5] = {T(0), T(0), T(0), T(0), T(0)};  // Q* at the own site, plane p-2
-    constexpr int NQ = PlaneLoader<Shape, 5>::NL, NU = PlaneLoader<Shape, 3>::NL;
-    T preQ[NQ], preU[NU];
     auto plane = [&](int p, const T (&qmm)[5], const T (&umm)[3], const T (&Wmm)[3][3], T (&q0)[5], T (&u0)[3],
                      T (&W0)[3][3]) __attribute__((always_inline)) {
         const bool more = p + 2 <= B.z1 + 1;
-        if constexpr (ONE) {
-            if (more && !dbg_nan) stage(p + 2, sf);
-        } else if (more) {
-            LQ.fetch(Qin, N, wrapi(p + 2, G.nz) * sxy, preQ);
-            LU.fetch(u, N, wrapi(p + 2, G.nz) * sxy, preU);
-        }
+        if (more && !dbg_nan) stage(p + 2, sf);
         T qs0[5];
-        T *Scur = sS[ONE ? (p & 1) : 0];         // receives Q*(p)
-        const T *Sprev = sS[ONE ? (~p & 1) : 0];  // holds Q*(p-1)
+        T *Scur = sS[p & 1];         // receives Q*(p)
+        const T *Sprev = sS[~p & 1];  // holds Q*(p-1)
         if (eval) {
 #pragma unroll
             for (int k = 0; k < 5; ++k) q0[k] = sQ[sc][k * RS + rc];
@@ -654,10 +634,10 @@ __global__ __launch_bounds__(UpdateTile<T>::NB) void k_qupdate(Geom G, Coef<T> c
             velocity_staged<Shape, RS>(umm, sU[sc], sU[sn], rc, uc, W0);
             site_rhs<T, 2>(c, q, d, lap, uc, W0, R);
 #pragma unroll
-            for (int k = 0; k < 5; ++k) qs0[k] = q[k] + R[k];
-            if (ONE)
-#pragma unroll
-                for (int k = 0; k < 5; ++k) Scur[k * Shape::PN + pc] = qs0[k];
+            for (int k = 0; k < 5; ++k) {
+                qs0[k] = q[k] + R[k];
+                Scur[k * Shape::PN + pc] = qs0[k];
+            }
         }
         T out[5];
         if (tile && p - 1 >= B.z0) {
@@ -668,54 +648,33 @@ __global__ __launch_bounds__(UpdateTile<T>::NB) void k_qupdate(Geom G, Coef<T> c
             for (int k = 0; k < 5; ++k) {
                 out[k] = T(0.5) * (qmm[k] + q[k] + R[k]);
                 qs2[k] = q[k];
-                if (ONE) asm volatile("" : "+v"(out[k]));  // evaluated here, not after the wait below
+                asm volatile("" : "+v"(out[k]));  // evaluated here, not after the wait below
             }
         } else if (tile && p == B.z0) {
             // Q*(z0 - 1) is not corrected but is the z-neighbour of the corrector at z0
 #pragma unroll
             for (int k = 0; k < 5; ++k) qs2[k] = Sprev[k * Shape::PN + pc];
         }
-        if (ONE) copies_done();  // ahead of the stores, which are not waited for
+        copies_done();  // ahead of the stores, which are not waited for
         if (mine && p - 1 >= B.z0) {
             const size_t o = size_t(p - 1) * sxy + size_t(gy) * G.nx + gx;
 #pragma unroll
             for (int k = 0; k < 5; ++k) Qout[k * N + o] = out[k];
         }
-        if constexpr (ONE) {
-            if (dbg_nan) {  // the free slots and Q*(p-1) are no longer read
-                __syncthreads();
-                nan_fill(sQ[sf], 5 * RS);
-                nan_fill(sU[sf], 3 * RS);
-                nan_fill(const_cast<T *>(Sprev), 5 * Shape::PN);
-                __syncthreads();
-                if (more) stage(p + 2, sf);
-                copies_done();
-            }
+        if (dbg_nan) {  // the free slots and Q*(p-1) are no longer read
             __syncthreads();
-            const int o = sc;
-            sc = sn;
-            sn = sf;
-            sf = o;
-        } else {
-            __syncthreads();  // plane p, Q*(p-1) are no longer read
-            if (dbg_nan) {
-                nan_fill(sQ[sc], 5 * RS);
-                nan_fill(sU[sc], 3 * RS);
-                nan_fill(Scur, 5 * Shape::PN);
-                __syncthreads();
-            }
-            if (pred)
-#pragma unroll
-                for (int k = 0; k < 5; ++k) Scur[k * Shape::PN + pc] = qs0[k];
-            if (more) {
-                LQ.store(preQ, sQ[sc]);
-                LU.store(preU, sU[sc]);
-            }
+            nan_fill(sQ[sf], 5 * RS);
+            nan_fill(sU[sf], 3 * RS);
+            nan_fill(const_cast<T *>(Sprev), 5 * Shape::PN);
             __syncthreads();
-            const int o = sc;
-            sc = sn;
-            sn = o;
+            if (more) stage(p + 2, sf);
+            copies_done();
         }
+        __syncthreads();
+        const int o = sc;
+        sc = sn;
+        sn = sf;
+        sf = o;
     };
     int p = B.z0 - 1;
     if constexpr (sizeof(T) == 4) {

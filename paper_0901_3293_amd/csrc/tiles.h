@@ -127,21 +127,29 @@ struct TileMap {
     }
 };
 
-// Staging in chunks of 64 points of one component (RS of them a component, the
-// last RS - RN repeating the last point): which chunks the NW waves of a block
-// take.  Chunk k < FULL NW of every component belongs to wave k % NW; the one
-// chunk left over, if there is one, to the waves in turn by component.
-template <class S>
+// Staging in chunks of 64 dwords of one component (RS values of E dwords each,
+// the last RS - RN repeating the last point): which chunks the NW waves of a
+// block take.  Chunk k < FULL NW of every component belongs to wave k % NW; of
+// the REM chunks left over a wave takes one, for every NW/REM-th component.
+template <class S, int E = 1>
 struct ChunkPlan {
-    static constexpr int NW = S::NB / 64, CH = S::RS / 64, FULL = CH / NW, REM = CH % NW;
-    static_assert(REM <= 1, "at most one chunk left over");
-    // The f-th chunk of wave w (f < FULL + REM), and the i-th component of
+    static constexpr int NW = S::NB / 64, CH = S::RS * E / 64, FULL = CH / NW, REM = CH % NW;
+    static constexpr int LEFT = REM > 0, STEP = REM > 0 ? NW / REM : NW;
+    static_assert(REM == 0 || NW % REM == 0, "as many waves to each left-over chunk");
+    // The f-th chunk of wave w (f < FULL + LEFT), and the i-th component of
     // which it takes the left-over chunk (NC and past it: none).
-    __host__ __device__ static constexpr int chunk(int f, int w) { return f < FULL ? f * NW + w : CH - 1; }
-    __host__ __device__ static constexpr int left_over(int i, int w, int turn) { return (w + turn) % NW + i * NW; }
+    __host__ __device__ static constexpr int chunk(int f, int w)
+    {
+        return f < FULL ? f * NW + w : FULL * NW + (REM ? w % REM : 0);
+    }
+    __host__ __device__ static constexpr int left_over(int i, int w, int turn)
+    {
+        return ((REM ? w / REM : w) + turn) % STEP + i * STEP;
+    }
+    // The point whose dword (chunk * 64 + lane) % E a lane copies.
     __host__ __device__ static constexpr int point(int chunk, int lane)
     {
-        return chunk * 64 + lane < S::RN ? chunk * 64 + lane : S::RN - 1;
+        return (chunk * 64 + lane) / E < S::RN ? (chunk * 64 + lane) / E : S::RN - 1;
     }
 };
 

@@ -1,5 +1,5 @@
 """Chunked staging of the LDS tiles (ChunkPlan in tiles.h), on the host: every
-value of a staged plane is copied exactly once, from its own lattice site."""
+dword of a staged plane is copied exactly once, from its own lattice site."""
 import os
 import subprocess
 
@@ -17,4 +17,4 @@ def test_every_point_is_copied_once(tmp_path, turn):
     subprocess.check_call([HIPCC, "-O1", "-std=c++17", os.path.join(HERE, "hostcheck", "tile_chunks.cpp"), "-o", exe],
                           stderr=subprocess.DEVNULL)
     out = subprocess.run([exe, str(turn)], capture_output=True, text=True, check=True).stdout
-    assert out.split("\n")[:-1] == ["0 0"] * 4
+    assert out.split("\n")[:-1] == ["0 0"] * 6
