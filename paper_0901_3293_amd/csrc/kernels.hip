@@ -702,31 +702,32 @@ __global__ __launch_bounds__(UpdateTile<T>::NB) void k_qupdate(Geom G, Coef<T> c
 
 // ---------------------------------------------------------------- per-site kernels
 
-__device__ __forceinline__ int site_index() { return logical_block() * BLK + int(threadIdx.x); }
+template <int B = BLK>
+__device__ __forceinline__ int site_index() { return logical_block() * B + int(threadIdx.x); }
 
 // SPLIT: the 12 planes of the split coupling instead of the 9 of Pi.
 // Occupancy floors of the per-site Q-side kernels in FP64 (blocks of 256 per
 // CU): registers bounded to 128 (stress, corrector) and 96 (predictor)
 // without spills, 4 and 5 waves per SIMD.  FP32 is left to the compiler
 // (~60 registers, 8 waves).
-template <typename T, bool SPLIT>
-__global__ __launch_bounds__(BLK, sizeof(T) == 8 ? 4 : 1) void k_stress(Geom G, Coef<T> c, const T *__restrict__ Q,
+template <typename T, bool SPLIT, int B = BLK>
+__global__ __launch_bounds__(B, sizeof(T) == 8 ? 4 : 1) void k_stress(Geom G, Coef<T> c, const T *__restrict__ Q,
                                                 T *__restrict__ Pi, double *__restrict__ fpart)
 {
-    const int s = site_index();
+    const int s = site_index<B>();
     double fsum = 0.0;
     if (s < G.N) fsum = double(SPLIT ? split_at(G, c, Q, Pi, s) : stress_at(G, c, Q, Pi, s));
     if (fpart) {
         double v[1] = {fsum};
-        block_sum<1, BLK>(v, fpart + logical_block());
+        block_sum<1, B>(v, fpart + logical_block());
     }
 }
 
-template <typename T, bool SPLIT>
-__global__ __launch_bounds__(BLK) void k_lb(Geom G, Coef<T> c, const T *__restrict__ gin,
+template <typename T, bool SPLIT, int B>
+__global__ __launch_bounds__(B) void k_lb(Geom G, Coef<T> c, const T *__restrict__ gin,
                                             const T *__restrict__ Pi, T *__restrict__ gout, T *__restrict__ u)
 {
-    const int s = site_index();
+    const int s = site_index<B>();
     if (s >= G.N) return;
     if (SPLIT)
         lb_split_at<T, true>(G, c, gin, Pi, gout, u, s);
@@ -734,19 +735,19 @@ __global__ __launch_bounds__(BLK) void k_lb(Geom G, Coef<T> c, const T *__restri
         lb_at<T, true>(G, c, gin, Pi, gout, u, s);
 }
 
-template <typename T>
-__global__ __launch_bounds__(BLK, sizeof(T) == 8 ? 5 : 1) void k_qpred(Geom G, Coef<T> c, const T *__restrict__ Q,
+template <typename T, int B>
+__global__ __launch_bounds__(B, sizeof(T) == 8 ? 5 : 1) void k_qpred(Geom G, Coef<T> c, const T *__restrict__ Q,
                                                const T *__restrict__ u, T *__restrict__ Qs)
 {
-    const int s = site_index();
+    const int s = site_index<B>();
     if (s < G.N) pred_at(G, c, Q, u, Qs, s);
 }
 
-template <typename T>
-__global__ __launch_bounds__(BLK, sizeof(T) == 8 ? 4 : 1) void k_qcorr(Geom G, Coef<T> c, T *__restrict__ Q, const T *__restrict__ Qs,
+template <typename T, int B>
+__global__ __launch_bounds__(B, sizeof(T) == 8 ? 4 : 1) void k_qcorr(Geom G, Coef<T> c, T *__restrict__ Q, const T *__restrict__ Qs,
                                                const T *__restrict__ u)
 {
-    const int s = site_index();
+    const int s = site_index<B>();
     if (s < G.N) corr_at(G, c, Q, Qs, u, s);
 }
 
@@ -912,20 +913,20 @@ __global__ __launch_bounds__(B::NB) void k_bq(Geom G, Coef<T> c, int nblocks, co
 }
 
 // D3Q15 predictor-corrector LB, the two passes (see pc1_at, pc2_at).
-template <typename T, bool SPLIT>
-__global__ __launch_bounds__(BLK) void k_pc1(Geom G, Coef<T> c, const T *__restrict__ g, const T *__restrict__ Pi,
+template <typename T, bool SPLIT, int B>
+__global__ __launch_bounds__(B) void k_pc1(Geom G, Coef<T> c, const T *__restrict__ g, const T *__restrict__ Pi,
                                              T *__restrict__ P, T *__restrict__ u, T *__restrict__ bsave)
 {
-    const int s = site_index();
+    const int s = site_index<B>();
     if (s < G.N) pc1_at<T, SPLIT, true>(G, c, g, Pi, P, u, bsave, s);
 }
 
-template <typename T, bool SPLIT>
-__global__ __launch_bounds__(BLK) void k_pc2(Geom G, Coef<T> c, const T *__restrict__ g, const T *__restrict__ P,
+template <typename T, bool SPLIT, int B>
+__global__ __launch_bounds__(B) void k_pc2(Geom G, Coef<T> c, const T *__restrict__ g, const T *__restrict__ P,
                                              const T *__restrict__ Pi, const T *__restrict__ bsave,
                                              T *__restrict__ gout)
 {
-    const int s = site_index();
+    const int s = site_index<B>();
     if (s < G.N) pc2_at<T, SPLIT, true>(G, c, g, P, Pi, bsave, gout, s);
 }
 
@@ -1331,7 +1332,7 @@ __global__ __launch_bounds__(BLK) void k_fill(T *__restrict__ p, size_t n, T v)
 
 // ---------------------------------------------------------------- launchers
 
-inline int site_blocks(int N) { return ((N + BLK - 1) / BLK + 7) / 8 * 8; }
+inline int site_blocks(int N, int block = BLK) { return ((N + block - 1) / block + 7) / 8 * 8; }
 
 // Records an event pair around each launch when a timer is attached.
 struct Marks {
@@ -1389,14 +1390,38 @@ int tz_fill_t(const Device &D, int rounds)
 // but leave CUs idle on the lattices in question.
 typedef Brick<16, 4, 2> StepBrick;
 
-bool small_lattice(const Geom &G)
+int device_cus()
 {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return false;
-    return StepBrick::blocks(G) <= cus;
+        return 0;
+    return cus;
 }
+
+bool small_lattice(const Geom &G, int cus) { return StepBrick::blocks(G) <= cus; }
+
+// Threads per block of the per-site sweeps of a step.  With few blocks of 256
+// some CUs get one more than others and the launch waits for them, so where
+// that is more than a tenth, up to five blocks a CU, a block is one wave.  A
+// step in us with 256 and 64: 44^3 (333 blocks on 256 CUs) 19.4 and 18.7 in
+// FP32, 28.5 and 25.8 in FP64; 60 x 44 x 53 (547) 23.2 and 22.0, 38.3 and 33.2;
+// 70 x 66 x 61 (1101) 31.8 and 31.5, 59.5 and 57.5.  Even, 64^3 (1024): 26.8 and
+// 27.5, 51.0 and 50.0.  More blocks: 96 x 80 x 70 (2100) 45.5 and 47.4, 95.8 and
+// 95.7; 128^3 (8192) 139 and 150, 336 and 349.
+template <class F>
+void with_block(int N, int cus, F &&f)
+{
+    const int nb = site_blocks(N), rounds = (nb + cus - 1) / std::max(1, cus);
+    if (rounds <= 5 && 10 * (rounds * cus - nb) > nb) f(std::integral_constant<int, 64>{});
+    else f(std::integral_constant<int, BLK>{});
+}
+// Launches a per-site kernel template over the sites of the lattice, B threads per block.
+#define SWEEP(KERNEL, ...)                                                        \
+    with_block(G.N, cus, [&](auto block) {                                        \
+        constexpr int B = decltype(block)::value;                                 \
+        KERNEL<<<site_blocks(G.N, B), B, 0, D.stream>>>(__VA_ARGS__);             \
+    })
 
 template <typename T, bool SPLIT>
 hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *timer)
@@ -1411,7 +1436,7 @@ hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *time
     const bool dbg_nan = (D.debug & DEBUG_NAN_LDS) != 0;
     const Geom G = D.G;
     const Coef<T> c = make_coef<T>(p);
-    const int nb = site_blocks(G.N);
+    const int cus = device_cus();
     T *u = static_cast<T *>(D.u), *Pi = static_cast<T *>(D.Pi);
     Marks mark{timer, D.stream};
     hipError_t e = hipSuccess;
@@ -1420,7 +1445,7 @@ hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *time
     const TileGrid tg = tile_grid(G.nx, G.ny, G.nz, KernelTile<T>::TX, KernelTile<T>::TY, tile_tz(D));
     const TileGrid tgq = tile_grid(G.nx, G.ny, G.nz, UpdateTile<T>::TX, UpdateTile<T>::TY, tile_tzq(D));
     const int tb = KernelTile<T>::NB;
-    const bool pairs = sc == SCHED_SITES && small_lattice(G);
+    const bool pairs = sc == SCHED_SITES && small_lattice(G, cus);
     const int nbr = StepBrick::blocks(G), lbr = (nbr + 7) / 8 * 8;
     for (int n = 0; n < nsteps && e == hipSuccess; ++n) {
         T *Q = static_cast<T *>(D.Q[D.qcur]);
@@ -1437,26 +1462,26 @@ hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *time
                     k_qforce<T, false><<<tg.launch, tb, 0, D.stream>>>(G, c, tg, Q, Pi, nullptr, dbg_nan);
                 });
                 if (e == hipSuccess)
-                    e = mark(K_LBF, [&] { k_lbf<T><<<nb, BLK, 0, D.stream>>>(G, c, gin, Pi, gout, u); });
+                    e = mark(K_LBF, [&] { k_lbf<T><<<site_blocks(G.N), BLK, 0, D.stream>>>(G, c, gin, Pi, gout, u); });
             } else if (pairs && !pc) {
                 e = mark(K_QLB, [&] {
                     k_blb<T, SPLIT, StepBrick><<<lbr, StepBrick::NB, 0, D.stream>>>(G, c, nbr, Q, gin, gout, u);
                 });
             } else {
-                e = mark(K_STRESS, [&] { k_stress<T, SPLIT><<<nb, BLK, 0, D.stream>>>(G, c, Q, Pi, nullptr); });
+                e = mark(K_STRESS, [&] { SWEEP((k_stress<T, SPLIT, B>), G, c, Q, Pi, nullptr); });
                 if (pc) {
                     T *P = static_cast<T *>(D.aux);
                     T *bsave = gout + 15 * size_t(G.N);  // planes 15..17 of the target buffer
                     if (e == hipSuccess)
                         e = mark(K_PC1, [&] {
-                            k_pc1<T, SPLIT><<<nb, BLK, 0, D.stream>>>(G, c, gin, Pi, P, u, bsave);
+                            SWEEP((k_pc1<T, SPLIT, B>), G, c, gin, Pi, P, u, bsave);
                         });
                     if (e == hipSuccess)
                         e = mark(K_PC2, [&] {
-                            k_pc2<T, SPLIT><<<nb, BLK, 0, D.stream>>>(G, c, gin, P, Pi, bsave, gout);
+                            SWEEP((k_pc2<T, SPLIT, B>), G, c, gin, P, Pi, bsave, gout);
                         });
                 } else if (e == hipSuccess) {
-                    e = mark(K_LB, [&] { k_lb<T, SPLIT><<<nb, BLK, 0, D.stream>>>(G, c, gin, Pi, gout, u); });
+                    e = mark(K_LB, [&] { SWEEP((k_lb<T, SPLIT, B>), G, c, gin, Pi, gout, u); });
                 }
             }
             D.gcur ^= 1;
@@ -1476,9 +1501,9 @@ hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *time
             D.qcur ^= 1;
         } else {
             if (e == hipSuccess)
-                e = mark(K_QPRED, [&] { k_qpred<T><<<nb, BLK, 0, D.stream>>>(G, c, Q, u, Qs); });
+                e = mark(K_QPRED, [&] { SWEEP((k_qpred<T, B>), G, c, Q, u, Qs); });
             if (e == hipSuccess)
-                e = mark(K_QCORR, [&] { k_qcorr<T><<<nb, BLK, 0, D.stream>>>(G, c, Q, Qs, u); });
+                e = mark(K_QCORR, [&] { SWEEP((k_qcorr<T, B>), G, c, Q, Qs, u); });
         }
     }
     if (e != hipSuccess) return e;

@@ -2,7 +2,8 @@
 evaluate a site with the same operations in the same order, so a step by either
 schedule gives the same values bit for bit.  Lattices smaller than a tile, whole
 tiles, one site past them and one short, and z-chunks of one plane, of a
-remainder and of the whole depth."""
+remainder and of the whole depth; also lattices on either side of the size up to
+which the per-site sweeps go by blocks of one wave."""
 import numpy as np
 import pytest
 
@@ -11,7 +12,8 @@ from tests.hlbtest import say
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(4, 4, 4), (16, 12, 5), (17, 13, 9), (31, 11, 8), (32, 24, 7), (33, 25, 6), (65, 37, 12)]
+SHAPES = [(4, 4, 4), (16, 12, 5), (17, 13, 9), (31, 11, 8), (32, 24, 7), (33, 25, 6), (65, 37, 12),
+          (47, 46, 45), (72, 70, 66)]  # per-site sweeps by blocks of one wave, and of four
 
 
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
