@@ -751,6 +751,29 @@ __global__ __launch_bounds__(B, sizeof(T) == 8 ? 4 : 1) void k_qcorr(Geom G, Coe
     if (s < G.N) corr_at(G, c, Q, Qs, u, s);
 }
 
+// The same, two sites per thread (nx even), in FP64: a wave's load of one value
+// per lane is 512 bytes there, and the 61 to 66 of them that a site takes in k_qpred
+// and k_qcorr fill a CU's path to its cache; two sites a thread take 56 to 61 of
+// twice the width and no shifted rows.  254 registers, two waves per SIMD.  Both
+// together at 96^3 57 -> 45 us, 128^3 123 -> 100 (520 MB if nothing is cached: the
+// memory's rate), 64^3 21 -> 16.  In FP32 they are slower (128^3 52 -> 58): one
+// value per lane is at the memory's rate already, with four times the waves.
+template <typename T, int B>
+__global__ __launch_bounds__(B) void k_qpred2(Geom G, Coef<T> c, const T *__restrict__ Q, const T *__restrict__ u,
+                                              T *__restrict__ Qs)
+{
+    const int p = site_index<B>();
+    pred_pair(G, c, Q, u, Qs, 2 * min(p, G.N / 2 - 1), p < G.N / 2);
+}
+
+template <typename T, int B>
+__global__ __launch_bounds__(B) void k_qcorr2(Geom G, Coef<T> c, T *__restrict__ Q, const T *__restrict__ Qs,
+                                              const T *__restrict__ u)
+{
+    const int p = site_index<B>();
+    corr_pair(G, c, Q, Qs, u, 2 * min(p, G.N / 2 - 1), p < G.N / 2);
+}
+
 // ---------------------------------------------------------------- small lattices
 // The per-site sweeps in pairs, over bricks of sites: k_blb is k_stress and
 // k_lb, k_bq is k_qpred and k_qcorr.  A block evaluates the first of the two on
@@ -1417,11 +1440,12 @@ void with_block(int N, int cus, F &&f)
     else f(std::integral_constant<int, BLK>{});
 }
 // Launches a per-site kernel template over the sites of the lattice, B threads per block.
-#define SWEEP(KERNEL, ...)                                                        \
-    with_block(G.N, cus, [&](auto block) {                                        \
+#define SWEEP_OF(N, KERNEL, ...)                                                  \
+    with_block(N, cus, [&](auto block) {                                          \
         constexpr int B = decltype(block)::value;                                 \
-        KERNEL<<<site_blocks(G.N, B), B, 0, D.stream>>>(__VA_ARGS__);             \
+        KERNEL<<<site_blocks(N, B), B, 0, D.stream>>>(__VA_ARGS__);               \
     })
+#define SWEEP(KERNEL, ...) SWEEP_OF(G.N, KERNEL, __VA_ARGS__)
 
 template <typename T, bool SPLIT>
 hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *timer)
@@ -1499,6 +1523,13 @@ hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *time
                 e = mark(K_QUPDATE,
                          [&] { k_bq<T, StepBrick><<<lbr, StepBrick::NB, 0, D.stream>>>(G, c, nbr, Q, u, Qs); });
             D.qcur ^= 1;
+        } else if (sizeof(T) == 8 && G.nx % 2 == 0) {
+            if constexpr (sizeof(T) == 8) {
+                if (e == hipSuccess)
+                    e = mark(K_QPRED, [&] { SWEEP_OF(G.N / 2, (k_qpred2<T, B>), G, c, Q, u, Qs); });
+                if (e == hipSuccess)
+                    e = mark(K_QCORR, [&] { SWEEP_OF(G.N / 2, (k_qcorr2<T, B>), G, c, Q, Qs, u); });
+            }
         } else {
             if (e == hipSuccess)
                 e = mark(K_QPRED, [&] { SWEEP((k_qpred<T, B>), G, c, Q, u, Qs); });

@@ -375,6 +375,172 @@ __device__ __forceinline__ void corr_at(const Geom &G, const Coef<T> &c, T *__re
     for (int k = 0; k < 5; ++k) *at(plane(Q, k, N), O.s) = T(0.5) * (qn[k] + q[k] + R[k]);
 }
 
+// ---- two sites per thread: (x, x + 1), x even, nx even.  The rows are read two
+// values at a time; the neighbours in x are the thread's own other site and the
+// sites of the lanes below and above, or a load at the ends of a row or a wave.
+// All lanes of a wave take part (one past the last pair repeats it).
+template <typename T>
+using Two = T __attribute__((ext_vector_type(2)));
+
+template <typename T>
+struct PairAt {
+    Off<T> O;   // the first site; nb[0], nb[1]: the sites right and left of the pair
+    bool l, r;  // the left (right) neighbour is not the last (first) site of the lane below (above)
+};
+
+template <typename T>
+__device__ __forceinline__ PairAt<T> pair_at(const Geom &G, int s)
+{
+    Nbr S = nbr_of(G, s);
+    S.nb[0] = S.x + 2 == G.nx ? s + 2 - G.nx : s + 2;
+    PairAt<T> A;
+    A.O = offsets<T>(S);
+    const int lane = int(threadIdx.x) & 63;
+    A.l = lane == 0 || S.x == 0;
+    A.r = lane == 63 || S.x + 2 == G.nx;
+    return A;
+}
+
+template <int CTRL, typename T>
+__device__ __forceinline__ T lane_shift(T v)
+{
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
+    } else {
+        Two<int> w = __builtin_bit_cast(Two<int>, v);
+        w.x = __builtin_amdgcn_update_dpp(0, w.x, CTRL, 0xf, 0xf, false);
+        w.y = __builtin_amdgcn_update_dpp(0, w.y, CTRL, 0xf, 0xf, false);
+        return __builtin_bit_cast(T, w);
+    }
+}
+template <typename T>
+__device__ __forceinline__ T from_below(T v) { return lane_shift<0x138>(v); }  // lane i: lane i - 1's
+template <typename T>
+__device__ __forceinline__ T from_above(T v) { return lane_shift<0x130>(v); }  // lane i: lane i + 1's
+
+template <typename T>
+__device__ __forceinline__ Two<T> two(const T *P, unsigned b)
+{
+    return *reinterpret_cast<const Two<T> *>(at(P, b));
+}
+
+// The rows of NC components at a pair and its neighbours.
+template <typename T, int NC>
+struct PairRows {
+    Two<T> c[NC], yp[NC], ym[NC], zp[NC], zm[NC];
+    T l[NC], r[NC];
+
+    __device__ __forceinline__ void load(const T *__restrict__ F, int N, const PairAt<T> &A)
+    {
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            const T *P = plane(F, k, N);
+            c[k] = two(P, A.O.s);
+            yp[k] = two(P, A.O.nb[2]);
+            ym[k] = two(P, A.O.nb[3]);
+            zp[k] = two(P, A.O.nb[4]);
+            zm[k] = two(P, A.O.nb[5]);
+        }
+        if (A.l)
+#pragma unroll
+            for (int k = 0; k < NC; ++k) l[k] = *at(plane(F, k, N), A.O.nb[1]);
+        if (A.r)
+#pragma unroll
+            for (int k = 0; k < NC; ++k) r[k] = *at(plane(F, k, N), A.O.nb[0]);
+    }
+    __device__ __forceinline__ void edges(const PairAt<T> &A)
+    {
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            const T a = from_below(c[k].y), b = from_above(c[k].x);
+            l[k] = A.l ? l[k] : a;
+            r[k] = A.r ? r[k] : b;
+        }
+    }
+};
+
+// gather_q and gather_u at site h (0, 1) of the pair.
+template <typename T>
+__device__ __forceinline__ void pair_q(const PairRows<T, 5> &F, int h, T q[5], T d[3][5], T lap[5])
+{
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        q[k] = F.c[k][h];
+        stencil7(q[k], h ? F.r[k] : F.c[k].y, h ? F.c[k].x : F.l[k], F.yp[k][h], F.ym[k][h], F.zp[k][h], F.zm[k][h],
+                 d[0][k], d[1][k], d[2][k], lap[k]);
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void pair_u(const PairRows<T, 3> &F, int h, T uc[3], T W[3][3])
+{
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        uc[a] = F.c[a][h];
+        W[a][0] = (h ? F.r[a] : F.c[a].y) - (h ? F.c[a].x : F.l[a]);
+        W[a][1] = F.yp[a][h] - F.ym[a][h];
+        W[a][2] = F.zp[a][h] - F.zm[a][h];
+    }
+}
+
+// pred_at and corr_at at both sites of a pair (the pair's first site s; mine:
+// write them).
+template <typename T>
+__device__ __forceinline__ void pred_pair(const Geom &G, const Coef<T> &c, const T *__restrict__ Q,
+                                          const T *__restrict__ u, T *__restrict__ Qs, int s, bool mine)
+{
+    const int N = G.N;
+    const PairAt<T> A = pair_at<T>(G, s);
+    PairRows<T, 5> FQ;
+    PairRows<T, 3> FU;
+    FQ.load(Q, N, A);
+    FU.load(u, N, A);
+    FQ.edges(A);
+    FU.edges(A);
+    Two<T> out[5];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        T q[5], d[3][5], lap[5], uc[3], W[3][3], R[5];
+        pair_q(FQ, h, q, d, lap);
+        pair_u(FU, h, uc, W);
+        site_rhs<T, 2>(c, q, d, lap, uc, W, R);
+#pragma unroll
+        for (int k = 0; k < 5; ++k) out[k][h] = q[k] + R[k];
+    }
+    if (mine)
+#pragma unroll
+        for (int k = 0; k < 5; ++k) *reinterpret_cast<Two<T> *>(at(plane(Qs, k, N), A.O.s)) = out[k];
+}
+
+template <typename T>
+__device__ __forceinline__ void corr_pair(const Geom &G, const Coef<T> &c, T *__restrict__ Q,
+                                          const T *__restrict__ Qs, const T *__restrict__ u, int s, bool mine)
+{
+    const int N = G.N;
+    const PairAt<T> A = pair_at<T>(G, s);
+    PairRows<T, 5> FQ;
+    PairRows<T, 3> FU;
+    Two<T> qn[5], out[5];
+    FQ.load(Qs, N, A);
+    FU.load(u, N, A);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) qn[k] = two(static_cast<const T *>(plane(Q, k, N)), A.O.s);
+    FQ.edges(A);
+    FU.edges(A);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        T q[5], d[3][5], lap[5], uc[3], W[3][3], R[5];
+        pair_q(FQ, h, q, d, lap);
+        pair_u(FU, h, uc, W);
+        site_rhs<T, 2>(c, q, d, lap, uc, W, R);
+#pragma unroll
+        for (int k = 0; k < 5; ++k) out[k][h] = T(0.5) * (qn[k][h] + q[k] + R[k]);
+    }
+    if (mine)
+#pragma unroll
+        for (int k = 0; k < 5; ++k) *reinterpret_cast<Two<T> *>(at(plane(Q, k, N), A.O.s)) = out[k];
+}
+
 // Free-energy density at one site (Eq. (1) with the divergence term).
 template <typename T>
 __device__ __forceinline__ T fdens_at(const Geom &G, const Coef<T> &c, const T *__restrict__ Q, int s)

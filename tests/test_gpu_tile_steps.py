@@ -3,7 +3,8 @@ evaluate a site with the same operations in the same order, so a step by either
 schedule gives the same values bit for bit.  Lattices smaller than a tile, whole
 tiles, one site past them and one short, and z-chunks of one plane, of a
 remainder and of the whole depth; also lattices on either side of the size up to
-which the per-site sweeps go by blocks of one wave."""
+which the per-site sweeps go by blocks of one wave, and rows of one, several and
+many pairs of sites (even lengths, FP64)."""
 import numpy as np
 import pytest
 
@@ -12,7 +13,7 @@ from tests.hlbtest import say
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(4, 4, 4), (16, 12, 5), (17, 13, 9), (31, 11, 8), (32, 24, 7), (33, 25, 6), (65, 37, 12),
+SHAPES = [(4, 4, 4), (6, 5, 4), (130, 9, 6), (16, 12, 5), (17, 13, 9), (31, 11, 8), (32, 24, 7), (33, 25, 6), (65, 37, 12),
           (47, 46, 45), (72, 70, 66)]  # per-site sweeps by blocks of one wave, and of four
 
 
@@ -26,7 +27,7 @@ def test_tiled_steps_equal_the_per_site_steps(prec, coupling):
     for shape in SHAPES:
         Q = 0.4 * I.smooth_field(shape, 0.5, seed=3) + I.noise(shape, 1e-2, 4)
         out = []
-        for sched, tz in [("sites", 0), ("fused-tiled", 1), ("fused-tiled", 3), ("fused-tiled", shape[2])]:
+        for sched, tz in [("sites", 0), ("fused-tiled", 1), ("fused-tiled", 3), ("fused", 3), ("fused-tiled", shape[2])]:
             say("case: tile step", shape, prec, coupling, sched, tz)
             s = hlb.Solver(shape, prec, coupling=p.coupling)
             s.set_schedule(sched, tz)
