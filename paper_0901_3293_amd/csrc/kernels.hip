@@ -224,13 +224,13 @@ __device__ __forceinline__ void stencil_staged(const T lo[5], const T *mid, cons
 }
 
 // Same for the three-slot form (all of planes p-1, p, p+1 staged).
-template <class Shape, typename T>
+template <class Shape, int RS, typename T>
 __device__ __forceinline__ void stencil_ring(const T *lo, const T *mid, const T *hi, int r, T q[5],
                                              T d[3][5], T lap[5])
 {
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
-        const int o = k * Shape::RN + r;
+        const int o = k * RS + r;
         q[k] = mid[o];
         stencil7(q[k], mid[o + 1], mid[o - 1], mid[o + Shape::RX], mid[o - Shape::RX], hi[o], lo[o], d[0][k], d[1][k],
                  d[2][k], lap[k]);
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(KernelTile<T>::NB) __attribute__((amdgpu_waves_per_
         // ring points: only the planes whose in-plane divergence is output
         if (eval && (tile || (p >= B.z0 && p < B.z1))) {
             T q[5], d[3][5], lap[5], P[3][3], fd, H[5];
-            stencil_ring<Shape>(sQ[s1], sQ[s2], sQ[s3], rc, q, d, lap);
+            stencil_ring<Shape, Shape::RN>(sQ[s1], sQ[s2], sQ[s3], rc, q, d, lap);
             site_stress<T, 2>(c, q, d, lap, P, fd, H);
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
@@ -409,20 +409,26 @@ __global__ __launch_bounds__(KernelTile<T>::NB) __attribute__((amdgpu_waves_per_
 // force b_a = d_b tau_ab + h_a, and a tile thread keeps sigma^xi and h of its
 // site of plane p-1 in registers for the collision with sigma^xi in the
 // equilibrium.
-// FP32: at most 128 registers (four waves per SIMD, two blocks per CU); FP64:
-// about 230 (two waves per SIMD, two four-wave blocks per CU).
-template <typename T, bool SPLIT>
-__global__ __launch_bounds__(KernelTile<T>::NB) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 1 : 4))) void k_qlb(Geom G, Coef<T> c, TileGrid tg,
-                                                      const T *__restrict__ Q, const T *__restrict__ gin,
+// FP32: 110 registers, four waves per SIMD, two blocks per CU; FP64: about 200,
+// two waves per SIMD and two four-wave blocks.  The planes of Q go straight into
+// LDS (staged through registers: 127 and 231).
+// Bound by memory, 46 values per site: rows as long as a lattice row's share
+// of whole lines matter more than the ring.  Q update included, FP32 192^3: 32 x 8
+// tiles 448 us, 32 x 12 426, 64 x 5 416; 128^3 147 (157 through registers) and 146;
+// 96^3, where 64 does not divide the row, 80 (86) and 83.  FP64 128^3: 16 x 12
+// 277 us, 32 x 4 264.
+template <typename T, bool SPLIT, class Shape>
+__global__ __launch_bounds__(Shape::NB) void k_qlb(Geom G, Coef<T> c, TileGrid tg, const T *__restrict__ Q, const T *__restrict__ gin,
                                                       T *__restrict__ gout, T *__restrict__ u, bool dbg_nan)
 {
-    using Shape = KernelTile<T>;
-    __shared__ T sQ[4][5 * Shape::RN];
-    __shared__ T sP[2][6 * Shape::PN];
+    constexpr int RS = Shape::RS;
+    __shared__ T smem[4 * 5 * RS + 2 * 6 * Shape::PN];
+    T(*sQ)[5 * RS] = reinterpret_cast<T(*)[5 * RS]>(smem);
+    T(*sP)[6 * Shape::PN] = reinterpret_cast<T(*)[6 * Shape::PN]>(smem + 4 * 5 * RS);
     const Block B = block_of<Shape>(G, tg);
     if (!B.ok) return;
     if (dbg_nan) {
-        nan_fill(&sQ[0][0], 4 * 5 * Shape::RN);
+        nan_fill(&sQ[0][0], 4 * 5 * RS);
         nan_fill(&sP[0][0], 2 * 6 * Shape::PN);
         __syncthreads();
     }
@@ -435,22 +441,24 @@ __global__ __launch_bounds__(KernelTile<T>::NB) __attribute__((amdgpu_waves_per_
     const int gx = B.x0 + t % Shape::TX, gy = B.y0 + t / Shape::TX;
     const bool mine = tile && gx < G.nx && gy < G.ny;
 
-    PlaneLoader<Shape, 5> L;
+    PlaneCopy<Shape, T> L;
     L.init(G, B.x0, B.y0);
+    auto stage = [&](int z, int slot) __attribute__((always_inline)) {
+        L.template issue<5>(Q, size_t(N), wrapi(z, G.nz) * sxy, sQ[slot], 0);
+    };
     int s0 = 0, s1 = 1, s2 = 2, s3 = 3;  // s1, s2, s3: planes p-1, p, p+1; s0 free
-    L.load(Q, size_t(N), wrapi(B.z0 - 2, G.nz) * sxy, sQ[s1]);
-    L.load(Q, size_t(N), wrapi(B.z0 - 1, G.nz) * sxy, sQ[s2]);
-    L.load(Q, size_t(N), wrapi(B.z0, G.nz) * sxy, sQ[s3]);
+    stage(B.z0 - 2, s1);
+    stage(B.z0 - 1, s2);
+    stage(B.z0, s3);
+    copies_done();
     __syncthreads();
 
     // z columns of the own point at planes p-1 and p-2: Pi_az, or (SPLIT) tau xz, yz
     T Pz1[3] = {T(0), T(0), T(0)}, Pz2[3] = {T(0), T(0), T(0)};
     T sig1[6], h1[3];  // SPLIT: sigma^xi and h of the own site at plane p-1
-    constexpr int NL = PlaneLoader<Shape, 5>::NL;
-    T pre[NL];
     for (int p = B.z0 - 1; p <= B.z1; ++p) {
         const bool more = p + 2 <= B.z1 + 1;
-        if (more) L.fetch(Q, size_t(N), wrapi(p + 2, G.nz) * sxy, pre);
+        if (more && !dbg_nan) stage(p + 2, s0);
         const bool lb = mine && p - 1 >= B.z0;  // this plane collides site (gx, gy, p-1)
         Off<T> O;
         T g[19];
@@ -466,7 +474,7 @@ __global__ __launch_bounds__(KernelTile<T>::NB) __attribute__((amdgpu_waves_per_
         // ring points: only the planes whose in-plane divergence is used
         if (eval && (tile || (p >= B.z0 && p < B.z1))) {
             T q[5], d[3][5], lap[5], fd;
-            stencil_ring<Shape>(sQ[s1], sQ[s2], sQ[s3], rc, q, d, lap);
+            stencil_ring<Shape, RS>(sQ[s1], sQ[s2], sQ[s3], rc, q, d, lap);
             if constexpr (SPLIT) {
                 T tau3[3];
                 site_split<T, 2>(c, q, d, lap, sig0, tau3, h0, fd);
@@ -485,6 +493,7 @@ __global__ __launch_bounds__(KernelTile<T>::NB) __attribute__((amdgpu_waves_per_
                 }
             }
         }
+        copies_done();  // and the populations, ahead of the stores, which are not waited for
         if (tile) {
             if (lb) {
                 T f[3], uu[3], rho;
@@ -525,11 +534,12 @@ __global__ __launch_bounds__(KernelTile<T>::NB) __attribute__((amdgpu_waves_per_
         }
         if (dbg_nan) {  // the free slot and the stress of plane p-1 are no longer read
             __syncthreads();
-            nan_fill(sQ[s0], 5 * Shape::RN);
+            nan_fill(sQ[s0], 5 * RS);
             nan_fill(const_cast<T *>(Pp), 6 * Shape::PN);
             __syncthreads();
+            if (more) stage(p + 2, s0);
+            copies_done();
         }
-        if (more) L.store(pre, sQ[s0]);  // plane p+2 into the free slot
         __syncthreads();
         const int o = s0;
         s0 = s1;
@@ -1395,7 +1405,7 @@ int tz_fill_t(const Device &D, int rounds)
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bq, k_qupdate<T>, UpdateTile<T>::NB, 0) != hipSuccess) return 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bf, k_qforce<T, false>, S::NB, 0) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bl, k_qlb<T, false>, S::NB, 0) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bl, (k_qlb<T, false, KernelTile<T>>), S::NB, 0) != hipSuccess) return 0;
     const long long slots = (long long)cus * std::max(1, std::min(bq, std::min(bf, bl))) * rounds;
     const long long cols = (long long)((D.G.nx + S::TX - 1) / S::TX) * ((D.G.ny + S::TY - 1) / S::TY);
     const long long chunks = slots / cols;
@@ -1468,6 +1478,8 @@ hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *time
         k_fill<T><<<1024, BLK, 0, D.stream>>>(u, 3 * size_t(G.N), T(0));
     const TileGrid tg = tile_grid(G.nx, G.ny, G.nz, KernelTile<T>::TX, KernelTile<T>::TY, tile_tz(D));
     const TileGrid tgq = tile_grid(G.nx, G.ny, G.nz, UpdateTile<T>::TX, UpdateTile<T>::TY, tile_tzq(D));
+    const TileGrid tgw = tile_grid(G.nx, G.ny, G.nz, WideTile<T>::TX, WideTile<T>::TY, tile_tz(D));
+    const bool wide = wide_tiles<T>(G.nx);
     const int tb = KernelTile<T>::NB;
     const bool pairs = sc == SCHED_SITES && small_lattice(G, cus);
     const int nbr = StepBrick::blocks(G), lbr = (nbr + 7) / 8 * 8;
@@ -1479,7 +1491,12 @@ hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *time
             T *gout = static_cast<T *>(D.g[D.gcur ^ 1]);
             if (sc == SCHED_FUSED || sc == SCHED_FUSED_TILED) {
                 e = mark(K_QLB, [&] {
-                    k_qlb<T, SPLIT><<<tg.launch, tb, 0, D.stream>>>(G, c, tg, Q, gin, gout, u, dbg_nan);
+                    if (wide)
+                        k_qlb<T, SPLIT, WideTile<T>><<<tgw.launch, WideTile<T>::NB, 0, D.stream>>>(G, c, tgw, Q, gin,
+                                                                                                   gout, u, dbg_nan);
+                    else
+                        k_qlb<T, SPLIT, KernelTile<T>><<<tg.launch, tb, 0, D.stream>>>(G, c, tg, Q, gin, gout, u,
+                                                                                       dbg_nan);
                 });
             } else if (sc == SCHED_TILED) {
                 e = mark(K_QFORCE, [&] {

@@ -50,11 +50,23 @@ struct TileShape {
 // the fused stress and LB share a CU): the LB moves 41 values per site, and
 // rows of 16 sites, 64 bytes, cost it more than the blocks gain (a 192^3 step
 // 600 us where 32 x 8 takes 475).  FP64: 16 x 12 sites (252 points, four
-// waves): the FP64 kernels hold about 180 and 230 registers, two waves per
+// waves): the FP64 kernels hold about 180 and 200 registers, two waves per
 // SIMD, so two four-wave blocks share a CU where a six-wave block would run
 // alone with a quarter of the CU's wave slots empty.
 template <typename T>
 using KernelTile = typename std::conditional<sizeof(T) == 8, TileShape<16, 12>, TileShape<32, 8>>::type;
+
+// The tile of the fused stress and LB on lattices whose rows it fills to a
+// tenth: 256 bytes a row, which the populations gain more from than the ring,
+// 1.44 to 1.59 points a site instead of 1.31, costs (measured at k_qlb).
+template <typename T>
+using WideTile = typename std::conditional<sizeof(T) == 8, TileShape<32, 4>, TileShape<64, 5>>::type;
+template <typename T>
+inline bool wide_tiles(int nx)
+{
+    const int TX = WideTile<T>::TX;
+    return 10 * ((nx + TX - 1) / TX * TX - nx) <= nx;
+}
 
 // The tile of the Q update, which is bound by its instructions and not by
 // memory: blocks of four waves, one to each SIMD, of which four share a CU in
