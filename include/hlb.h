@@ -238,7 +238,7 @@ int hlb_set_state(hlb_ctx *ctx, const void *host_buf, size_t nbytes);
 /* Step schedules.  HLB_SCHED_SITES: four sweeps with one lattice site per
  * thread (stress to HBM, LB with its divergence, predictor, corrector in
  * place), on lattices too small to fill the device two sweeps of the same
- * arithmetic, bit for bit (stress and LB, predictor and corrector).
+ * arithmetic (stress and LB, predictor and corrector).
  * HLB_SCHED_TILED: three sweeps in which 2.5D z-marching LDS tiles hold the
  * stress and the predictor stage (recomputed on a one-site halo ring; tiles
  * of 16 x 12 sites, in FP32 of 32 x 8 for the stress), tz planes per tile

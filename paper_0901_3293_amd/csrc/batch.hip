@@ -138,19 +138,6 @@ __device__ __forceinline__ Coef<T> uni(const Coef<T> &c)
     r.rho0 = uni(c.rho0);
     r.omega = uni(c.omega);
     r.pref = uni(c.pref);
-    r.lin0 = uni(c.lin0);
-    r.Kq0 = uni(c.Kq0);
-    r.K4 = uni(c.K4);
-    r.K8 = uni(c.K8);
-    r.xip = uni(c.xip);
-    r.xim = uni(c.xim);
-    r.xi23 = uni(c.xi23);
-    r.hp = uni(c.hp);
-    r.hm = uni(c.hm);
-    r.xih = uni(c.xih);
-    r.xi3 = uni(c.xi3);
-    r.xi6 = uni(c.xi6);
-    r.xi9 = uni(c.xi9);
     return r;
 }
 

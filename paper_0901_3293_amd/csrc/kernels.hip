@@ -205,11 +205,11 @@ __device__ __forceinline__ void copies_done()
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), no other counter
 }
 
-// Q, twice its derivatives and its Laplacian at staged coordinate r of plane p:
-// the value and its in-plane neighbours from the staged slot `mid` (two-site
-// halo, RS values from one component to the next), the z-neighbours from `lo` (plane p-1,
-// registers of the thread owning the point) and the staged slot `hi`
-// (plane p+1).
+// Derivatives of the 5-component Q at staged coordinate r of plane p: the
+// value and its in-plane neighbours from the staged slot `mid` (two-site
+// halo, RS values from one component to the next), the z-neighbours from `lo`
+// (plane p-1, registers of the thread owning the point) and the staged slot
+// `hi` (plane p+1).
 template <class Shape, int RS, typename T>
 __device__ __forceinline__ void stencil_staged(const T lo[5], const T *mid, const T *hi, int r, T q[5],
                                                T d[3][5], T lap[5])
@@ -237,9 +237,9 @@ __device__ __forceinline__ void stencil_ring(const T *lo, const T *mid, const T 
     }
 }
 
-// Same for a 5-component field held on the evaluation plane (PX x PY, PN points
-// per component) at point r: value and in-plane neighbours from `mid`,
-// z-neighbours from registers.
+// Derivatives of a 5-component field held on the evaluation plane (PX x PY,
+// PN points per component) at point r: value and in-plane neighbours from
+// `mid`, z-neighbours from registers.
 template <class Shape, typename T>
 __device__ __forceinline__ void stencil_eval(const T lo[5], const T *mid, const T hi[5], int r, T q[5],
                                              T d[3][5], T lap[5])
@@ -253,8 +253,8 @@ __device__ __forceinline__ void stencil_eval(const T lo[5], const T *mid, const 
     }
 }
 
-// u and twice its centred gradient, W_ab = 2 d_b u_a, at staged coordinate r of
-// plane p: in-plane from `mid`, z from `lo` (registers, plane p-1) and `hi`.
+// u and its centred gradient W_ab = d_b u_a at staged coordinate r of plane
+// p: in-plane from `mid`, z from `lo` (registers, plane p-1) and `hi`.
 template <class Shape, int RS, typename T>
 __device__ __forceinline__ void velocity_staged(const T lo[3], const T *mid, const T *hi, int r, T uc[3],
                                                 T W[3][3])
@@ -263,9 +263,9 @@ __device__ __forceinline__ void velocity_staged(const T lo[3], const T *mid, con
     for (int a = 0; a < 3; ++a) {
         const int o = a * RS + r;
         uc[a] = mid[o];
-        W[a][0] = mid[o + 1] - mid[o - 1];
-        W[a][1] = mid[o + Shape::RX] - mid[o - Shape::RX];
-        W[a][2] = hi[o] - lo[a];
+        W[a][0] = T(0.5) * (mid[o + 1] - mid[o - 1]);
+        W[a][1] = T(0.5) * (mid[o + Shape::RX] - mid[o - Shape::RX]);
+        W[a][2] = T(0.5) * (hi[o] - lo[a]);
     }
 }
 
@@ -351,7 +351,7 @@ __global__ __launch_bounds__(KernelTile<T>::NB) __attribute__((amdgpu_waves_per_
         if (eval && (tile || (p >= B.z0 && p < B.z1))) {
             T q[5], d[3][5], lap[5], P[3][3], fd, H[5];
             stencil_ring<Shape, Shape::RN>(sQ[s1], sQ[s2], sQ[s3], rc, q, d, lap);
-            site_stress<T, 2>(c, q, d, lap, P, fd, H);
+            site_stress(c, q, d, lap, P, fd, H);
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 Pc[a * Shape::PN + pc] = P[a][0];
@@ -409,7 +409,7 @@ __global__ __launch_bounds__(KernelTile<T>::NB) __attribute__((amdgpu_waves_per_
 // force b_a = d_b tau_ab + h_a, and a tile thread keeps sigma^xi and h of its
 // site of plane p-1 in registers for the collision with sigma^xi in the
 // equilibrium.
-// FP32: 110 registers, four waves per SIMD, two blocks per CU; FP64: about 200,
+// FP32: 111 registers, four waves per SIMD, two blocks per CU; FP64: about 200,
 // two waves per SIMD and two four-wave blocks.  The planes of Q go straight into
 // LDS (staged through registers: 127 and 231).
 // Bound by memory, 46 values per site: rows as long as a lattice row's share
@@ -477,14 +477,14 @@ __global__ __launch_bounds__(Shape::NB) void k_qlb(Geom G, Coef<T> c, TileGrid t
             stencil_ring<Shape, RS>(sQ[s1], sQ[s2], sQ[s3], rc, q, d, lap);
             if constexpr (SPLIT) {
                 T tau3[3];
-                site_split<T, 2>(c, q, d, lap, sig0, tau3, h0, fd);
+                site_split(c, q, d, lap, sig0, tau3, h0, fd);
 #pragma unroll
                 for (int k = 0; k < 3; ++k) Pc[k * Shape::PN + pc] = tau3[k];
                 Pz[0] = tau3[1];
                 Pz[1] = tau3[2];
             } else {
                 T P[3][3], H[5];
-                site_stress<T, 2>(c, q, d, lap, P, fd, H);
+                site_stress(c, q, d, lap, P, fd, H);
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
                     Pc[a * Shape::PN + pc] = P[a][0];
@@ -501,10 +501,10 @@ __global__ __launch_bounds__(Shape::NB) void k_qlb(Geom G, Coef<T> c, TileGrid t
                     // b_a = d_b tau_ab + h_a at plane p-1: in-plane differences from LDS,
                     // z differences from the own point's tau at planes p and p-2
                     const T *txy = Pp, *txz = Pp + Shape::PN, *tyz = Pp + 2 * Shape::PN;
-                    f[0] = fmat(T(0.5), (txy[pc + Shape::PX] - txy[pc - Shape::PX]) + (Pz[0] - Pz2[0]), h1[0]);
-                    f[1] = fmat(T(0.5), (Pz[1] - Pz2[1]) - (txy[pc + 1] - txy[pc - 1]), h1[1]);
-                    f[2] = fmat(T(0.5), -(txz[pc + 1] - txz[pc - 1]) - (tyz[pc + Shape::PX] - tyz[pc - Shape::PX]),
-                                h1[2]);
+                    f[0] = T(0.5) * ((txy[pc + Shape::PX] - txy[pc - Shape::PX]) + (Pz[0] - Pz2[0])) + h1[0];
+                    f[1] = T(0.5) * ((Pz[1] - Pz2[1]) - (txy[pc + 1] - txy[pc - 1])) + h1[1];
+                    f[2] = T(0.5) * (-(txz[pc + 1] - txz[pc - 1]) - (tyz[pc + Shape::PX] - tyz[pc - Shape::PX])) +
+                           h1[2];
                     lb_collide_split(c, g, f, sig1, uu, rho);
                 } else {
 #pragma unroll
@@ -560,14 +560,14 @@ __global__ __launch_bounds__(Shape::NB) void k_qlb(Geom G, Coef<T> c, TileGrid t
 // Q*(p-2), Q*(p) in registers, with u(p-1) and W(p-1) kept from the
 // predictor of plane p-1.  Q*(p) goes into the other of two LDS buffers and the
 // plane p+2 is copied into the third staging slot meanwhile, so a plane takes
-// one barrier.  FP32: 127 registers and 40.8 kB, four blocks a CU; FP64: 170
+// one barrier.  FP32: 127 registers and 40.8 kB, four blocks a CU; FP64: 208
 // and 81.6 kB, two.
-// Bound by issue: about 400 vector instructions a point and plane, of which the
+// Bound by issue: about 450 vector instructions a point and plane, of which the
 // ring and the two extra planes of a chunk repeat half.  FP32 at 192^3: 222 us
-// with 32 x 8 tiles staged through registers, 157 us now (590 MB of Q and u, 3.8
-// TB/s); at 128^3 65 and 51 us, where k_qpred and k_qcorr take 52.  FP64, staged
+// with 32 x 8 tiles staged through registers, 160 us now (590 MB of Q and u, 3.7
+// TB/s); at 128^3 65 and 53 us, where k_qpred and k_qcorr take 47.  FP64, staged
 // through registers into two slots and one buffer with two barriers a plane:
-// 96^3 55 us and now 44, 128^3 95 and 93, 192^3 297 and 272.
+// 96^3 55 us and now 46, 128^3 97 and 97, 192^3 297 and 279.
 template <typename T>
 __global__ __launch_bounds__(UpdateTile<T>::NB) void k_qupdate(Geom G, Coef<T> c, TileGrid tg,
                                                        const T *__restrict__ Qin, const T *__restrict__ u,
@@ -642,7 +642,7 @@ __global__ __launch_bounds__(UpdateTile<T>::NB) void k_qupdate(Geom G, Coef<T> c
             T q[5], d[3][5], lap[5], uc[3], R[5];
             stencil_staged<Shape, RS>(qmm, sQ[sc], sQ[sn], rc, q, d, lap);
             velocity_staged<Shape, RS>(umm, sU[sc], sU[sn], rc, uc, W0);
-            site_rhs<T, 2>(c, q, d, lap, uc, W0, R);
+            site_rhs(c, q, d, lap, uc, W0, R);
 #pragma unroll
             for (int k = 0; k < 5; ++k) {
                 qs0[k] = q[k] + R[k];
@@ -653,7 +653,7 @@ __global__ __launch_bounds__(UpdateTile<T>::NB) void k_qupdate(Geom G, Coef<T> c
         if (tile && p - 1 >= B.z0) {
             T q[5], d[3][5], lap[5], R[5];
             stencil_eval<Shape>(qs2, Sprev, qs0, pc, q, d, lap);
-            site_rhs<T, 2>(c, q, d, lap, umm, Wmm, R);
+            site_rhs(c, q, d, lap, umm, Wmm, R);
 #pragma unroll
             for (int k = 0; k < 5; ++k) {
                 out[k] = T(0.5) * (qmm[k] + q[k] + R[k]);
@@ -764,9 +764,9 @@ __global__ __launch_bounds__(B, sizeof(T) == 8 ? 4 : 1) void k_qcorr(Geom G, Coe
 // The same, two sites per thread (nx even), in FP64: a wave's load of one value
 // per lane is 512 bytes there, and the 61 to 66 of them that a site takes in k_qpred
 // and k_qcorr fill a CU's path to its cache; two sites a thread take 56 to 61 of
-// twice the width and no shifted rows.  254 registers, two waves per SIMD.  Both
-// together at 96^3 57 -> 45 us, 128^3 123 -> 100 (520 MB if nothing is cached: the
-// memory's rate), 64^3 21 -> 16.  In FP32 they are slower (128^3 52 -> 58): one
+// twice the width and no shifted rows.  About 235 registers, two waves per SIMD.
+// Both together at 96^3 57 -> 45 us, 128^3 123 -> 100 (520 MB if nothing is cached:
+// the memory's rate), 64^3 21 -> 17.  In FP32 they are slower (128^3 52 -> 58): one
 // value per lane is at the memory's rate already, with four times the waves.
 template <typename T, int B>
 __global__ __launch_bounds__(B) void k_qpred2(Geom G, Coef<T> c, const T *__restrict__ Q, const T *__restrict__ u,
@@ -789,7 +789,7 @@ __global__ __launch_bounds__(B) void k_qcorr2(Geom G, Coef<T> c, T *__restrict__
 // k_lb, k_bq is k_qpred and k_qcorr.  A block evaluates the first of the two on
 // its brick and the brick's six faces, one point per thread, into LDS, and the
 // second on the brick out of LDS; the stencils come from global memory as in
-// the per-site sweeps, whose results these give bit for bit.  That is about
+// the per-site sweeps, whose arithmetic these repeat.  That is about
 // twice the evaluations, but on a lattice that does not fill the chip a kernel
 // takes 3.5 us or more, whatever it computes, and a step has two of them instead
 // of four (see small_lattice).
@@ -882,12 +882,12 @@ __global__ __launch_bounds__(B::NB) void k_blb(Geom G, Coef<T> c, int nblocks, c
     gather_q(Q, N, O, q, d, lap);
     if constexpr (SPLIT) {
         T tau3[3];
-        site_split<T, 2>(c, q, d, lap, sig, tau3, h, fd);
+        site_split(c, q, d, lap, sig, tau3, h, fd);
 #pragma unroll
         for (int k = 0; k < 3; ++k) sP[k][p] = tau3[k];
     } else {
         T P[3][3], H[5];
-        site_stress<T, 2>(c, q, d, lap, P, fd, H);
+        site_stress(c, q, d, lap, P, fd, H);
 #pragma unroll
         for (int k = 0; k < 9; ++k) sP[k][p] = P[k / 3][k % 3];
     }
@@ -896,9 +896,9 @@ __global__ __launch_bounds__(B::NB) void k_blb(Geom G, Coef<T> c, int nblocks, c
     T f[3], uu[3], rho;
     if constexpr (SPLIT) {
         const T *txy = sP[0], *txz = sP[1], *tyz = sP[2];
-        f[0] = fmat(T(0.5), (txy[p + DY] - txy[p - DY]) + (txz[p + DZ] - txz[p - DZ]), h[0]);
-        f[1] = fmat(T(0.5), (tyz[p + DZ] - tyz[p - DZ]) - (txy[p + DX] - txy[p - DX]), h[1]);
-        f[2] = fmat(T(0.5), -(txz[p + DX] - txz[p - DX]) - (tyz[p + DY] - tyz[p - DY]), h[2]);
+        f[0] = T(0.5) * ((txy[p + DY] - txy[p - DY]) + (txz[p + DZ] - txz[p - DZ])) + h[0];
+        f[1] = T(0.5) * ((tyz[p + DZ] - tyz[p - DZ]) - (txy[p + DX] - txy[p - DX])) + h[1];
+        f[2] = T(0.5) * (-(txz[p + DX] - txz[p - DX]) - (tyz[p + DY] - tyz[p - DY])) + h[2];
         lb_collide_split(c, g, f, sig, uu, rho);
     } else {
 #pragma unroll
@@ -924,10 +924,19 @@ __global__ __launch_bounds__(B::NB) void k_bq(Geom G, Coef<T> c, int nblocks, co
     const BrickPoint b = brick_point<B>(G, block);
     const int N = G.N, p = b.p;
     const Off<T> O = offsets<T>(b.S);
-    T qn[5], q[5], d[3][5], lap[5], uc[3], W[3][3], R[5];
+    T qn[5], q[5], d[3][5], lap[5], uc[3], V[3][3], W[3][3], R[5];
     gather_q(Q, N, O, qn, d, lap);
-    gather_u(u, N, O, uc, W);
-    site_rhs<T, 2>(c, qn, d, lap, uc, W, R);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const T *P = plane(u, a, N);
+        uc[a] = *at(P, O.s);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+            V[a][e] = *at(P, O.nb[2 * e]) - *at(P, O.nb[2 * e + 1]);
+            W[a][e] = T(0.5) * V[a][e];
+        }
+    }
+    site_rhs(c, qn, d, lap, uc, W, R);
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
         q[k] = qn[k] + R[k];
@@ -935,12 +944,22 @@ __global__ __launch_bounds__(B::NB) void k_bq(Geom G, Coef<T> c, int nblocks, co
     }
     __syncthreads();
     if (!b.mine) return;
+    // The gradient once more from the differences, which the compiler may not
+    // trace back: shared between the two stages, its products would be fused
+    // otherwise than in k_qpred and k_qcorr.
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+            asm volatile("" : "+v"(V[a][e]));
+            W[a][e] = T(0.5) * V[a][e];
+        }
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
         const T *P = sS[k] + p;
         stencil7(q[k], P[DX], P[-DX], P[DY], P[-DY], P[DZ], P[-DZ], d[0][k], d[1][k], d[2][k], lap[k]);
     }
-    site_rhs<T, 2>(c, q, d, lap, uc, W, R);
+    site_rhs(c, q, d, lap, uc, W, R);
 #pragma unroll
     for (int k = 0; k < 5; ++k) *at(plane(Qout, k, N), O.s) = T(0.5) * (qn[k] + q[k] + R[k]);
 }

@@ -12,10 +12,7 @@
 
 namespace hlb {
 
-// Physical constants of one run, pre-combined in the arithmetic type.  The
-// kernels hand over the differences f(x + 1) - f(x - 1), twice the centred
-// derivative, and the factors 1/2 sit in the constants below (powers of two, so
-// nothing is rounded differently).
+// Physical constants of one run, pre-combined in the arithmetic type.
 template <typename T>
 struct Coef {
     T a;       // A0 (1 - gamma/3)                 bulk quadratic, Sec. 2.1 Eq. (1)
@@ -29,37 +26,7 @@ struct Coef {
     T rho0;    // reference density of the deviation populations
     T omega;   // 1 / tau_LB
     T pref;    // 1 - 1/(2 tau_LB), second-order forcing prefactor
-    T lin0;    // -(a + 4 K q0^2)                  linear term of H
-    T Kq0;     // K q0
-    T K4, K8;  // K / 4, K / 8
-    T xip, xim;    // xi + 1, 1 - xi
-    T xi23;    // 2 xi / 3
-    T hp, hm;  // (xi + 1) / 4, (xi - 1) / 4       M = xi D + w from twice W
-    T xih;     // xi / 2
-    T xi3;     // xi / 3
-    T xi6;     // xi / 6
-    T xi9;     // xi / 9
 };
-
-// a b + c with one rounding in either precision.  The site functions spell
-// out their fused products (contraction by the compiler is off in them), so
-// that every kernel that inlines them rounds alike.
-template <typename T>
-__host__ __device__ __forceinline__ T fmat(T a, T b, T c)
-{
-    if constexpr (sizeof(T) == 4)
-        return __builtin_fmaf(a, b, c);
-    else
-        return __builtin_fma(a, b, c);
-}
-
-// a b + c d + e f
-template <typename T>
-__host__ __device__ __forceinline__ T dot3(T a, T b, T c, T d, T e, T f)
-{
-#pragma clang fp contract(off)
-    return fmat(e, f, fmat(c, d, a * b));
-}
 
 template <typename T>
 __host__ __device__ __forceinline__ void full3(const T q[5], T Q[3][3])
@@ -139,54 +106,31 @@ __host__ __device__ __forceinline__ T free_energy(const Coef<T> &c, const T Q[3]
     return T(0.5) * c.a * trQ2 - c.bg * trQ3 / T(3) + T(0.25) * c.bg * trQ2 * trQ2 + T(0.5) * c.K * (dd + mm);
 }
 
-// Upper triangle (xx, xy, xz, yy, yz, zz) of Q^2 for symmetric traceless Q, and
-// its trace.  Off the diagonal the trace saves a product:
-// (Q^2)_xy = q_xy (q_xx + q_yy) + q_xz q_yz = q_xz q_yz - q_xy q_zz.
+// Upper triangle (xx, xy, xz, yy, yz, zz) of Q^2 for symmetric Q, and its
+// trace.
 template <typename T>
 __host__ __device__ __forceinline__ void square_sym(const T q[5], T qzz, T s[6], T &tr)
 {
-#pragma clang fp contract(off)
-    const T p1 = q[1] * q[1];
-    s[0] = fmat(q[0], q[0], fmat(q[2], q[2], p1));
-    s[1] = fmat(q[2], q[4], -(q[1] * qzz));
-    s[2] = fmat(q[1], q[4], -(q[2] * q[3]));
-    s[3] = fmat(q[3], q[3], fmat(q[4], q[4], p1));
-    s[4] = fmat(q[1], q[2], -(q[4] * q[0]));
-    s[5] = fmat(qzz, qzz, fmat(q[4], q[4], q[2] * q[2]));
-    tr = (s[0] + s[3]) + s[5];
+    s[0] = q[0] * q[0] + q[1] * q[1] + q[2] * q[2];
+    s[1] = q[0] * q[1] + q[1] * q[3] + q[2] * q[4];
+    s[2] = q[0] * q[2] + q[1] * q[4] + q[2] * qzz;
+    s[3] = q[1] * q[1] + q[3] * q[3] + q[4] * q[4];
+    s[4] = q[1] * q[2] + q[3] * q[4] + q[4] * qzz;
+    s[5] = q[2] * q[2] + q[4] * q[4] + qzz * qzz;
+    tr = s[0] + s[3] + s[5];
 }
 
-// Molecular field H (Eq. (2), as molecular_field) from the stored components,
-// Q^2 (s, with trace tr) and the curl sums
-//   C = {CQ_xx, CQ_xy + CQ_yx, CQ_xz + CQ_zx, CQ_yy, CQ_yz + CQ_zy}
-// of S times the derivatives (the diagonal entries enter H twice).
-template <int S, typename T>
-__host__ __device__ __forceinline__ void field_from(const Coef<T> &c, const T q[5], const T s[6], T tr, const T C[5],
-                                                    const T lap[5], T H[5])
-{
-#pragma clang fp contract(off)
-    static_assert(S == 1 || S == 2, "derivatives, or twice them");
-    const T off = S == 2 ? -c.Kq0 : -c.Kq0x2, diag = T(2) * off;
-    const T lin = fmat(-c.bg, tr, c.lin0);
-    const T tr3 = tr * (T(1) / T(3));
-    H[0] = fmat(lin, q[0], fmat(c.bg, s[0] - tr3, fmat(c.K, lap[0], diag * C[0])));
-    H[1] = fmat(lin, q[1], fmat(c.bg, s[1], fmat(c.K, lap[1], off * C[1])));
-    H[2] = fmat(lin, q[2], fmat(c.bg, s[2], fmat(c.K, lap[2], off * C[2])));
-    H[3] = fmat(lin, q[3], fmat(c.bg, s[3] - tr3, fmat(c.K, lap[3], diag * C[3])));
-    H[4] = fmat(lin, q[4], fmat(c.bg, s[4], fmat(c.K, lap[4], off * C[4])));
-}
-
-// Curl sums of field_from from (S times) the derivatives of the stored
-// components, d_g Q_zz = -(d_g Q_xx + d_g Q_yy).
+// Symmetric part (stored components) of CQ + (CQ)^T, the curl term of H, from
+// the derivatives of the stored components (d_g Q_zz = -(d_g Q_xx + d_g Q_yy)).
 template <typename T>
-__host__ __device__ __forceinline__ void curl_sums(const T d[3][5], T C[5])
+__host__ __device__ __forceinline__ void curl_sym(const T d[3][5], T C[5])
 {
-#pragma clang fp contract(off)
-    C[0] = d[1][2] - d[2][1];                                                       // dy Q_zx - dz Q_yx
-    C[1] = (d[1][4] - d[2][3]) + (d[2][0] - d[0][2]);                               // CQ_xy + CQ_yx
-    C[2] = (fmat(T(-2), d[1][0], d[0][1]) - d[1][3]) - d[2][4];                     // CQ_xz + CQ_zx
-    C[3] = d[2][1] - d[0][4];                                                       // dz Q_xy - dx Q_zy
-    C[4] = (fmat(T(2), d[0][3], d[0][0]) - d[1][1]) + d[2][2];                      // CQ_yz + CQ_zy
+    const T dzz0 = -(d[0][0] + d[0][3]), dzz1 = -(d[1][0] + d[1][3]);
+    C[0] = T(2) * (d[1][2] - d[2][1]);                    // 2 (dy Q_zx - dz Q_yx)
+    C[1] = (d[1][4] - d[2][3]) + (d[2][0] - d[0][2]);     // CQ_xy + CQ_yx
+    C[2] = (dzz1 - d[2][4]) + (d[0][1] - d[1][0]);        // CQ_xz + CQ_zx
+    C[3] = T(2) * (d[2][1] - d[0][4]);                    // 2 (dz Q_xy - dx Q_zy)
+    C[4] = (d[2][2] - dzz0) + (d[0][3] - d[1][1]);        // CQ_yz + CQ_zy
 }
 
 // Curl (CQ)_ab = eps_agd d_g Q_db from the derivatives of the stored
@@ -205,115 +149,88 @@ __host__ __device__ __forceinline__ void curl5(const T d[3][5], const T dzz[3], 
     CQ[2][2] = d[0][4] - d[1][2];  // dx Q_yz - dy Q_xz
 }
 
-// What the stresses share at one site: H, Q^2 and, for the gradient terms, S
-// times div Q and S times M = CQ + 2 q0 Q.
-template <typename T>
-struct Chem {
-    T s[6], tr, H[5], M[3][3], div[3];
-};
-
-template <int S, typename T>
-__host__ __device__ __forceinline__ void chem_at(const Coef<T> &c, const T q[5], T qzz, const T d[3][5],
-                                                 const T lap[5], Chem<T> &X)
-{
-#pragma clang fp contract(off)
-    const T dzz[3] = {-(d[0][0] + d[0][3]), -(d[1][0] + d[1][3]), -(d[2][0] + d[2][3])};
-    square_sym(q, qzz, X.s, X.tr);
-    curl5(d, dzz, X.M);
-    const T C[5] = {X.M[0][0], X.M[0][1] + X.M[1][0], X.M[0][2] + X.M[2][0], X.M[1][1], X.M[1][2] + X.M[2][1]};
-    field_from<S>(c, q, X.s, X.tr, C, lap, X.H);
-    const T m = S == 2 ? T(2) * c.q0x2 : c.q0x2;
-    const T Q[3][3] = {{q[0], q[1], q[2]}, {q[1], q[3], q[4]}, {q[2], q[4], qzz}};
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) X.M[a][b] = fmat(m, Q[a][b], X.M[a][b]);
-    X.div[0] = (d[0][0] + d[1][1]) + d[2][2];
-    X.div[1] = (d[0][1] + d[1][3]) + d[2][4];
-    X.div[2] = (d[0][2] + d[1][4]) + dzz[2];
-}
-
-// Free-energy density (Eq. (1) plus K/2 (d_b Q_ab)^2) from these:
-//   f = tr Q^2 (a/2 + bg/4 tr Q^2) - bg det Q + K/2 (|div Q|^2 + M:M)
-// (tr Q^3 = 3 det Q for traceless Q).
-template <int S, typename T>
-__host__ __device__ __forceinline__ T free_energy_of(const Coef<T> &c, const T q[5], T qzz, const Chem<T> &X)
-{
-#pragma clang fp contract(off)
-    const T det = fmat(q[0], fmat(q[3], qzz, -(q[4] * q[4])), fmat(q[1], X.s[1], q[2] * X.s[2]));
-    T m = fmat(X.div[2], X.div[2], fmat(X.div[1], X.div[1], X.div[0] * X.div[0]));
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) m = fmat(X.M[a][b], X.M[a][b], m);
-    const T bulk = fmat(T(0.25) * c.bg, X.tr, T(0.5) * c.a);
-    return fmat(bulk, X.tr, fmat(-c.bg, det, (S == 2 ? c.K8 : T(0.5) * c.K) * m));
-}
-
 // Chemical stress (Eqs. (6)-(8), the rho T part of the pressure left to the
 // lattice): Pi_ab = f d_ab + sigma^xi_ab - G_ab + tau_ab with
 //   sigma^xi = 2 xi (Q + I/3)(Q:H) - xi (HQ + QH + 2H/3),
 //   tau      = QH - HQ,
-//   G_ab     = d_a Q_gn Phi_gnb,  Phi_gnb = K [d_nb (div Q)_g + eps_lbg M_ln], M = CQ + 2 q0 Q.
-// Also returns f (Eq. (1) plus K/2 (d_b Q_ab)^2) and H (five components).  d:
-// S times the centred derivatives.
-// d_a Q is symmetric and traceless in (g, n), so G_ab takes five products with
-// the symmetric part of Phi, formed once per b for the five stored components
-// (xx and yy less zz, the others both ways; in the order xx, xy, xz, yy, yz):
-//   b = x: div_x + M_yz,  div_y + M_zx,  div_z - M_yx,  M_zy + M_yz,  M_zz - M_yy
-//   b = y: -(M_zx + M_xz),  div_x - M_zy,  M_xx - M_zz,  div_y - M_xz,  div_z + M_xy
-//   b = z: M_yx - div_z,  M_yy - M_xx,  div_x + M_yz,  -(M_xy + div_z),  div_y - M_xz
-// and sigma^xi + tau off the diagonal is 2 xi (Q:H) Q_ab - (2 xi/3) H_ab
-// - (xi + 1) (HQ)_ab + (1 - xi) (HQ)_ba.
-// With these the per-site FP32 stress kernel has 334 vector instructions (424
-// with G contracted over the full tensors), the predictor 250 (294) and the
-// corrector 260 (304); the step gained 1.5% in FP32 and 3% in FP64 at 128^3.
-template <typename T, int S = 1>
+//   G_ab     = d_a Q_gn Phi_gnb,  Phi_gnb = K [d_nb (div Q)_g + eps_lbg M_ln],
+// i.e. G_ab = K [ d_a Q_gb (div Q)_g + eps_bgl d_a Q_gn M_ln ], M = CQ + 2 q0 Q.
+// Also returns f (Eq. (1) plus K/2 (d_b Q_ab)^2) and H (five components).
+// sigma^xi is symmetric and tau antisymmetric (QH = (HQ)^T for symmetric H
+// and Q), so each is formed once per pair of entries.
+template <typename T>
 __host__ __device__ __forceinline__ void site_stress(const Coef<T> &c, const T q[5], const T d[3][5],
                                                      const T lap[5], T Pi[3][3], T &fdens, T H5[5])
 {
-#pragma clang fp contract(off)
     const T third = T(1) / T(3);
     const T qzz = -q[0] - q[3];
-    Chem<T> X;
-    chem_at<S>(c, q, qzz, d, lap, X);
-    fdens = free_energy_of<S>(c, q, qzz, X);
-    const T Q[3][3] = {{q[0], q[1], q[2]}, {q[1], q[3], q[4]}, {q[2], q[4], qzz}};
-    const T hzz = -X.H[0] - X.H[3];
-    const T H[3][3] = {{X.H[0], X.H[1], X.H[2]}, {X.H[1], X.H[3], X.H[4]}, {X.H[2], X.H[4], hzz}};
+    const T dzz[3] = {-(d[0][0] + d[0][3]), -(d[1][0] + d[1][3]), -(d[2][0] + d[2][3])};
+    T s[6], trQ2, CQ[3][3];
+    square_sym(q, qzz, s, trQ2);
+    curl5(d, dzz, CQ);
+    {
+        const T lin = -(c.a + c.bg * trQ2 + c.Kq0sq4);
+        const T diag = c.bg * trQ2 * third;
+        const T C[5] = {T(2) * CQ[0][0], CQ[0][1] + CQ[1][0], CQ[0][2] + CQ[2][0], T(2) * CQ[1][1],
+                        CQ[1][2] + CQ[2][1]};
+        const int k2s[5] = {0, 1, 2, 3, 4};
 #pragma unroll
-    for (int k = 0; k < 5; ++k) H5[k] = X.H[k];
+        for (int k = 0; k < 5; ++k) {
+            T v = lin * q[k] + c.bg * s[k2s[k]] + c.K * lap[k] - c.Kq0x2 * C[k];
+            if (k == 0 || k == 3) v -= diag;
+            H5[k] = v;
+        }
+    }
+    const T Q[3][3] = {{q[0], q[1], q[2]}, {q[1], q[3], q[4]}, {q[2], q[4], qzz}};
+    const T hzz = -H5[0] - H5[3];
+    const T H[3][3] = {{H5[0], H5[1], H5[2]}, {H5[1], H5[3], H5[4]}, {H5[2], H5[4], hzz}};
+    T M[3][3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) M[a][b] = CQ[a][b] + c.q0x2 * Q[a][b];
+    const T div[3] = {d[0][0] + d[1][1] + d[2][2], d[0][1] + d[1][3] + d[2][4], d[0][2] + d[1][4] + dzz[2]};
+    {
+        const T trQ3 = s[0] * q[0] + s[3] * q[3] + s[5] * qzz + T(2) * (s[1] * q[1] + s[2] * q[2] + s[4] * q[4]);
+        T mm = T(0);
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) mm += M[a][b] * M[a][b];
+        const T dd = div[0] * div[0] + div[1] * div[1] + div[2] * div[2];
+        fdens = T(0.5) * c.a * trQ2 - c.bg * trQ3 * third + T(0.25) * c.bg * trQ2 * trQ2 + T(0.5) * c.K * (dd + mm);
+    }
     T HQ[3][3];
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) HQ[a][b] = dot3(H[a][0], Q[0][b], H[a][1], Q[1][b], H[a][2], Q[2][b]);
-    const T xq = T(2) * c.xi * ((HQ[0][0] + HQ[1][1]) + HQ[2][2]);  // 2 xi Q:H
-    const T(&M)[3][3] = X.M;
-    const T(&v)[3] = X.div;
-    const T Phi[3][5] = {{v[0] + M[1][2], v[1] + M[2][0], v[2] - M[1][0], M[2][1] + M[1][2], M[2][2] - M[1][1]},
-                         {-(M[2][0] + M[0][2]), v[0] - M[2][1], M[0][0] - M[2][2], v[1] - M[0][2], v[2] + M[0][1]},
-                         {M[1][0] - v[2], M[1][1] - M[0][0], v[0] + M[1][2], -(M[0][1] + v[2]), v[1] - M[0][2]}};
-    const T mk = S == 2 ? -c.K4 : -c.K;
-    T G[3][3];  // -G_ab / (K / S^2)
+        for (int b = 0; b < 3; ++b) HQ[a][b] = H[a][0] * Q[0][b] + H[a][1] * Q[1][b] + H[a][2] * Q[2][b];
+    const T QdH = q[0] * H5[0] + q[3] * H5[3] + qzz * hzz + T(2) * (q[1] * H5[1] + q[2] * H5[2] + q[4] * H5[4]);
+    const T xq = T(2) * c.xi * QdH;
+    T sig[3][3], tau[3][3];
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            T g = d[a][0] * Phi[b][0];
-#pragma unroll
-            for (int k = 1; k < 5; ++k) g = fmat(d[a][k], Phi[b][k], g);
-            G[a][b] = g;
+        for (int b = a; b < 3; ++b) {
+            const T v = xq * (Q[a][b] + (a == b ? third : T(0))) -
+                        c.xi * (HQ[a][b] + HQ[b][a] + T(2) * third * H[a][b]);
+            sig[a][b] = v;
+            sig[b][a] = v;
+            const T w = HQ[b][a] - HQ[a][b];
+            tau[a][b] = w;
+            tau[b][a] = -w;
         }
-    const T iso = fmat(xq, third, fdens);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        Pi[a][a] = fmat(mk, G[a][a], fmat(T(-2) * c.xi, HQ[a][a], fmat(-c.xi23, H[a][a], fmat(xq, Q[a][a], iso))));
+        const T P[3][3] = {{d[a][0], d[a][1], d[a][2]}, {d[a][1], d[a][3], d[a][4]}, {d[a][2], d[a][4], dzz[a]}};
 #pragma unroll
-        for (int b = a + 1; b < 3; ++b) {
-            const T y = fmat(xq, Q[a][b], -(c.xi23 * H[a][b]));
-            Pi[a][b] = fmat(mk, G[a][b], fmat(-c.xip, HQ[a][b], fmat(c.xim, HQ[b][a], y)));
-            Pi[b][a] = fmat(mk, G[b][a], fmat(-c.xip, HQ[b][a], fmat(c.xim, HQ[a][b], y)));
+        for (int b = 0; b < 3; ++b) {
+            // G_ab; the eps_bgl M-contraction written out per column b
+            T g = P[0][b] * div[0] + P[1][b] * div[1] + P[2][b] * div[2];
+            const int b1 = (b + 1) % 3, b2 = (b + 2) % 3;
+#pragma unroll
+            for (int n = 0; n < 3; ++n) g += P[b1][n] * M[b2][n] - P[b2][n] * M[b1][n];
+            Pi[a][b] = (a == b ? fdens : T(0)) + sig[a][b] - c.K * g + tau[a][b];
         }
     }
 }
@@ -324,51 +241,82 @@ __host__ __device__ __forceinline__ void site_stress(const Coef<T> &c, const T q
 // (upper triangle xx, xy, xz, yy, yz, zz), the antisymmetric stress
 // tau = QH - HQ (xy, xz, yz), and h_a = -H:d_a Q, the divergence of the
 // gradient and free-energy part of the stress by the identity of Eq. (21).
-// The body force is b_a = d_b tau_ab + h_a.  Also returns f.  d: S times the
-// centred derivatives.
-template <typename T, int S = 1>
+// The body force is b_a = d_b tau_ab + h_a.  Also returns f.
+template <typename T>
 __host__ __device__ __forceinline__ void site_split(const Coef<T> &c, const T q[5], const T d[3][5], const T lap[5],
                                            T sig[6], T tau3[3], T h[3], T &fdens)
 {
-#pragma clang fp contract(off)
-    const T third = T(1) / T(3);
-    const T qzz = -q[0] - q[3];
-    Chem<T> X;
-    chem_at<S>(c, q, qzz, d, lap, X);
-    fdens = free_energy_of<S>(c, q, qzz, X);
-    const T Q[3][3] = {{q[0], q[1], q[2]}, {q[1], q[3], q[4]}, {q[2], q[4], qzz}};
-    const T hzz = -X.H[0] - X.H[3];
-    const T H[3][3] = {{X.H[0], X.H[1], X.H[2]}, {X.H[1], X.H[3], X.H[4]}, {X.H[2], X.H[4], hzz}};
+    T Q[3][3], dQ[3][3][3], CQ[3][3], Q2[3][3], trQ2, H5[5];
+    full3(q, Q);
+    full_grad(d, dQ);
+    curl(dQ, CQ);
+    molecular_field(c, Q, CQ, lap, H5, Q2, trQ2);
+    T H[3][3];
+    full3(H5, H);
+
+    T M[3][3], div[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+#pragma unroll
+        for (int b = 0; b < 3; ++b) M[a][b] = CQ[a][b] + c.q0x2 * Q[a][b];
+        div[a] = dQ[0][a][0] + dQ[1][a][1] + dQ[2][a][2];
+    }
+    fdens = free_energy(c, Q, Q2, trQ2, div, M);
+
     T HQ[3][3];
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) HQ[a][b] = dot3(H[a][0], Q[0][b], H[a][1], Q[1][b], H[a][2], Q[2][b]);
-    const T xq = T(2) * c.xi * ((HQ[0][0] + HQ[1][1]) + HQ[2][2]);
-    const T iso = xq * third;
+        for (int b = 0; b < 3; ++b) HQ[a][b] = H[a][0] * Q[0][b] + H[a][1] * Q[1][b] + H[a][2] * Q[2][b];
+    T QdH = T(0);
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) QdH += Q[a][b] * H[a][b];
+
+    const T third = T(1) / T(3);
     const int ia[6] = {0, 0, 0, 1, 1, 2};
     const int ib[6] = {0, 1, 2, 1, 2, 2};
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
         const int a = ia[k], b = ib[k];
-        if (a == b)
-            sig[k] = fmat(T(-2) * c.xi, HQ[a][a], fmat(-c.xi23, H[a][a], fmat(xq, Q[a][a], iso)));
-        else
-            sig[k] = fmat(-c.xi, HQ[a][b] + HQ[b][a], fmat(xq, Q[a][b], -(c.xi23 * H[a][b])));
+        sig[k] = T(2) * c.xi * (Q[a][b] + (a == b ? third : T(0))) * QdH
+               - c.xi * (HQ[a][b] + HQ[b][a] + T(2) * third * H[a][b]);
     }
     // (QH)_ab = (HQ)_ba for symmetric H and Q
     tau3[0] = HQ[1][0] - HQ[0][1];
     tau3[1] = HQ[2][0] - HQ[0][2];
     tau3[2] = HQ[2][1] - HQ[1][2];
-    // H:d_a Q over the stored components: xx and yy less zz, the others twice
-    const T s = S == 2 ? T(-0.5) : T(-1);
-    const T w[5] = {s * (X.H[0] - hzz), T(2) * s * X.H[1], T(2) * s * X.H[2], s * (X.H[3] - hzz), T(2) * s * X.H[4]};
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        T g = w[0] * d[a][0];
+        T v = T(0);
 #pragma unroll
-        for (int k = 1; k < 5; ++k) g = fmat(w[k], d[a][k], g);
-        h[a] = g;
+        for (int g = 0; g < 3; ++g)
+#pragma unroll
+            for (int n = 0; n < 3; ++n) v += H[g][n] * dQ[a][g][n];
+        h[a] = -v;
+    }
+}
+
+// Molecular field from the stored components (the same H as molecular_field,
+// written for the five components).
+template <typename T>
+__host__ __device__ __forceinline__ void molecular_field5(const Coef<T> &c, const T q[5], const T d[3][5],
+                                                          const T lap[5], T H[5])
+{
+    const T qzz = -q[0] - q[3];
+    T s[6], trQ2, C[5];
+    square_sym(q, qzz, s, trQ2);
+    curl_sym(d, C);
+    const T third = T(1) / T(3);
+    const T lin = -(c.a + c.bg * trQ2 + c.Kq0sq4);
+    const T diag = c.bg * trQ2 * third;
+    const int k2s[5] = {0, 1, 2, 3, 4};
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        T v = lin * q[k] + c.bg * s[k2s[k]] + c.K * lap[k] - c.Kq0x2 * C[k];
+        if (k == 0 || k == 3) v -= diag;
+        H[k] = v;
     }
 }
 
@@ -380,48 +328,40 @@ __host__ __device__ __forceinline__ void site_split(const Coef<T> &c, const T q[
 // Written with M = xi D + w: the first two terms are M Q + (M Q)^T + (2 xi/3) D
 // (Q symmetric, so Q M^T = (M Q)^T), tr(QW) = Q:W, and tr S = (2 xi/3) div u
 // is the only trace in the bracket (u.grad Q and H are traceless), so the
-// projection removes (2 xi/9) div u from the diagonal.  d and W: S times the
-// centred derivatives.
-template <typename T, int S = 1>
+// projection removes (2 xi/9) div u from the diagonal.
+template <typename T>
 __host__ __device__ __forceinline__ void site_rhs(const Coef<T> &c, const T q[5], const T d[3][5], const T lap[5],
                                                   const T u[3], const T W[3][3], T R[5])
 {
-#pragma clang fp contract(off)
+    T H[5];
+    molecular_field5(c, q, d, lap, H);
     const T qzz = -q[0] - q[3];
-    T s[6], tr, C[5], H[5];
-    square_sym(q, qzz, s, tr);
-    curl_sums(d, C);
-    field_from<S>(c, q, s, tr, C, lap, H);
     const T Q[3][3] = {{q[0], q[1], q[2]}, {q[1], q[3], q[4]}, {q[2], q[4], qzz}};
-    const T k2 = S == 2 ? T(1) : T(2);  // the constants below are those of S = 2
-    const T hp = k2 * c.hp, hm = k2 * c.hm, xw = k2 * c.xih;
+    const T hp = T(0.5) * (c.xi + T(1)), hm = T(0.5) * (c.xi - T(1));
     T M[3][3];
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) M[a][b] = a == b ? xw * W[a][a] : fmat(hp, W[a][b], hm * W[b][a]);
+        for (int b = 0; b < 3; ++b) M[a][b] = a == b ? c.xi * W[a][a] : hp * W[a][b] + hm * W[b][a];
     // M Q, the entries the five stored components of S need
     T P[3][3];
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) P[a][b] = dot3(M[a][0], Q[0][b], M[a][1], Q[1][b], M[a][2], Q[2][b]);
+        for (int b = 0; b < 3; ++b) P[a][b] = M[a][0] * Q[0][b] + M[a][1] * Q[1][b] + M[a][2] * Q[2][b];
     const T s01 = W[0][1] + W[1][0], s02 = W[0][2] + W[2][0], s12 = W[1][2] + W[2][1];
-    const T QW = fmat(q[4], s12, fmat(q[2], s02, fmat(q[1], s01, dot3(q[0], W[0][0], q[3], W[1][1], qzz, W[2][2]))));
-    const T t = (S == 2 ? -c.xi : T(-2) * c.xi) * QW;  // -2 xi tr(QW)
-    const T x3 = k2 * c.xi6, x23 = k2 * c.xi3;         // xi/3 and 2 xi/3 over S
-    const T iso = fmat(t, T(1) / T(3), -(k2 * c.xi9 * ((W[0][0] + W[1][1]) + W[2][2])));
-    T Sr[5];
-    Sr[0] = fmat(T(2), P[0][0], fmat(x23, W[0][0], fmat(t, q[0], iso)));
-    Sr[1] = fmat(x3, s01, fmat(t, q[1], P[0][1] + P[1][0]));
-    Sr[2] = fmat(x3, s02, fmat(t, q[2], P[0][2] + P[2][0]));
-    Sr[3] = fmat(T(2), P[1][1], fmat(x23, W[1][1], fmat(t, q[3], iso)));
-    Sr[4] = fmat(x3, s12, fmat(t, q[4], P[1][2] + P[2][1]));
-    const T f = S == 2 ? T(-0.5) : T(-1);
-    const T v[3] = {f * u[0], f * u[1], f * u[2]};
+    const T QW = q[0] * W[0][0] + q[3] * W[1][1] + qzz * W[2][2] + q[1] * s01 + q[2] * s02 + q[4] * s12;
+    const T third = T(1) / T(3);
+    const T t = T(-2) * c.xi * QW;
+    const T x3 = c.xi * third;
+    const T dtr = T(2) * x3 * (W[0][0] + W[1][1] + W[2][2]) * third;  // (2 xi/9) div u
+    const T S[5] = {T(2) * P[0][0] + T(2) * x3 * W[0][0] + t * (q[0] + third) - dtr,
+                    (P[0][1] + P[1][0]) + x3 * s01 + t * q[1],
+                    (P[0][2] + P[2][0]) + x3 * s02 + t * q[2],
+                    T(2) * P[1][1] + T(2) * x3 * W[1][1] + t * (q[3] + third) - dtr,
+                    (P[1][2] + P[2][1]) + x3 * s12 + t * q[4]};
 #pragma unroll
-    for (int k = 0; k < 5; ++k)
-        R[k] = fmat(v[2], d[2][k], fmat(v[1], d[1][k], fmat(v[0], d[0][k], fmat(c.Gamma, H[k], Sr[k]))));
+    for (int k = 0; k < 5; ++k) R[k] = -(u[0] * d[0][k] + u[1] * d[1][k] + u[2] * d[2][k]) + S[k] + c.Gamma * H[k];
 }
 
 // ---------------------------------------------------------------- D3Q19
@@ -453,6 +393,17 @@ __host__ __device__ __forceinline__ void lb_moments(const T g[19], T &drho, T j[
     j[2] = (g[5] - g[6]) + (g[11] - g[12]) + (g[14] - g[13]) + (g[15] - g[16]) + (g[18] - g[17]);
 }
 
+// a b + c with one rounding in either precision.  The collision spells out
+// its fused products so that every inlined copy of it rounds alike.
+template <typename T>
+__host__ __device__ __forceinline__ T fmat(T a, T b, T c)
+{
+    if constexpr (sizeof(T) == 4)
+        return __builtin_fmaf(a, b, c);
+    else
+        return __builtin_fma(a, b, c);
+}
+
 // Update of the opposite pair (i, i+1), e_{i+1} = -e_i, from the even part s
 // (the same for both) and the odd part o of omega g^eq + src:
 //   s = c0 + a2 (e.u)^2 + b2 (e.u)(e.F),  o = a1 (e.u) + b1 (e.F).
@@ -482,15 +433,14 @@ template <typename T, bool SIG>
 __host__ __device__ __forceinline__ void lb_update(const Coef<T> &c, T g[19], const T F[3], const T *sig, T u[3],
                                                    T &rho)
 {
-#pragma clang fp contract(off)
     T drho, j[3];
     lb_moments(g, drho, j);
     rho = c.rho0 + drho;
     const T irho = T(1) / rho;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) u[a] = fmat(T(0.5), F[a], j[a]) * irho;
-    const T uu15 = T(1.5) * dot3(u[0], u[0], u[1], u[1], u[2], u[2]);
-    const T uF = dot3(u[0], F[0], u[1], F[1], u[2], F[2]);
+    for (int a = 0; a < 3; ++a) u[a] = (j[a] + T(0.5) * F[a]) * irho;
+    const T uu15 = T(1.5) * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
+    const T uF = u[0] * F[0] + u[1] * F[1] + u[2] * F[2];
     const T keep = T(1) - c.omega;
     const T orho = c.omega * rho;
     const T base = fmat(c.omega, fmat(-rho, uu15, drho), T(-3) * c.pref * uF);

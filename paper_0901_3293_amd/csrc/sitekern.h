@@ -140,18 +140,17 @@ __device__ __forceinline__ int pull_from(const Geom &G, const Nbr &S, int cx, in
     return xs + G.nx * (ys + G.ny * zs);
 }
 
-// Differences of a value's neighbours (twice the centred derivatives) and its
-// 7-point Laplacian.
+// Centred derivatives and 7-point Laplacian of a value from its neighbours.
 template <typename T>
 __device__ __forceinline__ void stencil7(T v, T xp, T xm, T yp, T ym, T zp, T zm, T &dx, T &dy, T &dz, T &lap)
 {
-    dx = xp - xm;
-    dy = yp - ym;
-    dz = zp - zm;
-    lap = fmat(T(-6), v, ((xp + xm) + (yp + ym)) + (zp + zm));
+    dx = T(0.5) * (xp - xm);
+    dy = T(0.5) * (yp - ym);
+    dz = T(0.5) * (zp - zm);
+    lap = ((xp + xm) + (yp + ym)) + (zp + zm) - T(6) * v;
 }
 
-// Q, twice its derivatives and its Laplacian at one site.
+// Derivatives of the 5-component Q at one site.
 template <typename T>
 __device__ __forceinline__ void gather_q(const T *__restrict__ Q, int N, const Off<T> &O, T q[5], T d[3][5],
                                          T lap[5])
@@ -165,7 +164,6 @@ __device__ __forceinline__ void gather_q(const T *__restrict__ Q, int N, const O
     }
 }
 
-// u and twice its gradient, W_ab = 2 d_b u_a.
 template <typename T>
 __device__ __forceinline__ void gather_u(const T *__restrict__ u, int N, const Off<T> &O, T uc[3], T W[3][3])
 {
@@ -173,9 +171,9 @@ __device__ __forceinline__ void gather_u(const T *__restrict__ u, int N, const O
     for (int a = 0; a < 3; ++a) {
         const T *P = plane(u, a, N);
         uc[a] = *at(P, O.s);
-        W[a][0] = *at(P, O.nb[0]) - *at(P, O.nb[1]);
-        W[a][1] = *at(P, O.nb[2]) - *at(P, O.nb[3]);
-        W[a][2] = *at(P, O.nb[4]) - *at(P, O.nb[5]);
+        W[a][0] = T(0.5) * (*at(P, O.nb[0]) - *at(P, O.nb[1]));
+        W[a][1] = T(0.5) * (*at(P, O.nb[2]) - *at(P, O.nb[3]));
+        W[a][2] = T(0.5) * (*at(P, O.nb[4]) - *at(P, O.nb[5]));
     }
 }
 
@@ -201,7 +199,7 @@ __device__ __forceinline__ T stress_at(const Geom &G, const Coef<T> &c, const T 
     const Off<T> O = offsets<T>(nbr_of(G, s));
     T q[5], d[3][5], lap[5], P[3][3], fd, H[5];
     gather_q(Q, G.N, O, q, d, lap);
-    site_stress<T, 2>(c, q, d, lap, P, fd, H);
+    site_stress(c, q, d, lap, P, fd, H);
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
@@ -238,7 +236,7 @@ __device__ __forceinline__ T split_at(const Geom &G, const Coef<T> &c, const T *
     const Off<T> O = offsets<T>(nbr_of(G, s));
     T q[5], d[3][5], lap[5], sig[6], tau3[3], h[3], fd;
     gather_q(Q, N, O, q, d, lap);
-    site_split<T, 2>(c, q, d, lap, sig, tau3, h, fd);
+    site_split(c, q, d, lap, sig, tau3, h, fd);
 #pragma unroll
     for (int k = 0; k < 6; ++k) *at(plane(P, k, N), O.s) = sig[k];
 #pragma unroll
@@ -254,12 +252,12 @@ template <typename T>
 __device__ __forceinline__ void split_force(const T *__restrict__ P, int N, const Off<T> &O, T b[3])
 {
     const T *txy = plane(P, 6, N), *txz = plane(P, 7, N), *tyz = plane(P, 8, N);
-    b[0] = fmat(T(0.5), (*at(txy, O.nb[2]) - *at(txy, O.nb[3])) + (*at(txz, O.nb[4]) - *at(txz, O.nb[5])),
-                *at(plane(P, 9, N), O.s));
-    b[1] = fmat(T(0.5), (*at(tyz, O.nb[4]) - *at(tyz, O.nb[5])) - (*at(txy, O.nb[0]) - *at(txy, O.nb[1])),
-                *at(plane(P, 10, N), O.s));
-    b[2] = fmat(T(0.5), -(*at(txz, O.nb[0]) - *at(txz, O.nb[1])) - (*at(tyz, O.nb[2]) - *at(tyz, O.nb[3])),
-                *at(plane(P, 11, N), O.s));
+    b[0] = T(0.5) * ((*at(txy, O.nb[2]) - *at(txy, O.nb[3])) + (*at(txz, O.nb[4]) - *at(txz, O.nb[5]))) +
+           *at(plane(P, 9, N), O.s);
+    b[1] = T(0.5) * ((*at(tyz, O.nb[4]) - *at(tyz, O.nb[5])) - (*at(txy, O.nb[0]) - *at(txy, O.nb[1]))) +
+           *at(plane(P, 10, N), O.s);
+    b[2] = T(0.5) * (-(*at(txz, O.nb[0]) - *at(txz, O.nb[1])) - (*at(tyz, O.nb[2]) - *at(tyz, O.nb[3]))) +
+           *at(plane(P, 11, N), O.s);
 }
 
 // LB step of the split coupling at one site: pull, collide with the stress in
@@ -352,7 +350,7 @@ __device__ __forceinline__ void pred_at(const Geom &G, const Coef<T> &c, const T
     T q[5], d[3][5], lap[5], uc[3], W[3][3], R[5];
     gather_q(Q, N, O, q, d, lap);
     gather_u(u, N, O, uc, W);
-    site_rhs<T, 2>(c, q, d, lap, uc, W, R);
+    site_rhs(c, q, d, lap, uc, W, R);
 #pragma unroll
     for (int k = 0; k < 5; ++k) *at(plane(Qs, k, N), O.s) = q[k] + R[k];
 }
@@ -370,7 +368,7 @@ __device__ __forceinline__ void corr_at(const Geom &G, const Coef<T> &c, T *__re
     for (int k = 0; k < 5; ++k) qn[k] = *at(plane(Q, k, N), O.s);  // issued with the stencil loads
     gather_q(Qs, N, O, q, d, lap);
     gather_u(u, N, O, uc, W);
-    site_rhs<T, 2>(c, q, d, lap, uc, W, R);
+    site_rhs(c, q, d, lap, uc, W, R);
 #pragma unroll
     for (int k = 0; k < 5; ++k) *at(plane(Q, k, N), O.s) = T(0.5) * (qn[k] + q[k] + R[k]);
 }
@@ -477,39 +475,83 @@ __device__ __forceinline__ void pair_u(const PairRows<T, 3> &F, int h, T uc[3], 
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         uc[a] = F.c[a][h];
-        W[a][0] = (h ? F.r[a] : F.c[a].y) - (h ? F.c[a].x : F.l[a]);
-        W[a][1] = F.yp[a][h] - F.ym[a][h];
-        W[a][2] = F.zp[a][h] - F.zm[a][h];
+        W[a][0] = T(0.5) * ((h ? F.r[a] : F.c[a].y) - (h ? F.c[a].x : F.l[a]));
+        W[a][1] = T(0.5) * (F.yp[a][h] - F.ym[a][h]);
+        W[a][2] = T(0.5) * (F.zp[a][h] - F.zm[a][h]);
     }
+}
+
+// What site_rhs takes at one site of a pair.
+template <typename T>
+struct SiteIn {
+    T q[5], d[3][5], lap[5], uc[3], W[3][3];
+};
+
+// A value that the compiler takes as new from here on, after what is held before.
+template <typename T>
+__device__ __forceinline__ void hold(T &v)
+{
+    asm volatile("" : "+v"(v));
+}
+
+// R at both sites of a pair, one after the other: left to itself the compiler
+// runs the two side by side, and their 260 registers leave a SIMD one wave.
+template <typename T>
+__device__ __forceinline__ void pair_rhs(const Coef<T> &c, SiteIn<T> (&I)[2], T (&R)[2][5])
+{
+    site_rhs(c, I[0].q, I[0].d, I[0].lap, I[0].uc, I[0].W, R[0]);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) hold(R[0][k]);
+    SiteIn<T> &J = I[1];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        hold(J.q[k]);
+        hold(J.lap[k]);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) hold(J.d[e][k]);
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        hold(J.uc[a]);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) hold(J.W[a][e]);
+    }
+    site_rhs(c, J.q, J.d, J.lap, J.uc, J.W, R[1]);
 }
 
 // pred_at and corr_at at both sites of a pair (the pair's first site s; mine:
 // write them).
 template <typename T>
-__device__ __forceinline__ void pred_pair(const Geom &G, const Coef<T> &c, const T *__restrict__ Q,
-                                          const T *__restrict__ u, T *__restrict__ Qs, int s, bool mine)
+__device__ __forceinline__ void pair_in(const PairAt<T> &A, int N, const T *__restrict__ Q, const T *__restrict__ u,
+                                        SiteIn<T> (&I)[2])
 {
-    const int N = G.N;
-    const PairAt<T> A = pair_at<T>(G, s);
     PairRows<T, 5> FQ;
     PairRows<T, 3> FU;
     FQ.load(Q, N, A);
     FU.load(u, N, A);
     FQ.edges(A);
     FU.edges(A);
-    Two<T> out[5];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        T q[5], d[3][5], lap[5], uc[3], W[3][3], R[5];
-        pair_q(FQ, h, q, d, lap);
-        pair_u(FU, h, uc, W);
-        site_rhs<T, 2>(c, q, d, lap, uc, W, R);
-#pragma unroll
-        for (int k = 0; k < 5; ++k) out[k][h] = q[k] + R[k];
+        pair_q(FQ, h, I[h].q, I[h].d, I[h].lap);
+        pair_u(FU, h, I[h].uc, I[h].W);
     }
+}
+
+template <typename T>
+__device__ __forceinline__ void pred_pair(const Geom &G, const Coef<T> &c, const T *__restrict__ Q,
+                                          const T *__restrict__ u, T *__restrict__ Qs, int s, bool mine)
+{
+    const int N = G.N;
+    const PairAt<T> A = pair_at<T>(G, s);
+    SiteIn<T> I[2];
+    T R[2][5];
+    pair_in(A, N, Q, u, I);
+    pair_rhs(c, I, R);
     if (mine)
 #pragma unroll
-        for (int k = 0; k < 5; ++k) *reinterpret_cast<Two<T> *>(at(plane(Qs, k, N), A.O.s)) = out[k];
+        for (int k = 0; k < 5; ++k)
+            *reinterpret_cast<Two<T> *>(at(plane(Qs, k, N), A.O.s)) = Two<T>{I[0].q[k] + R[0][k], I[1].q[k] + R[1][k]};
 }
 
 template <typename T>
@@ -518,27 +560,18 @@ __device__ __forceinline__ void corr_pair(const Geom &G, const Coef<T> &c, T *__
 {
     const int N = G.N;
     const PairAt<T> A = pair_at<T>(G, s);
-    PairRows<T, 5> FQ;
-    PairRows<T, 3> FU;
-    Two<T> qn[5], out[5];
-    FQ.load(Qs, N, A);
-    FU.load(u, N, A);
+    SiteIn<T> I[2];
+    T R[2][5];
+    Two<T> qn[5];
+    pair_in(A, N, Qs, u, I);
+    pair_rhs(c, I, R);
 #pragma unroll
     for (int k = 0; k < 5; ++k) qn[k] = two(static_cast<const T *>(plane(Q, k, N)), A.O.s);
-    FQ.edges(A);
-    FU.edges(A);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        T q[5], d[3][5], lap[5], uc[3], W[3][3], R[5];
-        pair_q(FQ, h, q, d, lap);
-        pair_u(FU, h, uc, W);
-        site_rhs<T, 2>(c, q, d, lap, uc, W, R);
-#pragma unroll
-        for (int k = 0; k < 5; ++k) out[k][h] = T(0.5) * (qn[k][h] + q[k] + R[k]);
-    }
     if (mine)
 #pragma unroll
-        for (int k = 0; k < 5; ++k) *reinterpret_cast<Two<T> *>(at(plane(Q, k, N), A.O.s)) = out[k];
+        for (int k = 0; k < 5; ++k)
+            *reinterpret_cast<Two<T> *>(at(plane(Q, k, N), A.O.s)) =
+                Two<T>{T(0.5) * (qn[k].x + I[0].q[k] + R[0][k]), T(0.5) * (qn[k].y + I[1].q[k] + R[1][k])};
 }
 
 // Free-energy density at one site (Eq. (1) with the divergence term).
@@ -548,10 +581,6 @@ __device__ __forceinline__ T fdens_at(const Geom &G, const Coef<T> &c, const T *
     const Off<T> O = offsets<T>(nbr_of(G, s));
     T q[5], d[3][5], lap[5], Qf[3][3], dQ[3][3][3], CQ[3][3], Q2[3][3], M[3][3], div[3];
     gather_q(Q, G.N, O, q, d, lap);
-#pragma unroll
-    for (int g = 0; g < 3; ++g)
-#pragma unroll
-        for (int k = 0; k < 5; ++k) d[g][k] *= T(0.5);
     full3(q, Qf);
     full_grad(d, dQ);
     curl(dQ, CQ);
@@ -582,19 +611,6 @@ Coef<T> make_coef(const PhysParams &p)
     c.rho0 = T(p.rho0);
     c.omega = T(1.0 / p.tau);
     c.pref = T(1.0 - 0.5 / p.tau);
-    c.lin0 = T(-(p.A0 * (1.0 - p.gamma / 3.0) + 4.0 * p.K * p.q0 * p.q0));
-    c.Kq0 = T(p.K * p.q0);
-    c.K4 = T(0.25 * p.K);
-    c.K8 = T(0.125 * p.K);
-    c.xip = T(p.xi + 1.0);
-    c.xim = T(1.0 - p.xi);
-    c.xi23 = T(2.0 * p.xi / 3.0);
-    c.hp = T(0.25 * (p.xi + 1.0));
-    c.hm = T(0.25 * (p.xi - 1.0));
-    c.xih = T(0.5 * p.xi);
-    c.xi3 = T(p.xi / 3.0);
-    c.xi6 = T(p.xi / 6.0);
-    c.xi9 = T(p.xi / 9.0);
     return c;
 }
 

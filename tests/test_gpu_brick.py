@@ -1,8 +1,10 @@
 """The per-site schedule on small lattices, whose sweeps run in pairs over
 bricks of 16 x 4 x 2 sites, against the same schedule on a lattice large enough
 for the single sweeps: a periodic cell repeated along each axis gives the
-cell's step at every site, so the two are held bitwise equal (the arithmetic
-per site is the same).  Cells at the edges of the bricks: smaller than a brick,
+cell's step at every site.  The arithmetic per site is the same up to the
+products that the compiler fuses: a site's update sums some hundred rounded
+terms no larger than the field, so after three steps the two agree to 300
+roundings of the largest value.  Cells at the edges of the bricks: smaller than a brick,
 whole bricks, one site past them, and on either side of the 256 bricks (a CU
 each) that still go in pairs; odd and even numbers of steps."""
 import numpy as np
@@ -21,6 +23,7 @@ CELLS = [(4, 4, 4), (5, 9, 7), (16, 8, 6), (17, 4, 5), (32, 32, 32), (33, 32, 32
 def test_brick_step_matches_the_single_sweeps(prec, coupling):
     from paper_0901_3293_amd import hlb
 
+    eps = 2.0**-24 if prec == "fp32" else 2.0**-53
     for cell in CELLS:
         say("case: brick step", cell, prec, coupling)
         nx, ny, nz = cell
@@ -40,4 +43,4 @@ def test_brick_step_matches_the_single_sweeps(prec, coupling):
             s.close()
         for name, a, b in zip(("Q", "u", "rho"), *out):
             whole = np.tile(a, (1,) * (a.ndim - 3) + (rep[2], rep[1], rep[0]))
-            assert np.isfinite(a).all() and np.array_equal(whole, b), (cell, name)
+            assert np.isfinite(a).all() and np.abs(whole - b).max() <= 300 * eps * np.abs(a).max(), (cell, name)

@@ -1,10 +1,11 @@
-"""The tiled sweeps against the per-site ones at the edges of the tiles: both
-evaluate a site with the same operations in the same order, so a step by either
-schedule gives the same values bit for bit.  Lattices smaller than a tile, whole
-tiles, one site past them and one short, and z-chunks of one plane, of a
-remainder and of the whole depth; also lattices on either side of the size up to
-which the per-site sweeps go by blocks of one wave, and rows of one, several and
-many pairs of sites (even lengths, FP64)."""
+"""The tiled sweeps against the per-site ones at the edges of the tiles.  Both
+evaluate a site with the same operations up to the products that the compiler
+fuses: a site's update sums some hundred rounded terms no larger than the field,
+so after three steps they agree to 300 roundings of the largest value.  Lattices
+smaller than a tile, whole tiles, one site past them and one short, and z-chunks
+of one plane, of a remainder and of the whole depth; also lattices on either side
+of the size up to which the per-site sweeps go by blocks of one wave, and rows of
+one, several and many pairs of sites (even lengths, FP64)."""
 import numpy as np
 import pytest
 
@@ -20,11 +21,12 @@ SHAPES = [(4, 4, 4), (6, 5, 4), (130, 9, 6), (16, 12, 5), (17, 13, 9), (31, 11, 
 
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
 @pytest.mark.parametrize("coupling", ["force", "split", "off"])
-def test_tiled_steps_equal_the_per_site_steps(prec, coupling):
+def test_tiled_steps_match_the_per_site_steps(prec, coupling):
     from paper_0901_3293_amd import hlb
 
     p = I.reduced(0.8, -0.3, 0.25, flow=coupling != "off")
     p.coupling = "split" if coupling == "split" else "force"
+    eps = 2.0**-24 if prec == "fp32" else 2.0**-53
     for shape in SHAPES:
         Q = 0.4 * I.smooth_field(shape, 0.5, seed=3) + I.noise(shape, 1e-2, 4)
         out = []
@@ -39,4 +41,4 @@ def test_tiled_steps_equal_the_per_site_steps(prec, coupling):
             s.close()
         for other in out[1:]:
             for name, a, b in zip(("Q", "u", "rho"), out[0], other):
-                assert np.isfinite(a).all() and np.array_equal(a, b), (shape, name)
+                assert np.isfinite(a).all() and np.abs(a - b).max() <= 300 * eps * np.abs(a).max(), (shape, name)
