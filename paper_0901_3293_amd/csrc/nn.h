@@ -36,10 +36,19 @@ hipError_t conv(const Grid3 &g, int cip, int cop, int mode, const unsigned short
 // of scratch.
 hipError_t wgrad(const Grid3 &g, int cip, int cop, const unsigned short *X, const unsigned short *dZ, float *part,
                  int ci, int co, float *grad, hipStream_t st);
-// Fragment-ordered weights of one layer: Wf for the forward convolution
-// (cip -> cop), Wt for the backward-data convolution (cop -> cip).
-hipError_t wprep(const float *W, int ci, int co, int cip, int cop, unsigned short *Wf, unsigned short *Wt,
-                 hipStream_t st);
+// Fragment-ordered weights F of layers with CI -> CO channels, W as stored: for
+// the forward convolution (transposed = 0; cin, cout the padded CI, CO) or the
+// backward-data convolution (1; cin, cout the padded CO, CI).
+struct WeightArrays {
+    static constexpr int MOST = 8;
+    struct {
+        const float *W;
+        unsigned short *F;
+        int CI, CO, cin, cout, transposed;
+    } of[MOST];
+    int n;
+};
+hipError_t wprep(const WeightArrays &a, hipStream_t st);
 hipError_t pack(int N, const float *x, const float *norm, unsigned short *A0, hipStream_t st);
 hipError_t pack_state(bool fp32, int N, const void *Q, const void *u, const float *d1, const float *s2,
                       const float *norm, unsigned short *A0, hipStream_t st);

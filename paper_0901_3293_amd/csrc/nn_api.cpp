@@ -122,9 +122,15 @@ int nerr(hlbnn *n, int code, const char *fmt, ...)
 
 int prep_weights(hlbnn *n)
 {
-    for (int l = 0; l < NL; ++l)
-        N_TRY(n, hlb::nn::wprep(n->params + layer_offset(l), CI[l], CO[l], CIP[l], COP[l], n->Wf[l], n->Wt[l],
-                                n->stream));
+    hlb::nn::WeightArrays a;
+    static_assert(2 * NL <= hlb::nn::WeightArrays::MOST, "one launch");
+    a.n = 2 * NL;
+    for (int l = 0; l < NL; ++l) {
+        const float *W = n->params + layer_offset(l);
+        a.of[2 * l] = {W, n->Wf[l], CI[l], CO[l], CIP[l], COP[l], 0};
+        a.of[2 * l + 1] = {W, n->Wt[l], CI[l], CO[l], COP[l], CIP[l], 1};
+    }
+    N_TRY(n, hlb::nn::wprep(a, n->stream));
     return HLB_OK;
 }
 
