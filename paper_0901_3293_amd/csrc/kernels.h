@@ -87,7 +87,8 @@ struct Device {
 size_t partial_doubles(int nx, int ny, int nz);
 
 // Kernel kinds of one step, for per-kernel event timing (the per-site
-// schedule's paired sweeps on small lattices count as K_QLB and K_QUPDATE).
+// schedule's paired sweeps on small lattices count as K_QLB and K_QUPDATE, the
+// fused D3Q15 passes as K_PC2).
 enum KernelKind {
     K_STRESS = 0, K_LB = 1, K_QPRED = 2, K_QCORR = 3,  // per-site schedule
     K_QFORCE = 4, K_LBF = 5, K_QUPDATE = 6,            // tiled schedule

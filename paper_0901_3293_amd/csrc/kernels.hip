@@ -982,6 +982,99 @@ __global__ __launch_bounds__(B) void k_pc2(Geom G, Coef<T> c, const T *__restric
     if (s < G.N) pc2_at<T, SPLIT, true>(G, c, g, P, Pi, bsave, gout, s);
 }
 
+// Both passes in one sweep: the block marches along z as the tile kernels do,
+// with one point of the evaluation plane (tile and ring, corners included) per
+// thread.  Per plane p: the first pass at the own point, f and P = f + C into
+// LDS for the twelve velocities that move in the plane (rest and z stay in the
+// column's registers); then the tile threads pull: velocities with e_z = -1
+// arriving in plane p-1, which completes f* there and lets the second pass
+// write the site, those with e_z = 0 for plane p, and e_z = 1 for plane p+1.
+// Pulled pairs are carried as f* and (f + P)/2.  P and the saved force never
+// go to HBM: 45 values per site instead of 102.  One LDS buffer and two barriers
+// a plane; 99 registers in FP32, about 200 in FP64, two blocks a CU.
+// Bound by the path from the cache (36 loads a point and plane) and by latency:
+// 114 us at 128^3 in FP32, where k_pc1 and k_pc2 take 132.  A step in us with the
+// two passes and with this: 128^3 219 and 199 (64 x 5 tiles 204, 16 x 12 245,
+// 32 x 4 220), in FP64 524 and 472 (16 x 12 485); 96^3 96 and 90, 205 and 197.
+template <typename T, bool SPLIT>
+__global__ __launch_bounds__(PassTile<T>::NB) void k_pc(Geom G, Coef<T> c, TileGrid tg, const T *__restrict__ g,
+                                                         const T *__restrict__ Pi, T *__restrict__ gout,
+                                                         T *__restrict__ u)
+{
+    using Shape = PassTile<T>;
+    constexpr int PN = Shape::PN, PX = Shape::PX;
+    __shared__ T S[2][12][PN];  // f and P
+    const Block B = block_of<Shape>(G, tg);
+    if (!B.ok) return;
+    const int N = G.N, sxy = G.nx * G.ny;
+    // the threads past the last point repeat it (same values to the same places)
+    int pc, rc;
+    TileMap<Shape>::point(min(int(threadIdx.x), PN - 1), pc, rc);
+    const int x = wrapi(B.x0 + pc % PX - 1, G.nx), y = wrapi(B.y0 + pc / PX - 1, G.ny);
+    const bool mine = int(threadIdx.x) < Shape::NT && B.x0 + pc % PX - 1 < G.nx && B.y0 + pc / PX - 1 < G.ny;
+    // f* and (f + P)/2 arriving at the own site: in plane p-1 (e_z = 1 and 0) and plane p (e_z = 1)
+    T as[15], ao[15], ns[15], no[15], b1[3], sig1[6];
+    for (int p = B.z0 - 1; p <= B.z1; ++p) {
+        const int z = wrapi(p, G.nz);
+        const Off<T> O = offsets<T>(nbr_at(G, x + G.nx * y + z * sxy, x, y, z));
+        T f[15], C[15], b[3], sig[6], uu[3], rho;
+#pragma unroll
+        for (int i = 0; i < 15; ++i) f[i] = *at(plane(g, i, N), O.s);
+        force15<T, SPLIT>(Pi, N, O, b, sig);
+        lb15_collide<T, SPLIT>(c, f, sig, b, C, uu, rho);
+#pragma unroll
+        for (int i = 0; i < 15; ++i) {
+            C[i] += f[i];
+            if (DX15[i] || DY15[i]) {
+                const int k = i < 5 ? i - 1 : i - 3;
+                S[0][k][pc] = f[i];
+                S[1][k][pc] = C[i];
+            }
+        }
+        if (mine && p >= B.z0 && p < B.z1)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) *at(plane(u, a, N), O.s) = uu[a];
+        __syncthreads();
+        if (mine) {
+            auto pull = [&](int i, T &fs, T &fo) __attribute__((always_inline)) {
+                T f0 = f[i];
+                fs = C[i];
+                if (DX15[i] || DY15[i]) {
+                    const int k = i < 5 ? i - 1 : i - 3, o = pc - DX15[i] - PX * DY15[i];
+                    f0 = S[0][k][o];
+                    fs = S[1][k][o];
+                }
+                fo = T(0.5) * (f0 + fs);
+            };
+            if (p > B.z0) {
+#pragma unroll
+                for (int i = 0; i < 15; ++i)
+                    if (DZ15[i] < 0) pull(i, as[i], ao[i]);
+                T D[15], u2[3], rho2;
+                lb15_collide<T, SPLIT>(c, as, sig1, b1, D, u2, rho2);
+                const unsigned o = unsigned(x + G.nx * y + (p - 1) * sxy) * unsigned(sizeof(T));
+#pragma unroll
+                for (int i = 0; i < 15; ++i) pop_store<true>(plane(gout, i, N), o, fmat(T(0.5), D[i], ao[i]));
+            }
+#pragma unroll
+            for (int i = 0; i < 15; ++i) {
+                if (DZ15[i] == 0) pull(i, as[i], ao[i]);
+                if (DZ15[i] > 0) {
+                    as[i] = ns[i];
+                    ao[i] = no[i];
+                    pull(i, ns[i], no[i]);
+                }
+            }
+#pragma unroll
+            for (int a = 0; a < 3; ++a) b1[a] = b[a];
+            if constexpr (SPLIT)
+#pragma unroll
+                for (int k = 0; k < 6; ++k) sig1[k] = sig[k];
+        }
+        __syncthreads();
+    }
+}
+
 // D3Q15 state from (rho, u): g_i(x) = f_i^eq(rho(x), u(x)) - A_s(rho0) in
 // place, without stress or force terms; Q converted to the storage type.
 template <typename T>
@@ -995,7 +1088,7 @@ __global__ __launch_bounds__(BLK) void k_init15(Geom G, Coef<T> c, const double 
     const T uu3[3] = {T(u_in[s]), T(u_in[N + s]), T(u_in[2 * N + s])};
     const T uu = uu3[0] * uu3[0] + uu3[1] * uu3[1] + uu3[2] * uu3[2];
 #pragma unroll
-    for (int i = 0; i < 15; ++i) g[i * N + s] = lb15_eq(i, c.rho0, T(rho_in[s]), uu3, uu, static_cast<const T *>(nullptr));
+    for (int i = 0; i < 15; ++i) g[i * N + s] = lb15_eq(i, c.rho0, T(rho_in[s]), uu3, uu);
 #pragma unroll
     for (int k = 0; k < 5; ++k) Q[k * N + s] = T(Q_in[k * N + s]);
 }
@@ -1476,6 +1569,21 @@ void with_block(int N, int cus, F &&f)
     })
 #define SWEEP(KERNEL, ...) SWEEP_OF(G.N, KERNEL, __VA_ARGS__)
 
+// z-chunk of the fused D3Q15 passes, the one that gives a CU two blocks (all that
+// are resident) at once; 0 where the two sweeps are the better: a chunk under six
+// planes repeats too many of them (64^3, four planes: 36 us a step and 33 in FP32,
+// but 68 and 74 in FP64; 48^3 26 and 28, 37 and 45), and so do tiles that hang
+// over the lattice by more than a quarter.
+template <typename T>
+int pass_chunk(const Geom &G, int cus)
+{
+    using S = PassTile<T>;
+    const long long cols = (long long)((G.nx + S::TX - 1) / S::TX) * ((G.ny + S::TY - 1) / S::TY);
+    if (4 * cols * S::NT > 5LL * G.nx * G.ny) return 0;
+    const int chunks = int(std::max(1LL, 2LL * cus / cols)), tz = (G.nz + chunks - 1) / chunks;
+    return tz >= 6 ? tz : 0;
+}
+
 template <typename T, bool SPLIT>
 hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *timer)
 {
@@ -1499,6 +1607,7 @@ hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *time
     const TileGrid tgq = tile_grid(G.nx, G.ny, G.nz, UpdateTile<T>::TX, UpdateTile<T>::TY, tile_tzq(D));
     const TileGrid tgw = tile_grid(G.nx, G.ny, G.nz, WideTile<T>::TX, WideTile<T>::TY, tile_tz(D));
     const bool wide = wide_tiles<T>(G.nx);
+    const int tzp = pc ? pass_chunk<T>(G, cus) : 0;
     const int tb = KernelTile<T>::NB;
     const bool pairs = sc == SCHED_SITES && small_lattice(G, cus);
     const int nbr = StepBrick::blocks(G), lbr = (nbr + 7) / 8 * 8;
@@ -1529,7 +1638,13 @@ hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *time
                 });
             } else {
                 e = mark(K_STRESS, [&] { SWEEP((k_stress<T, SPLIT, B>), G, c, Q, Pi, nullptr); });
-                if (pc) {
+                if (pc && tzp) {
+                    const TileGrid tp = tile_grid(G.nx, G.ny, G.nz, PassTile<T>::TX, PassTile<T>::TY, tzp);
+                    if (e == hipSuccess)
+                        e = mark(K_PC2, [&] {
+                            k_pc<T, SPLIT><<<tp.launch, PassTile<T>::NB, 0, D.stream>>>(G, c, tp, gin, Pi, gout, u);
+                        });
+                } else if (pc) {
                     T *P = static_cast<T *>(D.aux);
                     T *bsave = gout + 15 * size_t(G.N);  // planes 15..17 of the target buffer
                     if (e == hipSuccess)

@@ -502,64 +502,84 @@ constexpr int DX15[15] = {0, 1, -1, 0, 0, 0, 0, 1, -1, 1, -1, 1, -1, -1, 1};
 constexpr int DY15[15] = {0, 0, 0, 1, -1, 0, 0, 1, -1, 1, -1, -1, 1, 1, -1};
 constexpr int DZ15[15] = {0, 0, 0, 0, 0, 1, -1, 1, -1, -1, 1, 1, -1, 1, -1};
 
-// Equilibrium deviation of velocity i, the printed polynomial
-//   A_s + B_s u.e + C_s u^2 + D_s (u.e)^2 + E_s:e e
+// Equilibrium deviation of velocity i without stress, the printed polynomial
+//   A_s + B_s u.e + C_s u^2 + D_s (u.e)^2
 // with the printed coefficients at T = 1/3: A_1 = A_2 = rho/30,
 // A_0 = rho - 14 A_2; B = (rho/3, rho/24); C = (-2rho/3, -rho/12, -rho/24);
-// D = (rho/2, rho/16); E_2 = -(sig - tr(sig)/3 I)/16, E_1 = 8 E_2 (faces,
-// corners).  sig: upper triangle xx, xy, xz, yy, yz, zz (null: no stress).
+// D = (rho/2, rho/16).
 template <typename T>
-__host__ __device__ __forceinline__ T lb15_eq(int i, T rho0, T rho, const T u[3], T uu, const T *sig)
+__host__ __device__ __forceinline__ T lb15_eq(int i, T rho0, T rho, const T u[3], T uu)
 {
     const T ex = T(DX15[i]), ey = T(DY15[i]), ez = T(DZ15[i]);
     const T eu = ex * u[0] + ey * u[1] + ez * u[2];
     const T dr = rho - rho0;
-    T v;
-    if (i == 0) {
-        v = dr - T(14) * (dr / T(30)) - T(2) * rho / T(3) * uu;
-    } else if (i <= 6) {
-        v = dr / T(30) + rho / T(3) * eu - rho / T(12) * uu + rho / T(2) * eu * eu;
-    } else {
-        v = dr / T(30) + rho / T(24) * eu - rho / T(24) * uu + rho / T(16) * eu * eu;
-    }
-    if (sig && i > 0) {
-        const T tr3 = (sig[0] + sig[3] + sig[5]) / T(3);
-        const T see = (sig[0] - tr3) * ex * ex + (sig[3] - tr3) * ey * ey + (sig[5] - tr3) * ez * ez
-                    + T(2) * (sig[1] * ex * ey + sig[2] * ex * ez + sig[4] * ey * ez);
-        v -= (i <= 6 ? T(8) : T(1)) * see / T(16);
-    }
-    return v;
-}
-
-// Forcing term p_i = P_s b.e with P_1 = 1/3, P_2 = 1/24.
-template <typename T>
-__host__ __device__ __forceinline__ T lb15_force(int i, const T b[3])
-{
-    if (i == 0) return T(0);
-    const T eb = T(DX15[i]) * b[0] + T(DY15[i]) * b[1] + T(DZ15[i]) * b[2];
-    return (i <= 6 ? T(1) / T(3) : T(1) / T(24)) * eb;
+    if (i == 0) return dr - T(14) * (dr / T(30)) - T(2) * rho / T(3) * uu;
+    if (i <= 6) return dr / T(30) + rho / T(3) * eu - rho / T(12) * uu + rho / T(2) * eu * eu;
+    return dr / T(30) + rho / T(24) * eu - rho / T(24) * uu + rho / T(16) * eu * eu;
 }
 
 // Collision operator of Eq. (16) on D3Q15 at one site: local moments
-// (rho u = sum f e, Eq. (14)), C_i = -(g_i - g_i^eq)/tau + p_i.
-template <typename T>
-__host__ __device__ __forceinline__ void lb15_collide(const Coef<T> &c, const T g[15], const T *sig, const T b[3], T C[15],
-                                             T u[3], T &rho)
+// (rho u = sum f e, Eq. (14)), C_i = -(g_i - g_i^eq)/tau + p_i with the
+// equilibrium of lb15_eq, with SIG its stress term E_s:e e, E_2 =
+// -(sig - tr(sig)/3 I)/16, E_1 = 8 E_2 (sig: xx, xy, xz, yy, yz, zz), and the
+// forcing P_s b.e, P_1 = 1/3, P_2 = 1/24.
+// Evaluated per pair of opposite velocities (i, i+1): with d = rho - rho0,
+// m = omega rho/24 and, on the corners, tr(sig) dropping out of sig:ee,
+//   C_i = -omega g_i + even + odd,  C_{i+1} = -omega g_{i+1} + even - odd,
+//   faces:   even = omega (d/30 - see/2) - 2 m u^2 + 12 m (u.e)^2,  odd = 8 m u.e + b.e/3
+//   corners: even = omega (d/30 - see/16) - m u^2 + 3/2 m (u.e)^2,  odd = m u.e + b.e/24,
+// and omega (d - 14 d/30) - 16 m u^2 at rest, which keeps the mass whatever
+// the rounding of d/30 and m.
+template <typename T, bool SIG>
+__host__ __device__ __forceinline__ void lb15_collide(const Coef<T> &c, const T g[15], const T *sig, const T b[3],
+                                                      T C[15], T u[3], T &rho)
 {
-    T drho = T(0), j[3] = {T(0), T(0), T(0)};
+#pragma clang fp contract(off)
+    T o[7], drho = g[0];
 #pragma unroll
-    for (int i = 0; i < 15; ++i) {
-        drho += g[i];
-        j[0] += T(DX15[i]) * g[i];
-        j[1] += T(DY15[i]) * g[i];
-        j[2] += T(DZ15[i]) * g[i];
+    for (int k = 0; k < 7; ++k) {
+        drho += g[2 * k + 1] + g[2 * k + 2];
+        o[k] = g[2 * k + 1] - g[2 * k + 2];
     }
     rho = c.rho0 + drho;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) u[a] = j[a] / rho;
-    const T uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-#pragma unroll
-    for (int i = 0; i < 15; ++i) C[i] = -(g[i] - lb15_eq(i, c.rho0, rho, u, uu, sig)) * c.omega + lb15_force(i, b);
+    const T irho = T(1) / rho;
+    u[0] = (o[0] + ((o[3] + o[4]) + (o[5] - o[6]))) * irho;
+    u[1] = (o[1] + ((o[3] + o[4]) - (o[5] - o[6]))) * irho;
+    u[2] = (o[2] + ((o[3] - o[4]) + (o[5] + o[6]))) * irho;
+    const T uu = fmat(u[0], u[0], fmat(u[1], u[1], u[2] * u[2]));
+    const T w = c.omega;
+    const T m = (T(1) / T(24)) * (w * rho), muu = m * uu;
+    const T d30 = (T(1) / T(30)) * drho, wd30 = w * d30;
+    C[0] = fmat(-w, g[0], fmat(T(-16), muu, w * fmat(T(-14), d30, drho)));
+    const T cf = fmat(T(-2), muu, wd30), cc = wd30 - muu;
+    T cx = cf, cy = cf, cz = cf, c3 = cc, c4 = cc, c5 = cc, c6 = cc;
+    if constexpr (SIG) {
+        const T tr3 = (sig[0] + sig[3] + sig[5]) / T(3);
+        const T m1 = T(-0.5) * w, m2 = T(-0.125) * w;
+        cx = fmat(m1, sig[0] - tr3, cf);
+        cy = fmat(m1, sig[3] - tr3, cf);
+        cz = fmat(m1, sig[5] - tr3, cf);
+        const T p = sig[2] + sig[4], q = sig[2] - sig[4];
+        c3 = fmat(m2, sig[1] + p, cc);  // e along (1, 1, 1), (1, 1, -1), (1, -1, 1), (-1, 1, 1)
+        c4 = fmat(m2, sig[1] - p, cc);
+        c5 = fmat(m2, q - sig[1], cc);
+        c6 = fmat(-m2, sig[1] + q, cc);
+    }
+    auto pair = [&](int i, T c0, T a2, T a1, T b1, T eu, T eb) __attribute__((always_inline)) {
+        const T s = fmat(a2 * eu, eu, c0);
+        const T h = fmat(a1, eu, b1 * eb);
+        C[i] = fmat(-w, g[i], s + h);
+        C[i + 1] = fmat(-w, g[i + 1], s - h);
+    };
+    const T f2 = T(12) * m, f1 = T(8) * m, k2 = T(1.5) * m;
+    constexpr T b3 = T(1) / T(3), b24 = T(1) / T(24);
+    pair(1, cx, f2, f1, b3, u[0], b[0]);
+    pair(3, cy, f2, f1, b3, u[1], b[1]);
+    pair(5, cz, f2, f1, b3, u[2], b[2]);
+    pair(7, c3, k2, m, b24, (u[0] + u[1]) + u[2], (b[0] + b[1]) + b[2]);
+    pair(9, c4, k2, m, b24, (u[0] + u[1]) - u[2], (b[0] + b[1]) - b[2]);
+    pair(11, c5, k2, m, b24, (u[0] - u[1]) + u[2], (b[0] - b[1]) + b[2]);
+    pair(13, c6, k2, m, b24, u[2] - (u[0] - u[1]), b[2] - (b[0] - b[1]));
 }
 
 // Equilibrium deviation for initialisation.

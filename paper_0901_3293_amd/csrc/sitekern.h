@@ -281,6 +281,20 @@ __device__ __forceinline__ void lb_split_at(const Geom &G, const Coef<T> &c, con
     for (int a = 0; a < 3; ++a) *at(plane(u, a, N), O.s) = uu[a];
 }
 
+// Body force b = div Pi of the D3Q15 LB at one site, or SPLIT b = div tau + h
+// beside sigma^xi.
+template <typename T, bool SPLIT>
+__device__ __forceinline__ void force15(const T *__restrict__ Pi, int N, const Off<T> &O, T b[3], T sig[6])
+{
+    if constexpr (SPLIT) {
+        split_force(Pi, N, O, b);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) sig[k] = *at(plane(Pi, k, N), O.s);
+    } else {
+        divergence(Pi, N, O, b);
+    }
+}
+
 // D3Q15 predictor-corrector LB (Eq. (15)), first pass at one site x: the
 // collision C(x, {f}) of the local populations with the stress and body force
 // of this step (split: sigma^xi from the 12-plane layout and b = div tau + h;
@@ -297,14 +311,8 @@ __device__ __forceinline__ void pc1_at(const Geom &G, const Coef<T> &c, const T 
     T f[15], C[15], b[3], sig[6], uu[3], rho;
 #pragma unroll
     for (int i = 0; i < 15; ++i) f[i] = *at(plane(g, i, N), O.s);
-    if (SPLIT) {
-        split_force(Pi, N, O, b);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) sig[k] = *at(plane(Pi, k, N), O.s);
-    } else {
-        divergence(Pi, N, O, b);
-    }
-    lb15_collide(c, f, SPLIT ? sig : static_cast<const T *>(nullptr), b, C, uu, rho);
+    force15<T, SPLIT>(Pi, N, O, b, sig);
+    lb15_collide<T, SPLIT>(c, f, sig, b, C, uu, rho);
 #pragma unroll
     for (int i = 0; i < 15; ++i) pop_store<STREAM>(plane(P, i, N), O.s, f[i] + C[i]);
 #pragma unroll
@@ -335,9 +343,9 @@ __device__ __forceinline__ void pc2_at(const Geom &G, const Coef<T> &c, const T 
     if (SPLIT)
 #pragma unroll
         for (int k = 0; k < 6; ++k) sig[k] = *at(plane(Pi, k, N), O.s);
-    lb15_collide(c, fs, SPLIT ? sig : static_cast<const T *>(nullptr), b, C, uu, rho);
+    lb15_collide<T, SPLIT>(c, fs, sig, b, C, uu, rho);
 #pragma unroll
-    for (int i = 0; i < 15; ++i) pop_store<STREAM>(plane(gout, i, N), O.s, fo[i] + T(0.5) * C[i]);
+    for (int i = 0; i < 15; ++i) pop_store<STREAM>(plane(gout, i, N), O.s, fmat(T(0.5), C[i], fo[i]));
 }
 
 // Predictor Q* = Q + R(Q, u) at one site (Eqs. (2)-(4)).

@@ -68,6 +68,10 @@ inline bool wide_tiles(int nx)
     return 10 * ((nx + TX - 1) / TX * TX - nx) <= nx;
 }
 
+// The tile of the fused D3Q15 passes (measured at k_pc).
+template <typename T>
+using PassTile = typename std::conditional<sizeof(T) == 8, TileShape<32, 4>, TileShape<32, 8>>::type;
+
 // The tile of the Q update, which is bound by its instructions and not by
 // memory: blocks of four waves, one to each SIMD, of which four share a CU in
 // FP32 (two in FP64).  In FP32 at 192^3: 32 x 8 (six waves, two blocks) 222 us,

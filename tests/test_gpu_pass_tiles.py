@@ -1,0 +1,40 @@
+"""The fused D3Q15 passes, which lattices large enough for two blocks of them per CU
+take, against the two sweeps of a small lattice: a periodic cell repeated along each
+axis gives the cell's step at every site.  The cells put the edges of the tiles
+(32 x 8 sites, in FP64 32 x 4) and of the z-chunks at every offset, with whole
+tiles and with remainders.  A site's update sums some hundred rounded terms no
+larger than the field, so after three steps the two agree to 300 roundings of the
+largest value."""
+import numpy as np
+import pytest
+
+from paper_0901_3293_amd import inputs as I
+from tests.hlbtest import say
+
+pytestmark = pytest.mark.gpu
+
+CELLS = [((10, 7, 4), (16, 20, 10)), ((13, 9, 5), (12, 15, 8)), ((32, 8, 6), (5, 17, 7)), ((31, 11, 7), (5, 12, 6))]
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("coupling", ["force", "split"])
+def test_fused_passes_match_the_two_sweeps(prec, coupling):
+    from paper_0901_3293_amd import hlb
+
+    eps = 2.0**-24 if prec == "fp32" else 2.0**-53
+    p = I.reduced(0.8, -0.3, 0.25)
+    p.coupling, p.lb_model, p.tau = coupling, "d3q15", 5.0
+    for cell, rep in CELLS:
+        say("case: fused passes", cell, prec, coupling)
+        Q = 0.4 * I.smooth_field(cell, 0.5, seed=3) + I.noise(cell, 1e-2, 4)
+        out = []
+        for r in ((1, 1, 1), rep):
+            s = hlb.Solver(tuple(n * k for n, k in zip(cell, r)), prec, coupling=coupling, lb_model="d3q15")
+            s.set_params(p)
+            s.set_fields(np.tile(Q, (1, r[2], r[1], r[0])))
+            s.step(3)
+            out.append([np.asarray(f) for f in s.fields()])
+            s.close()
+        for name, a, b in zip(("Q", "u", "rho"), *out):
+            whole = np.tile(a, (1,) * (a.ndim - 3) + (rep[2], rep[1], rep[0]))
+            assert np.isfinite(a).all() and np.abs(whole - b).max() <= 300 * eps * np.abs(a).max(), (cell, name)
