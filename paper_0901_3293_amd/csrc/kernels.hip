@@ -412,11 +412,10 @@ __global__ __launch_bounds__(KernelTile<T>::NB) __attribute__((amdgpu_waves_per_
 // FP32: 111 registers, four waves per SIMD, two blocks per CU; FP64: about 200,
 // two waves per SIMD and two four-wave blocks.  The planes of Q go straight into
 // LDS (staged through registers: 127 and 231).
-// Bound by memory, 46 values per site: rows as long as a lattice row's share
-// of whole lines matter more than the ring.  Q update included, FP32 192^3: 32 x 8
-// tiles 448 us, 32 x 12 426, 64 x 5 416; 128^3 147 (157 through registers) and 146;
-// 96^3, where 64 does not divide the row, 80 (86) and 83.  FP64 128^3: 16 x 12
-// 277 us, 32 x 4 264.
+// Bound by memory, 46 values per site: on large lattices rows of whole lines
+// matter more than the ring (see WideTile).  Q update included, FP32 192^3: 32 x 8
+// tiles 457 us, 64 x 5 423 (515 with 32 x 8 tiles of both kernels staged through
+// registers); 96^3 80 (86 through registers).
 template <typename T, bool SPLIT, class Shape>
 __global__ __launch_bounds__(Shape::NB) void k_qlb(Geom G, Coef<T> c, TileGrid tg, const T *__restrict__ Q, const T *__restrict__ gin,
                                                       T *__restrict__ gout, T *__restrict__ u, bool dbg_nan)
@@ -1606,7 +1605,7 @@ hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *time
     const TileGrid tg = tile_grid(G.nx, G.ny, G.nz, KernelTile<T>::TX, KernelTile<T>::TY, tile_tz(D));
     const TileGrid tgq = tile_grid(G.nx, G.ny, G.nz, UpdateTile<T>::TX, UpdateTile<T>::TY, tile_tzq(D));
     const TileGrid tgw = tile_grid(G.nx, G.ny, G.nz, WideTile<T>::TX, WideTile<T>::TY, tile_tz(D));
-    const bool wide = wide_tiles<T>(G.nx);
+    const bool wide = wide_tiles<T>(G.nx, G.ny, G.nz, cus);
     const int tzp = pc ? pass_chunk<T>(G, cus) : 0;
     const int tb = KernelTile<T>::NB;
     const bool pairs = sc == SCHED_SITES && small_lattice(G, cus);

@@ -56,16 +56,19 @@ struct TileShape {
 template <typename T>
 using KernelTile = typename std::conditional<sizeof(T) == 8, TileShape<16, 12>, TileShape<32, 8>>::type;
 
-// The tile of the fused stress and LB on lattices whose rows it fills to a
+// The tile of the fused stress and LB on large lattices whose rows it fills to a
 // tenth: 256 bytes a row, which the populations gain more from than the ring,
-// 1.44 to 1.59 points a site instead of 1.31, costs (measured at k_qlb).
+// 1.44 to 1.59 points a site instead of 1.31, costs, once there are some 6000
+// sites a CU; with fewer its larger blocks do not fill the chip.  FP32 steps,
+// the narrow and the wide tile: 64^3 43 and 45 us, 128 x 64 x 64 52 and 55, 128^3
+// 142 and 139, 192^3 457 and 423, 256^3 1092 and 1035; FP64 128^3 277 and 264.
 template <typename T>
 using WideTile = typename std::conditional<sizeof(T) == 8, TileShape<32, 4>, TileShape<64, 5>>::type;
 template <typename T>
-inline bool wide_tiles(int nx)
+inline bool wide_tiles(int nx, int ny, int nz, int cus)
 {
     const int TX = WideTile<T>::TX;
-    return 10 * ((nx + TX - 1) / TX * TX - nx) <= nx;
+    return 10 * ((nx + TX - 1) / TX * TX - nx) <= nx && (long long)nx * ny * nz >= 6000LL * cus;
 }
 
 // The tile of the fused D3Q15 passes (measured at k_pc).

@@ -15,7 +15,8 @@ from tests.hlbtest import say
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(4, 4, 4), (6, 5, 4), (130, 9, 6), (16, 12, 5), (17, 13, 9), (31, 11, 8), (32, 24, 7), (33, 25, 6), (65, 37, 12),
-          (64, 11, 6), (60, 4, 5), (128, 16, 4),  # rows that fill the wide tiles of the fused stress and LB
+          (64, 11, 6), (60, 4, 5), (128, 16, 4),
+          (126, 129, 97),  # the wide tiles of the fused stress and LB, with remainders
           (47, 46, 45), (72, 70, 66)]  # per-site sweeps by blocks of one wave, and of four
 
 
