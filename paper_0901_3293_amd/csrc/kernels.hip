@@ -1504,6 +1504,15 @@ struct Marks {
 int tile_tz(const Device &D) { return D.tz > 0 ? D.tz : 16; }
 int tile_tzq(const Device &D) { return D.tzq > 0 ? D.tzq : tile_tz(D); }
 
+int device_cus()
+{
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return 0;
+    return cus;
+}
+
 // z-chunk for which the blocks of the tiled kernels fill the device's
 // resident block slots `rounds` times: a launch of whole rounds leaves no CU
 // idle at the end (0 if the tile columns alone exceed the slots).
@@ -1511,14 +1520,26 @@ template <typename T>
 int tz_fill_t(const Device &D, int rounds)
 {
     using S = KernelTile<T>;
-    int dev = 0, cus = 0, bq = 0, bf = 0, bl = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bq, k_qupdate<T>, UpdateTile<T>::NB, 0) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bf, k_qforce<T, false>, S::NB, 0) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bl, (k_qlb<T, false, KernelTile<T>>), S::NB, 0) != hipSuccess) return 0;
-    const long long slots = (long long)cus * std::max(1, std::min(bq, std::min(bf, bl))) * rounds;
-    const long long cols = (long long)((D.G.nx + S::TX - 1) / S::TX) * ((D.G.ny + S::TY - 1) / S::TY);
+    using W = WideTile<T>;
+    const Geom &G = D.G;
+    const int cus = device_cus();
+    if (cus < 1) return 0;
+    long long slots = (long long)cus * rounds, cols;
+    if (wide_tiles<T>(G.nx, G.ny, G.nz, cus)) {
+        // the fused kernel's tile: at 128^3 FP32 15 planes, 137 us a step where 16 take 138
+        int bw = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bw, (k_qlb<T, false, W>), W::NB, 0) != hipSuccess) return 0;
+        slots *= std::max(1, bw);
+        cols = (long long)((G.nx + W::TX - 1) / W::TX) * ((G.ny + W::TY - 1) / W::TY);
+    } else {
+        int bq = 0, bf = 0, bl = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bq, k_qupdate<T>, UpdateTile<T>::NB, 0) != hipSuccess)
+            return 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bf, k_qforce<T, false>, S::NB, 0) != hipSuccess) return 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bl, (k_qlb<T, false, S>), S::NB, 0) != hipSuccess) return 0;
+        slots *= std::max(1, std::min(bq, std::min(bf, bl)));
+        cols = (long long)((G.nx + S::TX - 1) / S::TX) * ((G.ny + S::TY - 1) / S::TY);
+    }
     const long long chunks = slots / cols;
     if (chunks < 1) return 0;
     return int((D.G.nz + chunks - 1) / chunks);
@@ -1533,15 +1554,6 @@ int tz_fill_t(const Device &D, int rounds)
 // 65.  The brick: larger ones (8 x 8 x 4, 16 x 8 x 4) evaluate fewer face points,
 // but leave CUs idle on the lattices in question.
 typedef Brick<16, 4, 2> StepBrick;
-
-int device_cus()
-{
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return 0;
-    return cus;
-}
 
 bool small_lattice(const Geom &G, int cus) { return StepBrick::blocks(G) <= cus; }
 
