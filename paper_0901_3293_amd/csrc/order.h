@@ -160,7 +160,8 @@ __host__ __device__ __forceinline__ void order_site(const double q[5], double &l
 // threshold - Q is positive definite, i.e. its leading minors are positive.  A
 // minor within 1e-12 of zero (on the scale of |threshold| + |Q|, a hundred times
 // its rounding and that of the eigenvalue) leaves it to order_site, so the two
-// always agree; so do NaN and infinities, which fail every comparison.
+// always agree; so do scales whose cubes underflow or overflow, NaN and
+// infinities (the last two fail every comparison).
 __host__ __device__ __forceinline__ bool order_below(const double q[5], double threshold)
 {
     const double zz = -q[0] - q[3];
@@ -170,8 +171,10 @@ __host__ __device__ __forceinline__ bool order_below(const double q[5], double t
     const double m2 = a * e - b * b;
     const double m3 = g * m2 - (a * f * f + e * c * c + 2.0 * b * c * f);
     const double S = fabs(threshold) + sqrt(nrm), t1 = 1e-12 * S, t2 = t1 * S, t3 = t2 * S;
-    if (a > t1 && m2 > t2 && m3 > t3) return true;
-    if (a < -t1 || m2 < -t2 || m3 < -t3) return false;
+    if (S > 1e-90 && S < 1e90) {
+        if (a > t1 && m2 > t2 && m3 > t3) return true;
+        if (a < -t1 || m2 < -t2 || m3 < -t3) return false;
+    }
     double lam, d[3];
     order_site(q, lam, d);
     return lam < threshold;
