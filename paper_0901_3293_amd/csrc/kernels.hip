@@ -1396,7 +1396,8 @@ __global__ __launch_bounds__(BLK) void k_optics(Geom G, const T *__restrict__ Q,
         order_site(q5, qo, d);
         const double r2 = d[0] * d[0] + d[1] * d[1];
         double c = 1.0, sn = 0.0;
-        if (r2 > 0.0) {
+        // (closer to the beam the inverse overflows, and the retardance is zero to rounding about any axis)
+        if (r2 > 1e-290) {
             const double ir2 = 1.0 / r2;
             c = (d[0] * d[0] - d[1] * d[1]) * ir2;
             sn = 2.0 * d[0] * d[1] * ir2;
