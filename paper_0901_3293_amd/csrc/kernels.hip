@@ -1315,13 +1315,28 @@ __global__ __launch_bounds__(BLK) void k_count(Geom G, const T *__restrict__ Q, 
     if (threadIdx.x == 0) cnt[blockIdx.x] = total;
 }
 
+// sin and cos by the library (one copy, out of the way of the registers of the
+// kernel that needs it only for angles without a digit of phase).
+__device__ __attribute__((noinline)) double2 sincos_far(double x)
+{
+    double s, c;
+    sincos(x, &s, &c);
+    return make_double2(s, c);
+}
+
 // sin and cos of x: the Taylor sums up to pi/4 (rest under 1e-19), beyond it
-// after the nearest multiple of pi/2, in two parts, is taken off (exact to
-// 1e-17 up to 1e15).
+// after the nearest multiple of pi/2, in two parts, is taken off (rounded to
+// 6e-17, up to 1e14); past that by the library.
 __device__ __forceinline__ void sincos64(double x, double &sn, double &cs)
 {
     int n = 0;
     if (!(fabs(x) <= 0.785)) {
+        if (fabs(x) > 1e14) {
+            const double2 f = sincos_far(x);
+            sn = f.x;
+            cs = f.y;
+            return;
+        }
         const double k = rint(x * 0.63661977236758134308);  // 2 / pi
         x = fma(-k, 6.12323399573676588614e-17, fma(-k, 1.57079632679489661923, x));
         n = int((long long)k & 3);
@@ -1383,7 +1398,7 @@ __global__ __launch_bounds__(BLK) void k_optics(Geom G, const T *__restrict__ Q,
     for (int g = 0; g < OPT_G; ++g) {
         w[g] = 1.0;
         x[g] = y[g] = zq[g] = 0.0;
-        half[g] = g < ng ? 0.5 / op.lam[wl0 + g] : 0.0;
+        half[g] = g < ng ? fmin(0.5 / op.lam[wl0 + g], 1e308) : 0.0;  // finite: zero times it is zero
     }
     const double two_pi_h = 2.0 * 3.14159265358979323846 * op.h;
     const double no2 = op.n_o * op.n_o, ne2 = op.n_e * op.n_e, none = op.n_o * op.n_e;
