@@ -1596,21 +1596,6 @@ void with_block(int N, int cus, F &&f)
     })
 #define SWEEP(KERNEL, ...) SWEEP_OF(G.N, KERNEL, __VA_ARGS__)
 
-// z-chunk of the fused D3Q15 passes, the one that gives a CU two blocks (all that
-// are resident) at once; 0 where the two sweeps are the better: a chunk under six
-// planes repeats too many of them (64^3, four planes: 36 us a step and 33 in FP32,
-// but 68 and 74 in FP64; 48^3 26 and 28, 37 and 45), and so do tiles that hang
-// over the lattice by more than a quarter.
-template <typename T>
-int pass_chunk(const Geom &G, int cus)
-{
-    using S = PassTile<T>;
-    const long long cols = (long long)((G.nx + S::TX - 1) / S::TX) * ((G.ny + S::TY - 1) / S::TY);
-    if (4 * cols * S::NT > 5LL * G.nx * G.ny) return 0;
-    const int chunks = int(std::max(1LL, 2LL * cus / cols)), tz = (G.nz + chunks - 1) / chunks;
-    return tz >= 6 ? tz : 0;
-}
-
 template <typename T, bool SPLIT>
 hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *timer)
 {
@@ -1634,7 +1619,7 @@ hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *time
     const TileGrid tgq = tile_grid(G.nx, G.ny, G.nz, UpdateTile<T>::TX, UpdateTile<T>::TY, tile_tzq(D));
     const TileGrid tgw = tile_grid(G.nx, G.ny, G.nz, WideTile<T>::TX, WideTile<T>::TY, tile_tz(D));
     const bool wide = wide_tiles<T>(G.nx, G.ny, G.nz, cus);
-    const int tzp = pc ? pass_chunk<T>(G, cus) : 0;
+    const int tzp = pc ? pass_chunk<T>(G.nx, G.ny, G.nz, cus, SPLIT) : 0;
     const int tb = KernelTile<T>::NB;
     const bool pairs = sc == SCHED_SITES && small_lattice(G, cus);
     const int nbr = StepBrick::blocks(G), lbr = (nbr + 7) / 8 * 8;

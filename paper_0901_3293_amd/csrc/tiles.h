@@ -75,6 +75,46 @@ inline bool wide_tiles(int nx, int ny, int nz, int cus)
 template <typename T>
 using PassTile = typename std::conditional<sizeof(T) == 8, TileShape<32, 4>, TileShape<32, 8>>::type;
 
+// z-chunk of the fused D3Q15 passes, or 0 where the two sweeps are the better.
+// A CU evaluates its share of the blocks, each of the chunk's planes and two
+// more; of the chunks that give a CU two blocks or more (all that are resident;
+// with one its latencies show) the first is taken, or one with a tenth less to
+// evaluate per CU.  The sites evaluated, tiles that hang over the lattice and CUs
+// that wait for others included, over the sites there are tell which form is the
+// faster.  A step in us with the two sweeps and with this, split coupling, FP32:
+// 1.13 (128^3) 220 and 198, 1.26 (200^3) 1186 and 1157, 1.33 (96^3) 96 and 88, 1.36
+// (144^3) 358 and 344 (319 and 324 with the whole-stress force), 1.40 (112^3) 144
+// and 149, 1.46 (150 x 60 x 120) 117 and 124, 1.59 (140 x 100 x 100) 148 and 163;
+// FP64: 1.08 (192^3) 1957 and 1592, 1.25 (144^3) 815 and 697, 1.40 (112^3) 312 and 306,
+// 1.53 (300 x 50 x 120) 459 and 433.  Where a component's plane is no whole number
+// of 64-byte lines the sweeps' loads and stores straddle them, and more may be
+// evaluated: FP32 1.38 (61 x 159 x 127) 156 and 132, 1.43 (171 x 153 x 63) 215 and 188,
+// 1.56 (54 x 165 x 113) 123 and 112, 1.70 (106 x 155 x 47) 98 and 94; FP64 1.69
+// (81 x 58 x 91) 112 and 111 (107 and 104).  Tiles that hang over by more than a
+// quarter are left to the sweeps (100^3, FP64, 1.44: 216 and 220), and so are chunks
+// under six planes (64^3, four planes: 64 and 62, 35 and 34 in FP32).
+template <typename T>
+inline int pass_chunk(int nx, int ny, int nz, int cus, bool split)
+{
+    using S = PassTile<T>;
+    const long long N = (long long)nx * ny * nz;
+    const long long cols = (long long)((nx + S::TX - 1) / S::TX) * ((ny + S::TY - 1) / S::TY);
+    if (cus < 1 || 4 * cols * S::NT > 5LL * nx * ny) return 0;
+    int best = 0;
+    long long least = 0, first = 0;  // planes a CU evaluates
+    for (int c = cols < 2LL * cus ? int(2LL * cus / cols) : 1; (nz + c - 1) / c >= 6; ++c) {
+        const int tz = (nz + c - 1) / c;
+        const long long planes = (cols * ((nz + tz - 1) / tz) + cus - 1) / cus * (tz + 2);
+        if (!best) first = planes;
+        if (!best || (planes < least && 10 * planes <= 9 * first)) {
+            best = tz;
+            least = planes;
+        }
+    }
+    const int most = N * sizeof(T) % 64 ? 171 : (sizeof(T) == 8 ? 155 : (split ? 138 : 135));  // percent of N
+    return 100 * least * cus * S::NT <= most * N ? best : 0;
+}
+
 // The tile of the Q update, which is bound by its instructions and not by
 // memory: blocks of four waves, one to each SIMD, of which four share a CU in
 // FP32 (two in FP64).  In FP32 at 192^3: 32 x 8 (six waves, two blocks) 222 us,

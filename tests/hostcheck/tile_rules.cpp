@@ -1,0 +1,27 @@
+// Host build of the rules of tiles.h that choose a form of a step by the size of
+// the lattice, for tests/test_tile_rules.py.  argv: rule, precision (32, 64),
+// CUs, then nx ny nz of each lattice; prints one value a lattice.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+
+#include "../../paper_0901_3293_amd/csrc/tiles.h"
+
+template <typename T>
+static int rule(const char *name, int nx, int ny, int nz, int cus)
+{
+    if (!std::strcmp(name, "pass_chunk_force")) return hlb::pass_chunk<T>(nx, ny, nz, cus, false);
+    if (!std::strcmp(name, "pass_chunk_split")) return hlb::pass_chunk<T>(nx, ny, nz, cus, true);
+    return -1;
+}
+
+int main(int argc, char **argv)
+{
+    for (int i = 4; i + 2 < argc; i += 3) {
+        const int nx = std::atoi(argv[i]), ny = std::atoi(argv[i + 1]), nz = std::atoi(argv[i + 2]);
+        const int cus = std::atoi(argv[3]);
+        std::printf("%d\n", std::atoi(argv[2]) == 64 ? rule<double>(argv[1], nx, ny, nz, cus)
+                                                     : rule<float>(argv[1], nx, ny, nz, cus));
+    }
+    return 0;
+}

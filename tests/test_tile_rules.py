@@ -1,0 +1,49 @@
+"""The rules that choose a form of a step by the size of the lattice (tiles.h),
+on the host: lattices on which one form was measured the faster by 2% or more on
+256 CUs get it."""
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc not available")
+    exe = str(tmp_path_factory.mktemp("rules") / "tile_rules")
+    subprocess.check_call([HIPCC, "-O1", "-std=c++17", os.path.join(HERE, "hostcheck", "tile_rules.cpp"), "-o", exe],
+                          stderr=subprocess.DEVNULL)
+
+    def run(name, prec, shapes, cus=256):
+        out = subprocess.run([exe, name, str(prec), str(cus), *[str(n) for s in shapes for n in s]],
+                             capture_output=True, text=True, check=True).stdout
+        return [int(v) for v in out.split()]
+
+    return run
+
+
+FUSED = {32: [(128, 128, 128), (128, 128, 64), (96, 96, 96), (96, 128, 96), (120, 120, 120), (160, 160, 160),
+              (192, 192, 192), (200, 200, 200), (64, 64, 256), (61, 159, 127), (175, 149, 62), (170, 90, 111),
+              (54, 165, 113), (171, 153, 63)],
+         64: [(128, 128, 128), (128, 128, 64), (96, 96, 96), (96, 90, 48), (120, 120, 120), (144, 144, 144),
+              (160, 160, 160), (192, 192, 192), (200, 200, 200), (64, 64, 256), (140, 100, 100), (130, 130, 100),
+              (300, 50, 120), (64, 40, 160), (512, 4, 512), (81, 58, 91), (165, 122, 160)]}
+SWEEPS = {32: [(112, 112, 112), (300, 50, 120), (150, 60, 120), (140, 100, 100), (130, 130, 100), (100, 100, 100),
+               (72, 96, 120)],
+          64: [(100, 100, 100), (72, 96, 120)]}
+
+
+@pytest.mark.parametrize("coupling", ["force", "split"])
+@pytest.mark.parametrize("prec", [32, 64])
+def test_fused_passes_where_they_were_measured_faster(rule, prec, coupling):
+    name = "pass_chunk_" + coupling
+    for s, tz in zip(FUSED[prec], rule(name, prec, FUSED[prec])):
+        assert 6 <= tz <= s[2], s
+    assert not any(rule(name, prec, SWEEPS[prec]))
+    small = [(4, 4, 4), (32, 8, 5), (4, 4, 4096), (4096, 4, 4), (32, 32, 6), (1024, 1024, 4)]
+    assert all(tz == 0 or 6 <= tz <= s[2] for s, tz in zip(small, rule(name, prec, small)))
+    assert not any(rule(name, prec, FUSED[prec], cus=0))  # no device to ask
