@@ -1540,25 +1540,23 @@ int tz_fill_t(const Device &D, int rounds)
     const Geom &G = D.G;
     const int cus = device_cus();
     if (cus < 1) return 0;
-    long long slots = (long long)cus * rounds, cols;
-    if (wide_tiles<T>(G.nx, G.ny, G.nz, cus)) {
-        // the fused kernel's tile: at 128^3 FP32 15 planes, 137 us a step where 16 take 138
-        int bw = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bw, (k_qlb<T, false, W>), W::NB, 0) != hipSuccess) return 0;
-        slots *= std::max(1, bw);
-        cols = (long long)((G.nx + W::TX - 1) / W::TX) * ((G.ny + W::TY - 1) / W::TY);
-    } else {
-        int bq = 0, bf = 0, bl = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bq, k_qupdate<T>, UpdateTile<T>::NB, 0) != hipSuccess)
-            return 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bf, k_qforce<T, false>, S::NB, 0) != hipSuccess) return 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bl, (k_qlb<T, false, S>), S::NB, 0) != hipSuccess) return 0;
-        slots *= std::max(1, std::min(bq, std::min(bf, bl)));
-        cols = (long long)((G.nx + S::TX - 1) / S::TX) * ((G.ny + S::TY - 1) / S::TY);
-    }
-    const long long chunks = slots / cols;
-    if (chunks < 1) return 0;
-    return int((D.G.nz + chunks - 1) / chunks);
+    const long long slots = (long long)cus * rounds;
+    // chunk of tiles TX x TY of which a CU holds `per_cu`
+    auto fill = [&](int TX, int TY, int per_cu) {
+        const long long cols = (long long)((G.nx + TX - 1) / TX) * ((G.ny + TY - 1) / TY);
+        const long long chunks = slots * std::max(1, per_cu) / cols;
+        return chunks < 1 ? 0 : int((G.nz + chunks - 1) / chunks);
+    };
+    // the fused kernel's wide tile: at 128^3 FP32 15 planes, 137 us a step where 16 take 138
+    int bw = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bw, (k_qlb<T, false, W>), W::NB, 0) != hipSuccess) return 0;
+    const int tzw = fill(W::TX, W::TY, bw);
+    if (tzw > 0 && wide_tiles<T>(G.nx, G.ny, G.nz, cus, tzw)) return tzw;
+    int bq = 0, bf = 0, bl = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bq, k_qupdate<T>, UpdateTile<T>::NB, 0) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bf, k_qforce<T, false>, S::NB, 0) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bl, (k_qlb<T, false, S>), S::NB, 0) != hipSuccess) return 0;
+    return fill(S::TX, S::TY, std::min(bq, std::min(bf, bl)));
 }
 
 // Lattices whose per-site sweeps run in pairs over bricks: those of at most one
@@ -1618,7 +1616,7 @@ hipError_t steps_t(Device &D, const PhysParams &p, int nsteps, KernelTimer *time
     const TileGrid tg = tile_grid(G.nx, G.ny, G.nz, KernelTile<T>::TX, KernelTile<T>::TY, tile_tz(D));
     const TileGrid tgq = tile_grid(G.nx, G.ny, G.nz, UpdateTile<T>::TX, UpdateTile<T>::TY, tile_tzq(D));
     const TileGrid tgw = tile_grid(G.nx, G.ny, G.nz, WideTile<T>::TX, WideTile<T>::TY, tile_tz(D));
-    const bool wide = wide_tiles<T>(G.nx, G.ny, G.nz, cus);
+    const bool wide = wide_tiles<T>(G.nx, G.ny, G.nz, cus, std::min(G.nz, tile_tz(D)));
     const int tzp = pc ? pass_chunk<T>(G.nx, G.ny, G.nz, cus, SPLIT) : 0;
     const int tb = KernelTile<T>::NB;
     const bool pairs = sc == SCHED_SITES && small_lattice(G, cus);

@@ -56,19 +56,40 @@ struct TileShape {
 template <typename T>
 using KernelTile = typename std::conditional<sizeof(T) == 8, TileShape<16, 12>, TileShape<32, 8>>::type;
 
-// The tile of the fused stress and LB on large lattices whose rows it fills to a
-// tenth: 256 bytes a row, which the populations gain more from than the ring,
-// 1.44 to 1.59 points a site instead of 1.31, costs, once there are some 6000
-// sites a CU; with fewer its larger blocks do not fill the chip.  FP32 steps,
-// the narrow and the wide tile: 64^3 43 and 45 us, 128 x 64 x 64 52 and 55, 128^3
-// 142 and 139, 192^3 457 and 423, 256^3 1092 and 1035; FP64 128^3 277 and 264.
+// The tile of the fused stress and LB on large lattices: 256 bytes a row, which
+// the populations gain more from than the ring, 1.44 to 1.59 points a site instead
+// of 1.31, costs.  FP32 steps, the narrow and the wide tile, 16 planes a chunk:
+// 64^3 43 and 45 us, 128 x 64 x 64 52 and 55, 128^3 138 and 138, 192 x 192 x 64 176 and
+// 150, 192^3 457 and 423, 256^3 1092 and 1035; FP64 128^3 286 and 256.
 template <typename T>
 using WideTile = typename std::conditional<sizeof(T) == 8, TileShape<32, 4>, TileShape<64, 5>>::type;
+
+// Whether it is taken, for chunks of tz planes.  With few sites a CU its larger
+// blocks do not fill the chip: in FP64 it pays from 6000 sites a CU (128 x 128 x 100
+// 257 and 226 us; 512 x 11 x 256, 5632 a CU, 195 and 203), in FP32 as well with
+// chunks under 16 planes (192 x 64 x 130, 8 planes, 124 and 114; 16 planes 110 and
+// 116), else from 8000 unless its blocks leave CUs idle where a CU has one of the
+// others (128^3, 32 planes, 256 and 208 blocks, 145 and 156).  Its tiles may hang
+// over the rows by a tenth, and its five rows cover a tenth more than the narrow
+// tile's eight, a quarter more where chunks are short (512 x 6 x 512, eight rows and
+// ten: 109 and 121, 123 and 123 with 8 planes).  FP32 rows that are no whole number
+// of 64-byte lines cost the narrow tile more, whose every row of 32 starts or ends
+// inside a line: there the wide one is taken from 6000 sites a CU and up to a third
+// over (120^3 155 and 139, 150^3 377 and 310, 200^3 949 and 817, 61 x 159 x 180 172 and
+// 140; whole lines: 160^3, a fifth over, 278 and 260, but 248 and 261 with 32 planes).
 template <typename T>
-inline bool wide_tiles(int nx, int ny, int nz, int cus)
+inline bool wide_tiles(int nx, int ny, int nz, int cus, int tz)
 {
-    const int TX = WideTile<T>::TX;
-    return 10 * ((nx + TX - 1) / TX * TX - nx) <= nx && (long long)nx * ny * nz >= 6000LL * cus;
+    using W = WideTile<T>;
+    using S = KernelTile<T>;
+    const int cols = (nx + W::TX - 1) / W::TX, rows = (ny + W::TY - 1) / W::TY, chunks = (nz + tz - 1) / tz;
+    const int over = cols * W::TX - nx, narrow_cols = (nx + S::TX - 1) / S::TX, narrow_rows = (ny + S::TY - 1) / S::TY;
+    const bool lines = sizeof(T) == 8 || nx * sizeof(T) % 64 == 0, deep = sizeof(T) == 4 && tz >= 16;
+    const long long N = (long long)nx * ny * nz;
+    if ((lines ? 10 : 3) * over > nx || N < 6000LL * cus) return false;
+    if (20 * rows * W::TY > (deep ? 22 : 25) * narrow_rows * S::TY) return false;
+    if (!deep || !lines) return true;
+    return N >= 8000LL * cus && ((long long)cols * rows * chunks >= cus || (long long)narrow_cols * narrow_rows * chunks > cus);
 }
 
 // The tile of the fused D3Q15 passes (measured at k_pc).

@@ -1,6 +1,6 @@
 // Host build of the rules of tiles.h that choose a form of a step by the size of
-// the lattice, for tests/test_tile_rules.py.  argv: rule, precision (32, 64),
-// CUs, then nx ny nz of each lattice; prints one value a lattice.
+// the lattice, for tests/test_tile_rules.py.  argv: rule (with its
+// argument), precision (32, 64), CUs, then nx ny nz of each lattice; prints one value a lattice.
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -12,6 +12,7 @@ static int rule(const char *name, int nx, int ny, int nz, int cus)
 {
     if (!std::strcmp(name, "pass_chunk_force")) return hlb::pass_chunk<T>(nx, ny, nz, cus, false);
     if (!std::strcmp(name, "pass_chunk_split")) return hlb::pass_chunk<T>(nx, ny, nz, cus, true);
+    if (!std::strncmp(name, "wide_", 5)) return hlb::wide_tiles<T>(nx, ny, nz, cus, std::atoi(name + 5));
     return -1;
 }
 

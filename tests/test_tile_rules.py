@@ -47,3 +47,23 @@ def test_fused_passes_where_they_were_measured_faster(rule, prec, coupling):
     small = [(4, 4, 4), (32, 8, 5), (4, 4, 4096), (4096, 4, 4), (32, 32, 6), (1024, 1024, 4)]
     assert all(tz == 0 or 6 <= tz <= s[2] for s, tz in zip(small, rule(name, prec, small)))
     assert not any(rule(name, prec, FUSED[prec], cus=0))  # no device to ask
+
+
+# the fused stress and LB, chunks of 8, 16 and 32 planes
+WIDE = {32: {8: [(128, 128, 128), (192, 64, 130), (64, 64, 400), (150, 150, 150), (120, 120, 120), (100, 128, 130),
+                 (64, 16, 1700)],
+             16: [(128, 128, 128), (176, 176, 176), (192, 192, 64), (120, 120, 120), (150, 150, 150), (200, 200, 200),
+                  (100, 200, 200), (61, 159, 180), (58, 200, 200)],
+             32: [(176, 176, 176), (192, 192, 64), (150, 150, 150), (200, 200, 200), (120, 116, 160)]},
+        64: {tz: [(128, 128, 128), (128, 128, 100), (192, 64, 130), (512, 6, 512)] for tz in (8, 16, 32)}}
+NARROW = {32: {8: [(64, 64, 64), (128, 64, 64), (128, 128, 80), (192, 192, 40)],
+               16: [(64, 64, 64), (512, 6, 512), (512, 7, 512), (192, 64, 130), (192, 192, 48), (128, 128, 100)],
+               32: [(160, 160, 160), (128, 128, 128), (512, 8, 512), (192, 64, 130)]},
+          64: {tz: [(64, 64, 64), (512, 11, 256), (100, 200, 200)] for tz in (8, 16, 32)}}
+
+
+@pytest.mark.parametrize("prec", [32, 64])
+@pytest.mark.parametrize("tz", [8, 16, 32])
+def test_wide_tiles_where_they_were_measured_faster(rule, prec, tz):
+    assert all(rule(f"wide_{tz}", prec, WIDE[prec][tz]))
+    assert not any(rule(f"wide_{tz}", prec, NARROW[prec][tz]))
