@@ -507,16 +507,18 @@ int hlb_get_fz(hlb_ctx *c, double *fz)
     HLB_GUARD(c);
     if (!fz) return set_error(c, HLB_ERR_ARG, "fz is null");
     if (!c->have_fields) return set_error(c, HLB_ERR_STATE, "no fields set");
-    const int nz = c->D.G.nz, np = hlb::plane_parts(c->D.G);
-    std::vector<double> part(size_t(nz) * np);
+    const int nz = c->D.G.nz, np = hlb::fz_parts(c->D.G);
+    std::vector<double> part(np > 1 ? size_t(nz) * np : 0);
+    double *to = np > 1 ? part.data() : fz;
     HIP_TRY(c, hlb::run_fz(c->D, c->p, c->D.part));
-    HIP_TRY(c, hipMemcpyAsync(part.data(), c->D.part, part.size() * sizeof(double), hipMemcpyDeviceToHost, c->D.stream));
+    HIP_TRY(c, hipMemcpyAsync(to, c->D.part, size_t(nz) * np * sizeof(double), hipMemcpyDeviceToHost, c->D.stream));
     HIP_TRY(c, hipStreamSynchronize(c->D.stream));
-    for (int z = 0; z < nz; ++z) {
-        double s = 0.0;
-        for (int k = 0; k < np; ++k) s += part[size_t(z) * np + k];
-        fz[z] = s;
-    }
+    if (np > 1)
+        for (int z = 0; z < nz; ++z) {
+            double s = 0.0;
+            for (int k = 0; k < np; ++k) s += part[size_t(z) * np + k];
+            fz[z] = s;
+        }
     for (int z = 0; z < nz; ++z)
         if (!std::isfinite(fz[z])) return set_error(c, HLB_ERR_NONFINITE, "non-finite f(z) at z = %d", z);
     return HLB_OK;
@@ -537,7 +539,7 @@ int hlb_get_order(hlb_ctx *c, double threshold, double *q, double *dir3, unsigne
     unsigned char *df = reinterpret_cast<unsigned char *>(st + 4 * N + nz);
     const bool want_flags = defect || defects_z || n_defect;
     if (want_flags && !q && !dir3 && !defect) {  // counts only
-        const int np = hlb::plane_parts(c->D.G);
+        const int np = hlb::count_parts(c->D.G);
         std::vector<int> cnt(size_t(nz) * np);
         int *dn = reinterpret_cast<int *>(st);
         HIP_TRY(c, hlb::run_count(c->D, threshold, dn));

@@ -127,14 +127,15 @@ hipError_t run_readout(Device &D, const PhysParams &p, double *stage, double *to
 size_t readout_partials(const Geom &G);
 
 // Chunks each z-plane is cut into for run_fz and run_count.
-int plane_parts(const Geom &G);
+int fz_parts(const Geom &G);
+int count_parts(const Geom &G);
 
 // Sums of the free-energy density of the current Q over the chunks of every
-// plane, into device part[nz][plane_parts(G)].
+// plane, into device part[nz][fz_parts(G)].
 hipError_t run_fz(Device &D, const PhysParams &p, double *part);
 
 // Disclination sites (q < threshold) in the chunks of every plane, into device
-// cnt[nz][plane_parts(G)].
+// cnt[nz][count_parts(G)].
 hipError_t run_count(Device &D, double threshold, int *cnt);
 
 // Local order of the current Q into device buffers (any may be null; cnt

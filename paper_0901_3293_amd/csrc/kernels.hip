@@ -1256,17 +1256,25 @@ __global__ __launch_bounds__(BLK) void k_order(Geom G, const T *__restrict__ Q, 
     if (defect) defect[s] = lam < threshold ? 1 : 0;
 }
 
-// Chunks of `len` sites that a plane is cut into for the per-plane sums: 1024
-// sites, more where that would take over 16 chunks.
+// Chunks of `len` sites that a plane is cut into for the per-plane sums: about 1024
+// sites, more where that would take over 16 chunks.  Planes under 4096 sites stay
+// whole where there are enough of them for the chip (`whole`): their chunks, of
+// unequal size and an even number a plane, would all fall on the same XCDs.  f(z) of
+// 64 x 20 x 1300 sites in two chunks a plane and in one: 46 and 40 us a call, in FP64
+// 74 and 60; 512 x 6 x 512 43 and 38; 256 x 8 x 256 27 and 28; 64 x 64 x 512 in four and in
+// one 38 and 40.  Counts: 64 x 20 x 1300 33 and 30, 512 x 6 x 512 29 and 31.
 struct PlaneChunks {
     int len, n;
 };
 
-inline PlaneChunks plane_chunks(const Geom &G)
+constexpr int FZ_WHOLE = 384, COUNT_WHOLE = 1024;
+
+inline PlaneChunks plane_chunks(const Geom &G, int whole)
 {
     const int sxy = G.nx * G.ny;
+    const int most = sxy < 4096 && G.nz >= whole ? 1 : std::min(16, (sxy + 1023) / 1024);
     PlaneChunks c;
-    c.len = std::max(1024, ((sxy + 15) / 16 + BLK - 1) / BLK * BLK);
+    c.len = ((sxy + most - 1) / most + BLK - 1) / BLK * BLK;
     c.n = (sxy + c.len - 1) / c.len;
     return c;
 }
@@ -1758,7 +1766,7 @@ hipError_t readout_t(Device &D, const PhysParams &p, double *stage, double *tota
 template <typename T>
 hipError_t fz_t(Device &D, const PhysParams &p, double *part)
 {
-    const PlaneChunks pc = plane_chunks(D.G);
+    const PlaneChunks pc = plane_chunks(D.G, FZ_WHOLE);
     k_fz<T><<<D.G.nz * pc.n, BLK, 0, D.stream>>>(D.G, make_coef<T>(p), static_cast<const T *>(D.Q[D.qcur]), pc, part);
     return hipGetLastError();
 }
@@ -1792,11 +1800,12 @@ hipError_t run_order(Device &D, double threshold, double *q, double *dir, unsign
     return hipGetLastError();
 }
 
-int plane_parts(const Geom &G) { return plane_chunks(G).n; }
+int fz_parts(const Geom &G) { return plane_chunks(G, FZ_WHOLE).n; }
+int count_parts(const Geom &G) { return plane_chunks(G, COUNT_WHOLE).n; }
 
 hipError_t run_count(Device &D, double threshold, int *cnt)
 {
-    const PlaneChunks pc = plane_chunks(D.G);
+    const PlaneChunks pc = plane_chunks(D.G, COUNT_WHOLE);
     if (D.fp32)
         k_count<float><<<D.G.nz * pc.n, BLK, 0, D.stream>>>(D.G, static_cast<const float *>(D.Q[D.qcur]), threshold,
                                                             pc, cnt);
@@ -1823,8 +1832,8 @@ hipError_t run_fz(Device &D, const PhysParams &p, double *part)
 size_t partial_doubles(int nx, int ny, int nz)
 {
     // per-site blocks x 4 (readout moments) + per-site blocks (free energy),
-    // or the chunks of every z-plane (free-energy profile; at least 1024 sites
-    // each but the last)
+    // or the chunks of every z-plane (free-energy profile; at most one per 1024
+    // sites and one more a plane)
     return size_t(5) * site_blocks(nx * ny * nz) + size_t(nz) + 16;
 }
 

@@ -11,7 +11,7 @@ from tests.test_gpu_order import H, solver, special_field  # noqa: F401  (H: a f
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(13, 7, 9), (4, 4, 4), (32, 32, 5), (33, 32, 4), (45, 37, 6), (64, 64, 5), (160, 130, 4), (20, 64, 400)]
+SHAPES = [(13, 7, 9), (4, 4, 4), (32, 32, 5), (33, 32, 4), (45, 37, 6), (64, 64, 5), (160, 130, 4), (20, 64, 400), (36, 36, 1030)]
 
 
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
