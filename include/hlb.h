@@ -188,7 +188,8 @@ int hlb_get_totals_noalloc(hlb_ctx *ctx, double *mass, double *mom3, double *fre
 /* Free-energy profile along z: fz[z] = sum over the plane z of the
  * free-energy density (Eq. (1)) of the current Q, FP64, fixed-order per-plane
  * reduction; the domain-wall position of a slab run is read off this profile.
- * fz: host array of nz doubles.  Synchronises the stream. */
+ * fz: host array of nz doubles.  HLB_ERR_NOMEM if the host has no memory for the
+ * partial sums.  Synchronises the stream. */
 int hlb_get_fz(hlb_ctx *ctx, double *fz);
 
 /* Local order and disclinations of the current Q (Sec. 2.1): q[N] the largest
@@ -199,7 +200,8 @@ int hlb_get_fz(hlb_ctx *ctx, double *fz);
  * number of disclination sites per z-plane, *n_defect their total.  Computed
  * on the device in FP64 from the stored Q (cyclic Jacobi rotations); host
  * outputs, any of them NULL.  Errors: HLB_ERR_ARG for a non-finite threshold,
- * HLB_ERR_STATE without fields.  Synchronises the stream. */
+ * HLB_ERR_STATE without fields, HLB_ERR_NOMEM if the host has no memory for the
+ * partial counts.  Synchronises the stream. */
 int hlb_get_order(hlb_ctx *ctx, double threshold, double *q, double *dir3, unsigned char *defect,
                   long long *defects_z, long long *n_defect);
 

@@ -8,6 +8,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -508,8 +509,9 @@ int hlb_get_fz(hlb_ctx *c, double *fz)
     if (!fz) return set_error(c, HLB_ERR_ARG, "fz is null");
     if (!c->have_fields) return set_error(c, HLB_ERR_STATE, "no fields set");
     const int nz = c->D.G.nz, np = hlb::fz_parts(c->D.G);
-    std::vector<double> part(np > 1 ? size_t(nz) * np : 0);
-    double *to = np > 1 ? part.data() : fz;
+    std::unique_ptr<double[]> part(np > 1 ? new (std::nothrow) double[size_t(nz) * np] : nullptr);
+    if (np > 1 && !part) return set_error(c, HLB_ERR_NOMEM, "hlb_get_fz: no host memory for %d x %d sums", nz, np);
+    double *to = np > 1 ? part.get() : fz;
     HIP_TRY(c, hlb::run_fz(c->D, c->p, c->D.part));
     HIP_TRY(c, hipMemcpyAsync(to, c->D.part, size_t(nz) * np * sizeof(double), hipMemcpyDeviceToHost, c->D.stream));
     HIP_TRY(c, hipStreamSynchronize(c->D.stream));
@@ -540,10 +542,11 @@ int hlb_get_order(hlb_ctx *c, double threshold, double *q, double *dir3, unsigne
     const bool want_flags = defect || defects_z || n_defect;
     if (want_flags && !q && !dir3 && !defect) {  // counts only
         const int np = hlb::count_parts(c->D.G);
-        std::vector<int> cnt(size_t(nz) * np);
+        std::unique_ptr<int[]> cnt(new (std::nothrow) int[size_t(nz) * np]);
+        if (!cnt) return set_error(c, HLB_ERR_NOMEM, "hlb_get_order: no host memory for %d x %d counts", nz, np);
         int *dn = reinterpret_cast<int *>(st);
         HIP_TRY(c, hlb::run_count(c->D, threshold, dn));
-        HIP_TRY(c, hipMemcpyAsync(cnt.data(), dn, cnt.size() * sizeof(int), hipMemcpyDeviceToHost, c->D.stream));
+        HIP_TRY(c, hipMemcpyAsync(cnt.get(), dn, size_t(nz) * np * sizeof(int), hipMemcpyDeviceToHost, c->D.stream));
         HIP_TRY(c, hipStreamSynchronize(c->D.stream));
         long long total = 0;
         for (int z = 0; z < nz; ++z) {
