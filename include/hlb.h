@@ -283,14 +283,15 @@ enum { HLB_DEBUG_NAN_LDS = 1 };
 int hlb_set_debug(hlb_ctx *ctx, int flags);
 
 /* Autotuner: time trial_steps steps of every candidate schedule (per-site;
- * tiled, mixed, fused and fused-tiled with tz = 8, 16, 32 and the tz whose
- * tiled launch fills the device's resident block slots once or twice; only
+ * tiled, mixed, fused and fused-tiled with tz = 8, 16, 32 and the tz with which
+ * the blocks of the schedule's tiled stress kernel, or else of its tiled Q
+ * update, fill the device's resident block slots once or twice; only
  * the per-site and mixed schedules with the D3Q15 scheme, no tiled one with
  * the split coupling) on this context's lattice and precision with HIP events
  * on its stream, in two passes over the candidates (each scored by its faster
  * pass, 2 untimed steps before every trial), keep the fastest; if that is
- * HLB_SCHED_TILED or HLB_SCHED_FUSED_TILED, time the other chunks for the Q
- * update the same way (hlb_set_update_chunk) and keep a faster one; put the
+ * HLB_SCHED_TILED or HLB_SCHED_FUSED_TILED, time the Q update's own chunks
+ * the same way (hlb_set_update_chunk) and keep a faster one; put the
  * state back as it was (through a host copy of hlb_state_bytes bytes).
  * *best_ms_per_step (may be NULL) receives the winner's time per step.
  * Synchronises the stream. */

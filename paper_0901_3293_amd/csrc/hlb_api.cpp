@@ -379,21 +379,35 @@ int hlb_autotune(hlb_ctx *c, int trial_steps, double *best_ms_per_step)
     struct Cand {
         int sched, tz;
     };
-    // z-chunks of 8, 16 and 32 planes, and those whose tiled launches fill the
-    // device's resident block slots once or twice
-    int tzs[5] = {8, 16, 32, hlb::tile_tz_fill(c->D, 1), hlb::tile_tz_fill(c->D, 2)};
-    int ntz = 3;
-    for (int i = 3; i < 5; ++i) {
-        bool dup = tzs[i] < 1;
-        for (int j = 0; j < ntz; ++j) dup = dup || tzs[j] == tzs[i];
-        if (!dup) tzs[ntz++] = tzs[i];
-    }
-    const int tiledsc[4] = {HLB_SCHED_TILED, HLB_SCHED_MIXED, HLB_SCHED_FUSED, HLB_SCHED_FUSED_TILED};
+    // z-chunks of 8, 16 and 32 planes, and those with which a kernel's blocks fill
+    // the device's resident block slots once or twice
+    struct Chunks {
+        int tz[5], n;
+    };
+    auto chunks_of = [&](int kernel) {
+        Chunks t = {{8, 16, 32}, 3};
+        for (int rounds = 1; rounds <= 2; ++rounds) {
+            const int tz = hlb::tile_tz_fill(c->D, kernel, c->p.flow == HLB_FLOW_SPLIT, rounds);
+            bool dup = tz < 1;
+            for (int j = 0; j < t.n; ++j) dup = dup || t.tz[j] == tz;
+            if (!dup) t.tz[t.n++] = tz;
+        }
+        return t;
+    };
+    const Chunks update = chunks_of(hlb::K_QUPDATE);
+    // a schedule's chunk is that of its tiled stress kernel, or else of its Q update
+    const struct {
+        int sched;
+        Chunks chunks;
+    } tiledsc[4] = {{HLB_SCHED_TILED, chunks_of(hlb::K_QFORCE)},
+                    {HLB_SCHED_MIXED, update},
+                    {HLB_SCHED_FUSED, chunks_of(hlb::K_QLB)},
+                    {HLB_SCHED_FUSED_TILED, chunks_of(hlb::K_QLB)}};
     Cand cands[1 + 4 * 5];
     int NC = 0;
     cands[NC++] = {HLB_SCHED_SITES, 0};
-    for (int sc : tiledsc)
-        for (int j = 0; j < ntz; ++j) cands[NC++] = {sc, tzs[j]};
+    for (const auto &sc : tiledsc)
+        for (int j = 0; j < sc.chunks.n; ++j) cands[NC++] = {sc.sched, sc.chunks.tz[j]};
     hipEvent_t a, b;
     HIP_TRY(c, hipEventCreate(&a));
     HIP_TRY(c, hipEventCreate(&b));
@@ -447,19 +461,19 @@ int hlb_autotune(hlb_ctx *c, int trial_steps, double *best_ms_per_step)
     int pick_tzq = 0;
     if (pick.sched == HLB_SCHED_TILED || pick.sched == HLB_SCHED_FUSED_TILED) {
         double tq[5];
-        for (int j = 0; j < ntz; ++j) tq[j] = 1e300;
+        for (int j = 0; j < update.n; ++j) tq[j] = 1e300;
         for (int pass = 0; pass < 2; ++pass)
-            for (int j = 0; j < ntz; ++j) {
-                if (tzs[j] == pick.tz || (tzs[j] > c->D.G.nz && tzs[j] != 8)) continue;
+            for (int j = 0; j < update.n; ++j) {
+                if (update.tz[j] == pick.tz || (update.tz[j] > c->D.G.nz && update.tz[j] != 8)) continue;
                 double ms = 0.0;
-                const hipError_t e = trial(pick.sched, pick.tz, tzs[j], ms);
+                const hipError_t e = trial(pick.sched, pick.tz, update.tz[j], ms);
                 if (e != hipSuccess) return fail(e);
                 tq[j] = std::min(tq[j], ms);
             }
-        for (int j = 0; j < ntz; ++j)
+        for (int j = 0; j < update.n; ++j)
             if (tq[j] < best) {
                 best = tq[j];
-                pick_tzq = tzs[j];
+                pick_tzq = update.tz[j];
             }
     }
     (void)hipEventDestroy(a);

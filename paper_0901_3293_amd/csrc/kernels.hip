@@ -1537,34 +1537,30 @@ int device_cus()
     return cus;
 }
 
-// z-chunk for which the blocks of the tiled kernels fill the device's
-// resident block slots `rounds` times: a launch of whole rounds leaves no CU
-// idle at the end (0 if the tile columns alone exceed the slots).
-template <typename T>
-int tz_fill_t(const Device &D, int rounds)
+// z-chunk for which the blocks of a tiled kernel fill the device's resident block
+// slots `rounds` times: a launch of whole rounds leaves no CU idle at the end.
+template <class S, class K>
+int tz_fill_of(const Geom &G, K kernel, long long slots)
 {
-    using S = KernelTile<T>;
-    using W = WideTile<T>;
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, S::NB, 0) != hipSuccess) return 0;
+    return fill_chunk<S>(G.nx, G.ny, G.nz, slots * std::max(1, per_cu));
+}
+
+template <typename T, bool SPLIT>
+int tz_fill_t(const Device &D, int kernel, int rounds)
+{
     const Geom &G = D.G;
     const int cus = device_cus();
     if (cus < 1) return 0;
     const long long slots = (long long)cus * rounds;
-    // chunk of tiles TX x TY of which a CU holds `per_cu`
-    auto fill = [&](int TX, int TY, int per_cu) {
-        const long long cols = (long long)((G.nx + TX - 1) / TX) * ((G.ny + TY - 1) / TY);
-        const long long chunks = slots * std::max(1, per_cu) / cols;
-        return chunks < 1 ? 0 : int((G.nz + chunks - 1) / chunks);
-    };
-    // the fused kernel's wide tile: at 128^3 FP32 15 planes, 137 us a step where 16 take 138
-    int bw = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bw, (k_qlb<T, false, W>), W::NB, 0) != hipSuccess) return 0;
-    const int tzw = fill(W::TX, W::TY, bw);
-    if (tzw > 0 && wide_tiles<T>(G.nx, G.ny, G.nz, cus, tzw)) return tzw;
-    int bq = 0, bf = 0, bl = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bq, k_qupdate<T>, UpdateTile<T>::NB, 0) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bf, k_qforce<T, false>, S::NB, 0) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bl, (k_qlb<T, false, S>), S::NB, 0) != hipSuccess) return 0;
-    return fill(S::TX, S::TY, std::min(bq, std::min(bf, bl)));
+    if (kernel == K_QUPDATE) return tz_fill_of<UpdateTile<T>>(G, k_qupdate<T>, slots);
+    if (kernel == K_QFORCE) return tz_fill_of<KernelTile<T>>(G, k_qforce<T, false>, slots);
+    if (kernel != K_QLB) return 0;
+    // at 128^3 FP32 15 planes, 137 us a step where 16 take 138
+    const int tz = tz_fill_of<WideTile<T>>(G, k_qlb<T, SPLIT, WideTile<T>>, slots);
+    if (tz > 0 && wide_tiles<T>(G.nx, G.ny, G.nz, cus, tz)) return tz;
+    return tz_fill_of<KernelTile<T>>(G, k_qlb<T, SPLIT, KernelTile<T>>, slots);
 }
 
 // Lattices whose per-site sweeps run in pairs over bricks: those of at most one
@@ -1851,9 +1847,10 @@ hipError_t run_steps(Device &D, const PhysParams &p, int nsteps, KernelTimer *ti
     return D.fp32 ? steps_t<float, false>(D, p, nsteps, timer) : steps_t<double, false>(D, p, nsteps, timer);
 }
 
-int tile_tz_fill(const Device &D, int rounds)
+int tile_tz_fill(const Device &D, int kernel, bool split, int rounds)
 {
-    return D.fp32 ? tz_fill_t<float>(D, rounds) : tz_fill_t<double>(D, rounds);
+    if (split) return D.fp32 ? tz_fill_t<float, true>(D, kernel, rounds) : tz_fill_t<double, true>(D, kernel, rounds);
+    return D.fp32 ? tz_fill_t<float, false>(D, kernel, rounds) : tz_fill_t<double, false>(D, kernel, rounds);
 }
 
 hipError_t run_init(Device &D, const PhysParams &p, const double *stage)

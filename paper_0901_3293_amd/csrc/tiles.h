@@ -64,7 +64,16 @@ using KernelTile = typename std::conditional<sizeof(T) == 8, TileShape<16, 12>, 
 template <typename T>
 using WideTile = typename std::conditional<sizeof(T) == 8, TileShape<32, 4>, TileShape<64, 5>>::type;
 
-// Whether it is taken, for chunks of tz planes.  With few sites a CU its larger
+// z-chunk for which the tile columns S cut a lattice into fill `slots` resident
+// block slots and no more (0 if the columns alone exceed them).
+template <class S>
+inline int fill_chunk(int nx, int ny, int nz, long long slots)
+{
+    const long long cols = (long long)((nx + S::TX - 1) / S::TX) * ((ny + S::TY - 1) / S::TY), chunks = slots / cols;
+    return chunks < 1 ? 0 : int((nz + chunks - 1) / chunks);
+}
+
+// Whether the wide tile is taken, for chunks of tz planes.  With few sites a CU its larger
 // blocks do not fill the chip: in FP64 it pays from 6000 sites a CU (128 x 128 x 100
 // 257 and 226 us; 512 x 11 x 256, 5632 a CU, 195 and 203), in FP32 as well with
 // chunks under 16 planes (192 x 64 x 130, 8 planes, 124 and 114; 16 planes 110 and

@@ -31,7 +31,7 @@ hipError_t run_steps(Device &, const PhysParams &, int, KernelTimer *) { return 
 hipError_t run_readout(Device &, const PhysParams &, double *, double *, double *) { return hipErrorNotSupported; }
 size_t readout_partials(const Geom &) { return 0; }
 const char *kernel_name(int) { return nullptr; }
-int tile_tz_fill(const Device &, int) { return 0; }
+int tile_tz_fill(const Device &, int, bool, int) { return 0; }
 int fz_parts(const Geom &) { return 2; }
 int count_parts(const Geom &) { return 2; }
 hipError_t run_fz(Device &, const PhysParams &, double *) { return hipErrorNotSupported; }

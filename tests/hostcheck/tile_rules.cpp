@@ -12,6 +12,13 @@ static int rule(const char *name, int nx, int ny, int nz, int cus)
 {
     if (!std::strcmp(name, "pass_chunk_force")) return hlb::pass_chunk<T>(nx, ny, nz, cus, false);
     if (!std::strcmp(name, "pass_chunk_split")) return hlb::pass_chunk<T>(nx, ny, nz, cus, true);
+    // chunk of the Q update, the whole-stress kernel, the wide fused one with `argument` blocks a CU
+    if (!std::strncmp(name, "fill_update_", 12))
+        return hlb::fill_chunk<hlb::UpdateTile<T>>(nx, ny, nz, (long long)cus * std::atoi(name + 12));
+    if (!std::strncmp(name, "fill_stress_", 12))
+        return hlb::fill_chunk<hlb::KernelTile<T>>(nx, ny, nz, (long long)cus * std::atoi(name + 12));
+    if (!std::strncmp(name, "fill_wide_", 10))
+        return hlb::fill_chunk<hlb::WideTile<T>>(nx, ny, nz, (long long)cus * std::atoi(name + 10));
     if (!std::strncmp(name, "wide_", 5)) return hlb::wide_tiles<T>(nx, ny, nz, cus, std::atoi(name + 5));
     return -1;
 }

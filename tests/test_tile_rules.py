@@ -67,3 +67,23 @@ NARROW = {32: {8: [(64, 64, 64), (128, 64, 64), (128, 128, 80), (192, 192, 40)],
 def test_wide_tiles_where_they_were_measured_faster(rule, prec, tz):
     assert all(rule(f"wide_{tz}", prec, WIDE[prec][tz]))
     assert not any(rule(f"wide_{tz}", prec, NARROW[prec][tz]))
+
+
+TILES = {"update": {32: (16, 12), 64: (16, 12)}, "stress": {32: (32, 8), 64: (16, 12)}, "wide": {32: (64, 5), 64: (32, 4)}}
+
+
+@pytest.mark.parametrize("prec", [32, 64])
+@pytest.mark.parametrize("tile", list(TILES))
+@pytest.mark.parametrize("per_cu", [1, 2, 4, 8])
+def test_chunks_that_fill_the_device(rule, prec, tile, per_cu):
+    """The shallowest chunk with which a kernel's own tiles take no more than the slots."""
+    tx, ty = TILES[tile][prec]
+    shapes = [(128, 64, 128), (128, 128, 128), (192, 192, 192), (130, 130, 100), (96, 96, 96), (512, 6, 512), (61, 159, 180),
+              (4, 4, 4), (600, 600, 8)]
+    slots = 256 * per_cu
+    for (nx, ny, nz), tz in zip(shapes, rule(f"fill_{tile}_{per_cu}", prec, shapes)):
+        cols = -(-nx // tx) * -(-ny // ty)
+        assert (tz == 0) == (cols > slots)
+        if tz:
+            assert 1 <= tz <= nz and cols * -(-nz // tz) <= slots
+            assert tz == 1 or cols * -(-nz // (tz - 1)) > slots
