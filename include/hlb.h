@@ -198,8 +198,10 @@ int hlb_get_fz(hlb_ctx *ctx, double *fz);
  * positive; (0, 0, 1) where Q = 0), defect[N] = 1 where q < threshold (a
  * disclination site; the paper's runs use 0.19) else 0, defects_z[nz] the
  * number of disclination sites per z-plane, *n_defect their total.  Computed
- * on the device in FP64 from the stored Q (cyclic Jacobi rotations); host
- * outputs, any of them NULL.  Errors: HLB_ERR_ARG for a non-finite threshold,
+ * on the device in FP64 from the stored Q (Newton steps on the characteristic
+ * cubic and a column of the adjugate, cyclic Jacobi rotations where the two
+ * largest eigenvalues nearly coincide; counts alone from the signs of minors,
+ * with the same outcome at every site); host outputs, any of them NULL.  Errors: HLB_ERR_ARG for a non-finite threshold,
  * HLB_ERR_STATE without fields, HLB_ERR_NOMEM if the host has no memory for the
  * partial counts.  Synchronises the stream. */
 int hlb_get_order(hlb_ctx *ctx, double threshold, double *q, double *dir3, unsigned char *defect,

@@ -561,12 +561,15 @@ __global__ __launch_bounds__(Shape::NB) void k_qlb(Geom G, Coef<T> c, TileGrid t
 // plane p+2 is copied into the third staging slot meanwhile, so a plane takes
 // one barrier.  FP32: 127 registers and 40.8 kB, four blocks a CU; FP64: 208
 // and 81.6 kB, two.
-// Bound by issue: about 450 vector instructions a point and plane, of which the
-// ring and the two extra planes of a chunk repeat half.  FP32 at 192^3: 222 us
-// with 32 x 8 tiles staged through registers, 160 us now (590 MB of Q and u, 3.7
-// TB/s); at 128^3 65 and 53 us, where k_qpred and k_qcorr take 47.  FP64, staged
-// through registers into two slots and one buffer with two barriers a plane:
-// 96^3 55 us and now 46, 128^3 97 and 97, 192^3 297 and 279.
+// Bound neither by issue nor by memory alone: of its time at 128^3 vector issue
+// takes 0.58 in FP32 and 0.36 in FP64 (about 450 instructions a point and plane, of
+// which the ring and the two extra planes of a chunk repeat half), its 142 and 270 MB
+// at the rate of a copy 0.44 and 0.47, and a resident wave spends 0.37 and 0.34 in
+// waits (LDS, the copies, the barrier of a plane) and 0.17 and 0.20 for an issue slot.
+// FP32 at 192^3: 222 us with 32 x 8 tiles staged through registers, 160 us now (590
+// MB of Q and u, 3.7 TB/s); at 128^3 65 and 53 us, where k_qpred and k_qcorr take 47.
+// FP64, staged through registers into two slots and one buffer with two barriers a
+// plane: 96^3 55 us and now 46, 128^3 97 and 97, 192^3 297 and 279.
 template <typename T>
 __global__ __launch_bounds__(UpdateTile<T>::NB) void k_qupdate(Geom G, Coef<T> c, TileGrid tg,
                                                        const T *__restrict__ Qin, const T *__restrict__ u,
@@ -993,8 +996,9 @@ __global__ __launch_bounds__(B) void k_pc2(Geom G, Coef<T> c, const T *__restric
 // a plane; 99 registers in FP32, about 200 in FP64, two blocks a CU.
 // Bound by the path from the cache (36 loads a point and plane) and by latency:
 // 114 us at 128^3 in FP32, where k_pc1 and k_pc2 take 132.  A step in us with the
-// two passes and with this: 128^3 219 and 199 (64 x 5 tiles 204, 16 x 12 245,
-// 32 x 4 220), in FP64 524 and 472 (16 x 12 485); 96^3 96 and 90, 205 and 197.
+// two passes and with this, split coupling: 128^3 219 and 197 (with 64 x 5 tiles 5
+// more, 32 x 4 21, 16 x 12 46), in FP64 521 and 433 (16 x 12 13 more); 96^3 97 and 88,
+// 203 and 175.
 template <typename T, bool SPLIT>
 __global__ __launch_bounds__(PassTile<T>::NB) void k_pc(Geom G, Coef<T> c, TileGrid tg, const T *__restrict__ g,
                                                          const T *__restrict__ Pi, T *__restrict__ gout,
@@ -1383,8 +1387,8 @@ __device__ __forceinline__ void sincos64(double x, double &sn, double &cs)
 // for a group of up to OPT_G wavelengths: a thread multiplies the layers of its
 // segment (later layers on the left), then one thread per column and
 // wavelength the segments, out of LDS.  FP64 throughout.  Bound: the FP64
-// arithmetic (600 instructions per site), two waves per SIMD for its registers:
-// 49 us at 128^3, against 177 us with Jacobi sweeps and 3x3 matrices and 21 us
+// arithmetic (630 instructions per site), two waves per SIMD for its registers:
+// 50 us at 128^3, against 177 us with Jacobi sweeps and 3x3 matrices and 21 us
 // for a second kernel that composed the segments.
 constexpr int OPT_G = 3;
 
@@ -1571,6 +1575,7 @@ int tz_fill_t(const Device &D, int kernel, int rounds)
 // in FP64; 40^3 (600) 14.2 and 17.2, 19.7 and 25.8; 64^3 (2048) 26 and 32, 50 and
 // 65.  The brick: larger ones (8 x 8 x 4, 16 x 8 x 4) evaluate fewer face points,
 // but leave CUs idle on the lattices in question.
+// One limit for both pairs and precisions, below which all gain.
 typedef Brick<16, 4, 2> StepBrick;
 
 bool small_lattice(const Geom &G, int cus) { return StepBrick::blocks(G) <= cus; }

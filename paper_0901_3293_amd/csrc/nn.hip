@@ -449,9 +449,10 @@ int device_cus()
 // tile takes one barrier.
 //
 // Bound: the matrix cores, 46.7k cycles of MFMAs per SIMD and layer at 96^3
-// of about 77k cycles a wave lives (19 of 32 us; the kernel takes 42 us with
-// its launch and the write-back of its output, 1.16 PFLOP/s, against 62-72 us
-// before; 32 -> 16: 28 against 45 us).  The rest is the start of a block (its
+// of about 77k cycles a wave lives (19 of 32 us; in a network application the
+// kernel takes 42 us with its launch and the write-back of its output, 1.16
+// PFLOP/s, against 62-72 us before; 32 -> 16: 28 against 45 us; 48 and 32 under the
+// profiler).  The rest is the start of a block (its
 // weights and first brick) and the epilogues, which the two waves of a SIMD
 // reach together.  Nontemporal output stores measured 2% slower.
 //
@@ -763,7 +764,8 @@ hipError_t conv_launch(const Grid3 &g, const unsigned short *X, const unsigned s
 //
 // Bound: the matrix cores (19 us of MFMAs at 96^3) with the waits on loads
 // and barriers around them: 52 us per 32 -> 32 layer (0.94 PFLOP/s) against 120
-// us with 16 x 4 x 4 tiles staged between barriers, 32 -> 16 35 against 75 us.
+// us with 16 x 4 x 4 tiles staged between barriers, 32 -> 16 35 against 75 us (56
+// and 38 under the profiler).
 template <int COP>
 struct WgradShape {
     static constexpr int TX = 32, TY = 4, TZ = 2;

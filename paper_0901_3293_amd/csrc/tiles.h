@@ -145,9 +145,9 @@ inline int pass_chunk(int nx, int ny, int nz, int cus, bool split)
     return 100 * least * cus * S::NT <= most * N ? best : 0;
 }
 
-// The tile of the Q update, which is bound by its instructions and not by
-// memory: blocks of four waves, one to each SIMD, of which four share a CU in
-// FP32 (two in FP64).  In FP32 at 192^3: 32 x 8 (six waves, two blocks) 222 us,
+// The tile of the Q update, whose waves wait a third of their time (see
+// k_qupdate): blocks of four waves, one to each SIMD, of which four share a CU in
+// FP32 (two in FP64) and issue in turn.  In FP32 at 192^3: 32 x 8 (six waves, two blocks) 222 us,
 // 32 x 12 172, 16 x 12 166 (157 with the planes copied straight into LDS);
 // 24 x 7, 32 x 5, 20 x 10 and 64 x 6 were slower.
 template <typename T>
