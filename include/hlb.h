@@ -251,7 +251,7 @@ int hlb_set_state(hlb_ctx *ctx, const void *host_buf, size_t nbytes);
  * fused with the LB step (the force never leaves the CU), then the per-site
  * predictor and corrector.  HLB_SCHED_FUSED_TILED: the fused stress and LB
  * step, then the tiled predictor-corrector (two sweeps).  All give the same
- * step to rounding.  The default is HLB_SCHED_SITES.  With the D3Q15
+ * step to rounding, in FP32 with the D3Q19 scheme bit for bit.  The default is HLB_SCHED_SITES.  With the D3Q15
  * scheme, HLB_SCHED_TILED, HLB_SCHED_FUSED and HLB_SCHED_FUSED_TILED are
  * rejected (HLB_ERR_STATE), with the split coupling HLB_SCHED_TILED (its
  * stress kernel writes the whole-stress force; the fused kernel evaluates
@@ -269,7 +269,7 @@ int hlb_get_schedule(const hlb_ctx *ctx, int *schedule, int *tz);
 /* z-chunk of the tiled predictor-corrector (HLB_SCHED_TILED, HLB_SCHED_MIXED,
  * HLB_SCHED_FUSED_TILED) where it should differ from the schedule's tz
  * (0: the schedule's tz; hlb_set_schedule resets it to 0).  The step is the
- * same at any chunk to rounding (bitwise in FP64).  HLB_ERR_ARG for tzq < 0. */
+ * same at any chunk, bit for bit.  HLB_ERR_ARG for tzq < 0. */
 int hlb_set_update_chunk(hlb_ctx *ctx, int tzq);
 int hlb_get_update_chunk(const hlb_ctx *ctx, int *tzq);
 

@@ -690,11 +690,12 @@ __global__ __launch_bounds__(UpdateTile<T>::NB) void k_qupdate(Geom G, Coef<T> c
     };
     int p = B.z0 - 1;
     if constexpr (sizeof(T) == 4) {
-        for (; p + 1 <= B.z1; p += 2) {
+        for (; p <= B.z1; p += 2) {
             plane(p, qA, uA, WA, qB, uB, WB);
+            // an odd plane by this copy of the code too: one of its own would fuse other products
+            if (p + 1 > B.z1) break;
             plane(p + 1, qB, uB, WB, qA, uA, WA);
         }
-        if (p <= B.z1) plane(p, qA, uA, WA, qB, uB, WB);
     } else {
         // FP64: a second copy of the plane code costs more registers than the
         // copies of the plane state it saves

@@ -1,9 +1,11 @@
 """FP32 D3Q19 steps whose sweeps stand in for one another give the same bits: the
 paired sweeps over bricks and the single ones (a periodic cell, and the cell repeated
-along each axis to a lattice past the bricks), and the fused stress and LB, on narrow
-and on wide tiles, and the per-site stress and LB (both with the per-site Q update).
-The surrogate needs it: its jumps carry one rounding to 1e-4 within eight cycles, and
-a run of it is repeated on whichever of these the lattice and the schedule pick."""
+along each axis to a lattice past the bricks), the fused stress and LB, on narrow and
+on wide tiles, and the tiled stress against the per-site ones, and the tiled Q update,
+at chunks of odd and of even numbers of planes, against the per-site predictor and
+corrector.  The surrogate needs it: its jumps carry one rounding to 1e-4 within eight
+cycles, and a run of it is repeated on whichever of these the lattice and the
+autotuner pick."""
 import numpy as np
 import pytest
 
@@ -61,3 +63,17 @@ def test_fused_and_per_site(coupling):
             b = run(shape, Q, coupling, ("fused", tz), 5)
             for name, x, y in zip(("Q", "u", "rho"), a, b):
                 assert np.isfinite(x).all() and np.array_equal(x, y), (shape, tz, name)
+
+
+@pytest.mark.parametrize("coupling", ["force", "split", "off"])
+def test_tiled_update_and_per_site(coupling):
+    for shape in SHAPES:
+        Q = field(shape)
+        a = run(shape, Q, coupling, ("sites", 0), 6)
+        for sched, tz in (("mixed", 1), ("mixed", 5), ("fused-tiled", 8), ("fused-tiled", 15), ("tiled", 6), ("tiled", 7)):
+            if sched == "tiled" and coupling == "split":
+                continue
+            say("case: tiled update, same bits", shape, coupling, sched, tz)
+            b = run(shape, Q, coupling, (sched, tz), 6)
+            for name, x, y in zip(("Q", "u", "rho"), a, b):
+                assert np.isfinite(x).all() and np.array_equal(x, y), (shape, sched, tz, name)
