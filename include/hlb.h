@@ -251,11 +251,12 @@ int hlb_set_state(hlb_ctx *ctx, const void *host_buf, size_t nbytes);
  * fused with the LB step (the force never leaves the CU), then the per-site
  * predictor and corrector.  HLB_SCHED_FUSED_TILED: the fused stress and LB
  * step, then the tiled predictor-corrector (two sweeps).  All give the same
- * step to rounding, in FP32 with the D3Q19 scheme bit for bit.  The default is HLB_SCHED_SITES.  With the D3Q15
- * scheme, HLB_SCHED_TILED, HLB_SCHED_FUSED and HLB_SCHED_FUSED_TILED are
- * rejected (HLB_ERR_STATE), with the split coupling HLB_SCHED_TILED (its
- * stress kernel writes the whole-stress force; the fused kernel evaluates
- * the split terms and the split body force in its tiles). */
+ * step to rounding, in FP32 with the D3Q19 scheme bit for bit.  The default
+ * is HLB_SCHED_SITES.  With the D3Q15 scheme, HLB_SCHED_TILED,
+ * HLB_SCHED_FUSED and HLB_SCHED_FUSED_TILED are rejected (HLB_ERR_STATE),
+ * with the split coupling HLB_SCHED_TILED (its stress kernel writes the
+ * whole-stress force; the fused kernel evaluates the split terms and the
+ * split body force in its tiles). */
 enum {
     HLB_SCHED_SITES = 0,
     HLB_SCHED_TILED = 1,
